@@ -403,6 +403,18 @@ struct ScheduleBuilder {
     if (h->tile_policy == 5) return 4;
     return h->tile_policy == 1 ? 0 : (h->tile_policy == 2 && h->gdt >= 2) ? 2 : 1;
   }
+  // Whether every product of the launch reads 16-byte aligned operand columns,
+  // as the kernels with direct LDS loads need.  Tiles, pairs and work areas
+  // are; spike rows of a block padded by an odd number of rows (the direct
+  // reduced solve with full spikes) need not be.
+  bool operands_aligned(size_t q0) const {
+    uintptr_t bits = 0;
+    for (size_t q = q0; q < gemm.size(); ++q)
+      if (gemm[q].K > 0)
+        bits |= reinterpret_cast<uintptr_t>(gemm[q].A) | reinterpret_cast<uintptr_t>(gemm[q].B) |
+                (uintptr_t)gemm[q].lda * h->elt | (uintptr_t)gemm[q].ldb * h->elt;
+    return bits % 16 == 0;
+  }
   // GEMM launches: the requested tile, narrowed to the largest one every
   // problem of the launch fills (256 x 128 only for bf16 arithmetic, 128 x 128,
   // else 64 x 64); assigns each problem its first workgroup.
@@ -414,6 +426,7 @@ struct ScheduleBuilder {
       else if (mode == 2 && gemm[q].M < 256) mode = 1;
       else if (mode == 4 && (gemm[q].M < 256 || gemm[q].N < 256)) mode = 3;
     }
+    if (h->gdt < 2 && !operands_aligned((size_t)off)) mode = -1;
     int BM, BN;
     gemm_tile_shape(h->gdt, mode, &BM, &BN);
     nwg = 0;

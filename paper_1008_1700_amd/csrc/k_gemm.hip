@@ -1,23 +1,23 @@
 // Grouped GEMM on CDNA4 matrix cores: D = C0 +/- op(A) op(B) over a list of
 // independent problems (one launch covers every block of the partition).
 //
-// Three kernels: k_gemm_std (f64 / f32 MFMA 16x16x4), k_gemm_bf16 (bf16 MFMA
-// on FP32 operands staged through registers) and k_gemm_dl (the same bf16
-// products with the operands copied straight into LDS).  For k_gemm_std the
-// workgroup tile is BM x BN (64 x 64 or 128 x 128), 256 threads = 4 waves in
-// a 2 x 2 arrangement, each wave a (BM/2) x (BN/2) sub-tile of 16 x 16 MFMA
-// blocks; K advances in chunks of 16 staged through LDS, with the next
-// chunk's global loads in flight while the current chunk is multiplied.  Operands are column-major (LAPACK layout); M and N need
-// only be multiples of 64 (a 128-tile on the edge is masked).  Triangular
-// operands are exploited twice: the K range of each output tile is clipped
-// to where both operands can be nonzero, and masked loads read the
-// unit-lower / upper halves of the packed inverse tiles.
+// k_gemm_dma: f64 / f32 MFMA 16x16x4, operands copied from global memory
+// straight into LDS.  k_gemm_std: the same products with element loads, for
+// operands that are not 16-byte aligned.  k_gemm_bf16 (bf16 MFMA on FP32
+// operands staged through registers) and k_gemm_dl (the same bf16 products
+// with the operands copied straight into LDS).  Operands are column-major
+// (LAPACK layout); M and N need only be multiples of 64 (a larger tile on the
+// edge is masked).  Triangular operands are exploited twice: the K range of
+// each output tile is clipped to where both operands can be nonzero, and
+// masks read the unit-lower / upper / lower halves of the packed tiles.
 //
 // The MFMA is fed with B^T as its first and A^T as its second operand, so it
 // accumulates D^T: the 16 lanes of a lane group hold 16 consecutive rows of
 // one column of D, and the stores to the column-major D are 64-128-byte
 // segments.
 #include "ddps_internal.h"
+
+#include <type_traits>
 
 namespace ddps {
 
@@ -116,7 +116,10 @@ __device__ __forceinline__ TileCoord tile_of(const GemmProb& P, int wg) {
 }
 
 // ------------------------------------------------------------------------
-// f64 / f32: K chunk 16, one MFMA 16x16x4 per (k4, mi, ni).
+// f64 / f32 with element loads (any alignment): 256 threads = 4 waves in a
+// 2 x 2 arrangement, each wave a (BM/2) x (BN/2) sub-tile of 16 x 16 MFMA
+// blocks; K advances in chunks of 16 staged through LDS, with the next
+// chunk's global loads in flight while the current chunk is multiplied.
 // ------------------------------------------------------------------------
 template <typename T, int BM, int BN, int BK = 16, int OCC = 1>
 __global__ __launch_bounds__(256, OCC) void k_gemm_std(const GemmProb* __restrict__ probs, int nprob,
@@ -677,21 +680,261 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_dl(const GemmProb* __rest
                        I0 + BM <= P.M && J0 + BN <= P.N);
 }
 
+// ------------------------------------------------------------------------
+// f64 / f32 with the operands copied from global memory straight into LDS
+// (global_load_lds_dwordx4) and no vector instruction between them and the
+// products.  Workgroup tile BM x BN (128 x 128 or 64 x 64), 4 waves 2 x 2; a
+// K chunk is 128 bytes deep (16 doubles, 32 floats), two LDS stages.
+//   A as [k][m]: one wave instruction fills 1 KiB (1, 2 or 4 rows of k), the
+//     next one starts kPadA bytes later, so that the two k rows of a 32-lane
+//     read pass lie in different banks;
+//   B as [n][k]: one wave instruction fills 8 columns of 128 bytes; slot s of
+//     column n holds the 16-byte k piece s ^ (n >> 1 & 7).
+// Lane group g = lane / 16 takes the chunk's k in [g kq, (g + 1) kq), one per
+// product (kq = 4 doubles, 8 floats), so its B entries are two 16-byte reads,
+// and the lane's two rows of A are adjacent: an accumulator pair holds rows
+// 2i, 2i + 1 and is stored as one vector.  Wave (wm, wn) owns rows 64 h +
+// 32 wm + [0, 32) and columns 64 h + 32 wn + [0, 32), h < BM / 64: a tile
+// with only 64 rows or columns inside the problem does half the products on
+// every wave.
+//
+// Bound: the matrix pipe (64 cycles per f64 MFMA, 32 per f32; a loop of
+// products alone runs at 74.5 / 154 TF/s).  Element loads spent a quarter of
+// the time on addresses, masks and register staging that the pipe waited
+// for.  32 problems, TF/s before -> now: dense 1600^3 f64 48 -> 68, f32 93 ->
+// 127; upper triangle times 1600 x 3200 f64 45 -> 60, f32 95 -> 117; rank-256
+// update of 1344^2 f64 40 -> 57, f32 76 -> 100.
+// ------------------------------------------------------------------------
+template <typename T, int BM, int BN>
+struct DmaTile {
+  static constexpr int VE = 16 / (int)sizeof(T);            // entries per 16 bytes
+  static constexpr int BK = 128 / (int)sizeof(T);
+  static constexpr int KQ = BK / 4;                         // k per lane group
+  static constexpr int RPI = 1024 / (BM * (int)sizeof(T));  // k rows per A instruction
+  static constexpr int kPadA = sizeof(T) == 8 ? 0 : (BM == 128 ? 32 : 64);
+  static constexpr int kRowGroup = 1024 + kPadA;
+  static constexpr int kBytesA = BK / RPI * kRowGroup;
+  static constexpr int kBytesB = BN * 128;
+  static constexpr int NA = BK / RPI / 4, NB = BN / 32;     // instructions per wave and chunk
+  static constexpr int H = BM / 64, HN = BN / 64;
+  static __device__ __forceinline__ int a_row(int k) {
+    return k / RPI * kRowGroup + (k % RPI) * (BM * (int)sizeof(T));
+  }
+};
+
+// One chunk: the products of the stage cur, the DMA of the next chunk into
+// nxt.  The two are restrict so that the reads do not wait for the DMA.  HM,
+// HN: 64-row and 64-column groups inside the problem.
+template <typename T, int BM, int BN, int HM, int HN>
+__device__ __forceinline__ void dma_chunk(const char* __restrict__ cur, char* __restrict__ nxt,
+                                          const char* __restrict__ ga, const char* __restrict__ gb,
+                                          const int64_t (&offa)[DmaTile<T, BM, BN>::NA],
+                                          const int64_t (&offb)[DmaTile<T, BM, BN>::NB], bool issue_next, int wa, int wb,
+                                          int fa, const int (&fb)[2],
+                                          typename Mma<T>::acc (&acc)[BM / 64][2][BN / 32]) {
+  using D = DmaTile<T, BM, BN>;
+  typedef T vec2 __attribute__((ext_vector_type(2)));
+  typedef T vecb __attribute__((ext_vector_type(D::VE)));
+  if (issue_next) {
+#pragma unroll
+    for (int q = 0; q < D::NA; ++q)
+      __builtin_amdgcn_global_load_lds((dma_src_t)(ga + offa[q]), (dma_dst_t)(nxt + wa + q * D::kRowGroup), 16, 0, 0);
+#pragma unroll
+    for (int q = 0; q < D::NB; ++q)
+      __builtin_amdgcn_global_load_lds((dma_src_t)(gb + offb[q]), (dma_dst_t)(nxt + wb + q * 1024), 16, 0, 0);
+  }
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    vecb b[2 * HN];
+#pragma unroll
+    for (int n = 0; n < 2 * HN; ++n) b[n] = *(const vecb*)(cur + fb[p] + (n >> 1) * 8192 + (n & 1) * 2048);
+#pragma unroll
+    for (int e = 0; e < D::VE; ++e) {
+      vec2 a[HM];
+#pragma unroll
+      for (int h = 0; h < HM; ++h)
+        a[h] = *(const vec2*)(cur + fa + D::a_row(D::VE * p + e) + h * 64 * (int)sizeof(T));
+#pragma unroll
+      for (int h = 0; h < HM; ++h)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int n = 0; n < 2 * HN; ++n) acc[h][q][n] = Mma<T>::run(b[n][e], a[h][q], acc[h][q][n]);
+    }
+  }
+}
+
+template <typename T, int BM, int BN, int OCC>
+__global__ __launch_bounds__(256, OCC) void k_gemm_dma(const GemmProb* __restrict__ probs, int nprob,
+                                                       const int32_t* __restrict__ order) {
+  using D = DmaTile<T, BM, BN>;
+  using acc_t = typename Mma<T>::acc;
+  typedef T vec2 __attribute__((ext_vector_type(2)));
+  __shared__ __attribute__((aligned(1024))) char lds[2][D::kBytesA + D::kBytesB];
+  const int wg = order ? order[xcd_swizzle(blockIdx.x, gridDim.x)] : xcd_swizzle(blockIdx.x, gridDim.x);
+  const GemmProb P = probs[find_prob(probs, nprob, wg)];
+  const TileCoord tc = tile_of<BM, BN>(P, wg);
+  const int I0 = tc.I0, J0 = tc.J0, kb = tc.kb, ke = tc.ke;
+  const int fl = P.flags;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave & 1, wn = wave >> 1;
+  const int li = lane & 15, g = lane >> 4;
+  acc_t acc[D::H][2][2 * D::HN];
+#pragma unroll
+  for (int h = 0; h < D::H; ++h)
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int n = 0; n < 2 * D::HN; ++n) acc[h][q][n] = acc_t{0, 0, 0, 0};
+
+  // 64: the two 64-row groups are taken in reverse order (lower triangular A)
+  const int flip = D::H == 2 && (fl & G_A_LO) && I0 + BM <= P.M ? 64 : 0;
+  if (kb < ke) {
+    const bool a_lu = fl & G_A_MLU, a_up = fl & G_A_MUP, b_lu = fl & G_B_MLU, b_up = fl & G_B_MUP;
+    const bool a_lo = fl & G_A_MLO, b_lo = fl & G_B_MLO;
+    // byte offsets of the lane's 16-byte pieces from the chunk's first row of
+    // k (A) and first k (B); rows and columns past the problem re-read its
+    // last ones (they only feed outputs that are not stored)
+    int64_t offa[D::NA], offb[D::NB];
+    const int64_t lda8 = (int64_t)P.lda * (int)sizeof(T), ldb8 = (int64_t)P.ldb * (int)sizeof(T);
+    const int am = ((lane * D::VE) % BM) ^ flip, ak = (lane * D::VE) / BM;
+#pragma unroll
+    for (int q = 0; q < D::NA; ++q)
+      offa[q] = ((wave * D::NA + q) * D::RPI + ak) * lda8 + (int64_t)min(I0 + am, P.M - D::VE) * (int)sizeof(T);
+#pragma unroll
+    for (int q = 0; q < D::NB; ++q) {
+      const int n = 8 * (wave * D::NB + q) + (lane >> 3);
+      offb[q] = min(J0 + n, P.N - 1) * ldb8 + 16 * ((lane & 7) ^ ((n >> 1) & 7));
+    }
+    const char* A = (const char*)P.A + kb * lda8;
+    const char* B = (const char*)P.B + (int64_t)kb * (int)sizeof(T);
+    // fragment addresses
+    const int fa = D::a_row(D::KQ * g) + (32 * wm + 2 * li) * (int)sizeof(T);
+    const int nb = 32 * wn + li;
+    const int fb[2] = {D::kBytesA + nb * 128 + (((2 * g) ^ ((nb >> 1) & 7)) << 4),
+                       D::kBytesA + nb * 128 + (((2 * g + 1) ^ ((nb >> 1) & 7)) << 4)};
+    const int wa = wave * D::NA * D::kRowGroup, wb = D::kBytesA + wave * D::NB * 1024;
+#pragma unroll
+    for (int q = 0; q < D::NA; ++q)
+      __builtin_amdgcn_global_load_lds((dma_src_t)(A + offa[q]), (dma_dst_t)(lds[0] + wa + q * D::kRowGroup), 16, 0, 0);
+#pragma unroll
+    for (int q = 0; q < D::NB; ++q)
+      __builtin_amdgcn_global_load_lds((dma_src_t)(B + offb[q]), (dma_dst_t)(lds[0] + wb + q * 1024), 16, 0, 0);
+    // chunks [k0, kend) with the first 64 HM rows and 64 HN columns
+    int st = 0, k0 = kb;
+    auto steps = [&](auto hm, auto hn, int kend) __attribute__((always_inline)) {
+      for (; k0 < kend; k0 += D::BK) {
+        __syncthreads();   // chunk k0 has landed; every wave is done with the other stage
+        const bool ma = (a_lu || a_up || a_lo) && k0 + D::BK > I0 && k0 < I0 + BM;
+        const bool mb = (b_lu || b_up || b_lo) && k0 + D::BK > J0 && k0 < J0 + BN;
+        if (ma || mb) {
+          if (ma)
+            for (int i = tid; i < D::BK * BM; i += 256) {
+              const int k = i / BM, m = i % BM;
+              T* e = (T*)(lds[st] + D::a_row(k) + m * (int)sizeof(T));
+              *e = select_op(*e, I0 + (m ^ flip), k0 + k, a_lu, a_up, a_lo, 1 << 30, 1 << 30);
+            }
+          if (mb)
+            for (int i = tid; i < BN * D::BK; i += 256) {
+              const int n = i / D::BK, k = i % D::BK;
+              T* e = (T*)(lds[st] + D::kBytesA + n * 128 + (((k / D::VE) ^ ((n >> 1) & 7)) << 4)) + k % D::VE;
+              *e = select_op(*e, k0 + k, J0 + n, b_lu, b_up, b_lo, 1 << 30, 1 << 30);
+            }
+          __syncthreads();
+        }
+        A += D::BK * lda8;
+        B += 128;
+        dma_chunk<T, BM, BN, decltype(hm)::value, decltype(hn)::value>(lds[st], lds[st ^ 1], A, B, offa, offb,
+                                                                       k0 + D::BK < ke, wa, wb, fa, fb, acc);
+        st ^= 1;
+      }
+    };
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, D::H>;
+    if constexpr (D::H == 2 && D::HN == 2) {
+      // the second group takes part where it is inside the problem and, with
+      // an upper A, from the k on that reaches its rows; with a lower A it
+      // holds the tile's first rows and leaves when k has passed them
+      const int k1 = I0 + 64 >= P.M ? ke : (fl & G_A_UP) ? min(ke, I0 + 64) : kb;
+      const int k2 = flip ? min(ke, I0 + 64) : ke;
+      if (J0 + 64 < P.N) {
+        steps(I1{}, I2{}, k1);
+        steps(I2{}, I2{}, k2);
+        steps(I1{}, I2{}, ke);
+      } else {
+        steps(I1{}, I1{}, k1);
+        steps(I2{}, I1{}, k2);
+        steps(I1{}, I1{}, ke);
+      }
+    } else {
+      steps(I2{}, I2{}, ke);
+    }
+  }
+
+  // lane: rows r, r + 1 of the columns c + Mma::row(lane, v)
+  gptr<T> C0 = (gptr<T>)P.C0;
+  gmut<T> Dp = (gmut<T>)P.D;
+  const bool has_c0 = fl & G_C0;
+  const T sg = (fl & G_NEG) ? T(-1) : T(1);
+  // whole pairs in one access where the addresses allow it
+  const uintptr_t al = (uintptr_t)P.D | (uintptr_t)P.ldd * sizeof(T) |
+                       (has_c0 ? (uintptr_t)P.C0 | (uintptr_t)P.ldc0 * sizeof(T) : 0);
+  const bool vec = (al & (2 * sizeof(T) - 1)) == 0 && !(fl & (G_D_UP | G_D_LO));
+#pragma unroll
+  for (int h = 0; h < D::H; ++h) {
+    const int r = I0 + ((64 * h) ^ flip) + 32 * wm + 2 * li;
+    if (r >= P.M) continue;
+#pragma unroll
+    for (int n = 0; n < 2 * D::HN; ++n) {
+      const int c = J0 + 64 * (n >> 1) + 32 * wn + 16 * (n & 1);
+      if (c >= P.N) continue;
+      if (vec) {
+        vec2 cv[4];
+        if (has_c0) {
+#pragma unroll
+          for (int v = 0; v < 4; ++v) cv[v] = *(gptr<vec2>)(C0 + (int64_t)(c + Mma<T>::row(lane, v)) * P.ldc0 + r);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          vec2 o = {sg * acc[h][0][n][v], sg * acc[h][1][n][v]};
+          if (has_c0) o = vec2{o[0] + cv[v][0], o[1] + cv[v][1]};
+          *(gmut<vec2>)(Dp + (int64_t)(c + Mma<T>::row(lane, v)) * P.ldd + r) = o;
+        }
+      } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const int cc = c + Mma<T>::row(lane, v);
+            if (!store_ok(fl, r + q, cc)) continue;
+            T val = sg * acc[h][q][n][v];
+            if (has_c0) val += C0[(int64_t)cc * P.ldc0 + r + q];
+            Dp[(int64_t)cc * P.ldd + r + q] = val;
+          }
+      }
+    }
+  }
+}
+
 // mode: 0 = 64 x 64 tiles, 1 = 128 x 128 tiles, 2 = 256 x 128 tiles (bf16 only),
 // 3 = 128 x 128 tiles with direct LDS loads (bf16 only; otherwise as 1),
-// 4 = 256 x 256 tiles on 8 waves with direct LDS loads (bf16 only; otherwise as 1)
+// 4 = 256 x 256 tiles on 8 waves with direct LDS loads (bf16 only; otherwise as 1),
+// -1 = f64 / f32 operands that are not 16-byte aligned (64 x 64 tiles, element loads)
 void launch_gemm(int dtype, int mode, const GemmProb* probs, int nprob, int nwg, hipStream_t s,
                  const int32_t* order) {
   if (nwg <= 0 || nprob <= 0) return;
   const dim3 g(nwg), b(256);
-  // two workgroups per CU (two waves per SIMD) measured best for f64/f32
   if (dtype <= 1) {
-    if (mode >= 1) {
-      if (dtype == 0) hipLaunchKernelGGL((k_gemm_std<double, 128, 128, 16, 2>), g, b, 0, s, probs, nprob, order);
-      else hipLaunchKernelGGL((k_gemm_std<float, 128, 128, 16, 2>), g, b, 0, s, probs, nprob, order);
-    } else {
+    if (mode < 0) {
       if (dtype == 0) hipLaunchKernelGGL((k_gemm_std<double, 64, 64, 16, 2>), g, b, 0, s, probs, nprob, order);
       else hipLaunchKernelGGL((k_gemm_std<float, 64, 64, 16, 2>), g, b, 0, s, probs, nprob, order);
+    } else if (mode >= 1) {
+      if (dtype == 0) hipLaunchKernelGGL((k_gemm_dma<double, 128, 128, 2>), g, b, 0, s, probs, nprob, order);
+      else hipLaunchKernelGGL((k_gemm_dma<float, 128, 128, 2>), g, b, 0, s, probs, nprob, order);
+    } else {
+      if (dtype == 0) hipLaunchKernelGGL((k_gemm_dma<double, 64, 64, 2>), g, b, 0, s, probs, nprob, order);
+      else hipLaunchKernelGGL((k_gemm_dma<float, 64, 64, 2>), g, b, 0, s, probs, nprob, order);
     }
     return;
   }
