@@ -276,14 +276,14 @@ int ddps_last_singular(ddps_handle h, int32_t* block, int64_t* row);
  * different groups factor concurrently; 0 = automatic), graph = 1 to capture
  * the factorisation once as a HIP graph and replay it, and tile_policy the
  * GEMM tile of each launch:
- *   0  128 x 128 where every problem of the launch allows it,
+ *   0  chosen for each launch by a rule on its sizes,
  *   1  64 x 64 only,
  *   2  256 x 128 where every problem allows it (bf16 arithmetic, else as 0),
  *   3  a tile chosen per launch by ddps_autotune (as 0 until it has run),
  *   4  128 x 128 with operands loaded straight into LDS (bf16 arithmetic,
  *      else as 0),
- *   5  256 x 256 on 8 waves, operands loaded straight into LDS (bf16
- *      arithmetic, else as 0; launches with a side below 256 take 4's tile).
+ *   5  256 x 256 on 8 waves (bf16 arithmetic, else as 0; launches with a
+ *      side below 256 take 4's tile).
  * Rebuilds the launch schedules; call before ddps_factor.  Errors:
  * DDPS_E_ARG, DDPS_E_NOMEM, DDPS_E_HIP. */
 int ddps_set_execution(ddps_handle h, int32_t streams, int32_t graph, int32_t tile_policy);

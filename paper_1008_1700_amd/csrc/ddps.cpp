@@ -28,6 +28,7 @@
 #include <cstdio>
 #include <cstring>
 #include <limits>
+#include <map>
 #include <new>
 #include <string>
 #include <vector>
@@ -173,9 +174,10 @@ struct ddps_ctx {
   std::vector<int> group_of;
   std::vector<Launch> sch_fwd, sch_bwd, sch_retr;
   int groups = 1;          // stream groups of the factor schedule
-  int tile_policy = 0;     // 0: 128 x 128 GEMM tiles where every problem allows, 1: 64 x 64 only,
+  int tile_policy = 0;     // 0: GEMM tile of each launch by a rule on its sizes, 1: 64 x 64 only,
                            // 2: 256 x 128 (bf16 arithmetic) where every problem allows,
-                           // 3: per launch, from mode_choice
+                           // 3: per launch, from mode_choice, 4 / 5: 128 x 128 / 256 x 256 with
+                           // direct LDS loads (bf16 arithmetic) where every problem allows
   std::vector<int8_t> mode_choice;  // policy 3: requested tile mode of each factor GEMM launch, in order
   int mode_cursor = 0;              // next factor GEMM launch while the schedules are built
   bool use_graph = false;  // capture ddps_factor once as a HIP graph, then replay it
@@ -395,13 +397,92 @@ struct ScheduleBuilder {
     gemv_aligned = true;
     off = k == LK_GEMM ? (int64_t)gemm.size() : k == LK_PANEL ? (int64_t)panel.size() : (int64_t)gemv.size();
   }
-  // Tile mode the policy asks for (0: 64 x 64, 1: 128 x 128, 2: 256 x 128).
+  // Tile mode the policy asks for; -2: by the size rule (auto_mode).
   int requested_mode() const {
     if (h->tile_policy == 3)
-      return h->mode_cursor < (int)h->mode_choice.size() ? h->mode_choice[h->mode_cursor] : 1;
+      return h->mode_cursor < (int)h->mode_choice.size() ? h->mode_choice[h->mode_cursor] : -2;
     if (h->tile_policy == 4) return 3;
     if (h->tile_policy == 5) return 4;
-    return h->tile_policy == 1 ? 0 : (h->tile_policy == 2 && h->gdt >= 2) ? 2 : 1;
+    return h->tile_policy == 1 ? 0 : (h->tile_policy == 2 && h->gdt >= 2) ? 2 : -2;
+  }
+  // Products of a tile at (I0, J0) of a problem, as K steps of a whole tile:
+  // its clipped K range times the part of its rows and columns inside the
+  // problem that the kernel of this mode computes.
+  double tile_work(const GemmProb& P, int mode, int BM, int BN, int I0, int J0) const {
+    int kb = 0, ke = P.K;
+    if (P.flags & G_A_UP) kb = std::max(kb, I0);
+    if (P.flags & G_B_LO) kb = std::max(kb, J0);
+    if (P.flags & G_A_LO) ke = std::min(ke, I0 + BM);
+    if (P.flags & G_B_UP) ke = std::min(ke, J0 + BN);
+    if (ke <= kb) return 0.0;
+    double part = 1.0;
+    const int rows = std::min(BM, P.M - I0), cols = std::min(BN, P.N - J0);
+    if (mode == 4) part = (double)((rows + 63) / 64 * 64) / BM * ((cols + 127) / 128 * 128) / BN;
+    else if (mode == 1 && h->gdt < 2) part = (double)rows / BM * cols / BN;
+    return (ke - kb) * part;
+  }
+  // Time of the launch (us) under a tile mode: per K step of a tile that has
+  // a CU to itself, per tile (its first loads and its stores, `slots` of
+  // which overlap on a CU), rounded up to whole rounds of the CUs a stream
+  // group can count on.  The constants are fits to launches of 32 problems
+  // (1344 x 1344 x 256 with C0: f64 128-tiles 524 us, 64-tiles 553; f32 302,
+  // 295; bf16x3 256-tiles 184, 128 176, 64 226; 2048 x 2048 x 1024: f64 3.90,
+  // 4.25 ms; bf16x3 0.72, 1.05, 1.74 ms; 256 x 256 x 256: f64 46, 28 us;
+  // bf16x3 25, 17, 16 us).
+  struct ModeCost {
+    int mode;
+    double per_k, per_tile, slots;
+  };
+  struct ShapeWork {
+    double tiles, work, longest;
+  };
+  std::map<std::array<int, 5>, ShapeWork> shape_work;   // (mode, M, N, K, flags)
+  double mode_time(const ModeCost& c) {
+    int BM, BN;
+    gemm_tile_shape(h->gdt, c.mode, &BM, &BN);
+    double tiles = 0, work = 0, longest = 0;
+    for (size_t q = (size_t)off; q < gemm.size(); ++q) {
+      const GemmProb& P = gemm[q];
+      auto it = shape_work.find({c.mode, P.M, P.N, P.K, P.flags});
+      if (it == shape_work.end()) {
+        ShapeWork w{0, 0, 0};
+        for (int I0 = 0; I0 < P.M; I0 += BM)
+          for (int J0 = 0; J0 < P.N; J0 += BN) {
+            const double k = tile_work(P, c.mode, BM, BN, I0, J0);
+            w.tiles += 1;
+            w.work += k;
+            w.longest = std::max(w.longest, k);
+          }
+        it = shape_work.insert({{c.mode, P.M, P.N, P.K, P.flags}, w}).first;
+      }
+      tiles += it->second.tiles;
+      work += it->second.work;
+      longest = std::max(longest, it->second.longest);
+    }
+    const double cus = std::max(32, 256 / std::max(1, h->groups));
+    return std::max(std::ceil(tiles / cus) * (work / tiles), longest) * c.per_k +
+           std::ceil(tiles / (cus * c.slots)) * c.per_tile;
+  }
+  // Large tiles read less per product and win where they fill the CUs a few
+  // times over; small ones win on short launches, on narrow problems and
+  // where a large tile's last round or edge is nearly empty.
+  int auto_mode() {
+    static const ModeCost f64[] = {{1, 0.1165, 14, 2}, {0, 0.0323, 9, 4}};
+    static const ModeCost f32[] = {{1, 0.0645, 5, 2}, {0, 0.0181, 3, 4}};
+    static const ModeCost x3[] = {{4, 0.0800, 14, 1}, {3, 0.0317, 8, 2}, {0, 0.0133, 4, 4}};
+    static const ModeCost x1[] = {{4, 0.0550, 14, 1}, {3, 0.0210, 8, 2}, {0, 0.0090, 4, 4}};
+    const ModeCost* c = h->gdt == 0 ? f64 : h->gdt == 1 ? f32 : h->gdt == 2 ? x3 : x1;
+    const int nc = h->gdt < 2 ? 2 : 3;
+    int best = 0;
+    double tbest = 1e300;
+    for (int q = 0; q < nc; ++q) {
+      const double t = mode_time(c[q]);
+      if (t < tbest) {
+        tbest = t;
+        best = c[q].mode;
+      }
+    }
+    return best;
   }
   // Whether every product of the launch reads 16-byte aligned operand columns,
   // as the kernels with direct LDS loads need.  Tiles, pairs and work areas
@@ -415,18 +496,28 @@ struct ScheduleBuilder {
                 (uintptr_t)gemm[q].lda * h->elt | (uintptr_t)gemm[q].ldb * h->elt;
     return bits % 16 == 0;
   }
-  // GEMM launches: the requested tile, narrowed to the largest one every
-  // problem of the launch fills (256 x 128 only for bf16 arithmetic, 128 x 128,
-  // else 64 x 64); assigns each problem its first workgroup.
+  // GEMM launches: the tile of the size rule, or the requested one narrowed to
+  // the largest one every problem of the launch fills (256 x 256 and
+  // 256 x 128 only for bf16 arithmetic, 128 x 128, else 64 x 64); assigns
+  // each problem its first workgroup.
   int finish_gemm() {
     int mode = requested_mode();
-    if (mode >= 2 && h->gdt < 2) mode = 1;
-    for (size_t q = (size_t)off; q < gemm.size(); ++q) {
-      if (gemm[q].M < 128 || gemm[q].N < 128) mode = 0;
-      else if (mode == 2 && gemm[q].M < 256) mode = 1;
-      else if (mode == 4 && (gemm[q].M < 256 || gemm[q].N < 256)) mode = 3;
+    if (mode == -2 && gemm.size() > (size_t)off) mode = auto_mode();
+    else {
+      if (mode >= 2 && h->gdt < 2) mode = 1;
+      for (size_t q = (size_t)off; q < gemm.size(); ++q) {
+        if (gemm[q].M < 128 || gemm[q].N < 128) mode = 0;
+        else if (mode == 2 && gemm[q].M < 256) mode = 1;
+        else if (mode == 4 && (gemm[q].M < 256 || gemm[q].N < 256)) mode = 3;
+      }
     }
-    if (h->gdt < 2 && !operands_aligned((size_t)off)) mode = -1;
+    if (mode != 0 || h->gdt < 2) {
+      // direct LDS loads need 16-byte aligned operand columns; the 256 x 256
+      // tile keeps 256 columns of B within a 32-bit byte offset
+      if ((h->gdt < 2 || mode >= 3) && !operands_aligned((size_t)off)) mode = h->gdt < 2 ? -1 : 0;
+      for (size_t q = (size_t)off; mode == 4 && q < gemm.size(); ++q)
+        if (gemm[q].ldb >= (1 << 22)) mode = 3;
+    }
     int BM, BN;
     gemm_tile_shape(h->gdt, mode, &BM, &BN);
     nwg = 0;
@@ -437,44 +528,76 @@ struct ScheduleBuilder {
       nwg += ((P.M + BM - 1) / BM) * ((P.N + BN - 1) / BN);
       flops += gemm_prob_flops(P, BM, BN);
     }
-    tile_order(BM, BN);
+    tile_order(mode, BM, BN);
     return mode;
   }
   // Dispatch order of the launch's tiles.  The kernels map workgroup b to
   // logical tile (b % 8) * (n / 8) + ... (a contiguous range per XCD, which
-  // the XCD's CUs take in order).  Where triangular operands make the tiles'
-  // K ranges unequal, each XCD's range is sorted longest first (stable), so
-  // the short tiles fill in at the end instead of a long one starting last;
-  // the XCD still gets the same tiles.  The kernel reads order[logical] for
-  // the tile to compute.  Plain launches keep the identity (cur_ord = -1).
-  void tile_order(int BM, int BN) {
+  // the XCD's CUs take in order).  Where triangular operands or partly filled
+  // edge tiles make the tiles' work unequal, each XCD's range is sorted
+  // longest first (stable), so that short tiles fill in at the end instead of
+  // a long one starting last, and so that a CU does not meet the same tile
+  // row over and over when the rows of a problem divide the XCD's CUs (f64,
+  // 64 problems: upper triangle times 1024 x 2048 2.82 ms, in the problems'
+  // order 3.32; lower times 1024^2 1.25 and 1.61).  The 256 x 256 tiles, one
+  // to a CU, are sorted in the last four rounds only: the tiles before them
+  // keep the order of the problem, in which neighbours share operand panels
+  // in the XCD's L2 (bf16x3, 64 problems: lower triangle times 1600 x 3200
+  // with C0 2.35 ms, all sorted 2.51; times 1600^2 1.05 and 1.13; upper times
+  // 1024 x 2048 0.61 and 0.59).  The kernel reads order[logical] for the tile
+  // to compute.  Launches of equal tiles keep the identity (cur_ord = -1).
+  void tile_order(int mode, int BM, int BN) {
     cur_ord = -1;
-    bool tri = false;
-    for (size_t q = (size_t)off; q < gemm.size(); ++q)
-      tri = tri || (gemm[q].flags & (G_A_UP | G_A_LO | G_B_UP | G_B_LO));
-    if (!tri || nwg < 2) return;
-    std::vector<int32_t> klen(nwg);
+    if (nwg < 2) return;
+    // each tile's rank among the launch's distinct amounts of work (0: most),
+    // from one pattern per problem shape
+    std::map<std::array<int, 4>, std::vector<int>> shapes;
+    std::map<float, int, std::greater<float>> rank;
     for (size_t q = (size_t)off; q < gemm.size(); ++q) {
       const GemmProb& P = gemm[q];
+      std::vector<int>& w = shapes[{P.M, P.N, P.K, P.flags}];
+      if (!w.empty()) continue;
       const int tm = (P.M + BM - 1) / BM, tn = (P.N + BN - 1) / BN;
+      w.resize((size_t)tm * tn);
       for (int l = 0; l < tm * tn; ++l) {
-        const int I0 = (l % tm) * BM, J0 = (l / tm) * BN;
-        int kb = 0, ke = P.K;
-        if (P.flags & G_A_UP) kb = std::max(kb, I0);
-        if (P.flags & G_B_LO) kb = std::max(kb, J0);
-        if (P.flags & G_A_LO) ke = std::min(ke, I0 + BM);
-        if (P.flags & G_B_UP) ke = std::min(ke, J0 + BN);
-        klen[P.tile0 + l] = std::max(0, ke - kb);
+        const float k = (float)tile_work(P, mode, BM, BN, (l % tm) * BM, (l / tm) * BN);
+        rank[k] = 0;
+        std::memcpy(&w[l], &k, sizeof(k));
       }
+    }
+    if (rank.size() < 2) return;
+    int nr = 0;
+    for (auto& r : rank) r.second = nr++;
+    for (auto& sh : shapes)
+      for (int& w : sh.second) {
+        float k;
+        std::memcpy(&k, &w, sizeof(k));
+        w = rank[k];
+      }
+    std::vector<int> of(nwg);
+    const std::vector<int>* w = nullptr;
+    std::array<int, 4> last{};
+    for (size_t q = (size_t)off; q < gemm.size(); ++q) {
+      const GemmProb& P = gemm[q];
+      const std::array<int, 4> key{P.M, P.N, P.K, P.flags};
+      if (!w || key != last) w = &shapes[key];
+      last = key;
+      std::copy(w->begin(), w->end(), of.begin() + P.tile0);
     }
     cur_ord = (int64_t)order.size();
     order.resize(order.size() + nwg);
     int32_t* o = order.data() + cur_ord;
     const int per = nwg >> 3, rem = nwg & 7;
+    std::vector<int> at(nr + 1);
     for (int x = 0; x < 8; ++x) {
-      const int lo = x * per + std::min(x, rem), cnt = per + (x < rem ? 1 : 0);
-      for (int r = 0; r < cnt; ++r) o[lo + r] = lo + r;
-      std::stable_sort(o + lo, o + lo + cnt, [&](int32_t a, int32_t b) { return klen[a] > klen[b]; });
+      const int beg = x * per + std::min(x, rem), hi = beg + per + (x < rem ? 1 : 0);
+      const int lo = mode == 4 ? std::max(beg, hi - 4 * 32) : beg;
+      for (int r = beg; r < lo; ++r) o[r] = r;
+      // counting sort of the rest
+      std::fill(at.begin(), at.end(), 0);
+      for (int r = lo; r < hi; ++r) ++at[of[r] + 1];
+      for (int r = 0; r < nr; ++r) at[r + 1] += at[r];
+      for (int r = lo; r < hi; ++r) o[lo + at[of[r]]++] = r;
     }
   }
   // GEMV kernel form of the current launch (see launch_gemv); the matrix
@@ -1122,10 +1245,13 @@ int run_launch(ddps_ctx* h, const Launch& L, int R, int64_t ldx, int64_t ldy, co
 
 int rhs_alloc(int k) { return k <= 1 ? 1 : k <= 2 ? 2 : k <= 4 ? 4 : 8; }
 
-// Default number of stream groups: enough to overlap one group's
-// latency-bound panel launches with the others' GEMMs, while each group
-// still has several blocks per launch.
-int default_groups(const ddps_ctx* h) { return std::max(1, std::min(4, h->p / 8)); }
+// Default number of stream groups: two overlap one group's latency-bound
+// panel launches with the other's GEMMs; more make the launches too small
+// for that (factor ms with 1 / 2 / 4 / 8 groups: 64 blocks of 8192 rows, band
+// 1024, bf16x3 30.3 / 27.8 / 32.9 / 37.6 and f64 94.1 / 92.0 / 99.2 / 105.0;
+// 128 blocks of 12800 rows, band 1600, bf16x3 178 / 173 / 181 / 181), and a
+// caller's stream with four groups no longer has a hardware queue for each.
+int default_groups(const ddps_ctx* h) { return std::max(1, std::min(2, h->p / 8)); }
 
 // ---------------------------------------------------------------- phases
 int do_scatter(ddps_ctx* h, hipStream_t s) {
@@ -2900,11 +3026,10 @@ double secs_since(const std::chrono::steady_clock::time_point& t0) {
 }
 
 int tune_launch_modes(ddps_ctx* h, int groups, double* ms) {
-  // fixed policies 0, 1, 2, 4 and 5 ask for tile modes 1, 0, 2, 3 and 4
-  static const int8_t mode_of_policy[5] = {1, 0, 2, 3, 4};
   static const int policy_of[5] = {0, 1, 2, 4, 5};
   const int nq = h->gdt >= 2 ? 5 : 2;
   std::vector<std::vector<float>> t(nq);
+  std::vector<std::vector<int8_t>> modes(nq);   // tile mode of each launch under each policy
   int rc;
   std::vector<float> t2;
   for (int q = 0; q < nq; ++q) {
@@ -2914,13 +3039,17 @@ int tune_launch_modes(ddps_ctx* h, int groups, double* ms) {
     if ((rc = time_gemm_launches(h, t2))) return rc;   // per launch, the faster of two runs
     if (t[q].size() != t[0].size() || t2.size() != t[q].size()) return DDPS_E_STATE;
     for (size_t i = 0; i < t2.size(); ++i) t[q][i] = std::min(t[q][i], t2[i]);
+    for (const auto& S : h->sch_group)
+      for (const Launch& L : S)
+        if (L.kind == LK_GEMM) modes[q].push_back((int8_t)std::max(0, L.mode));
+    if (modes[q].size() != t[q].size()) return DDPS_E_STATE;
   }
   h->mode_choice.assign(t[0].size(), 1);
   for (size_t i = 0; i < t[0].size(); ++i) {
     int best = 0;
     for (int q = 1; q < nq; ++q)
       if (t[q][i] < t[best][i]) best = q;
-    h->mode_choice[i] = mode_of_policy[best];
+    h->mode_choice[i] = modes[best][i];
   }
   if ((rc = ddps_set_execution(h, groups, 0, 3))) return rc;
   if ((rc = ddps_factor(h))) return rc;   // warm-up

@@ -4,8 +4,10 @@
 // k_gemm_dma: f64 / f32 MFMA 16x16x4, operands copied from global memory
 // straight into LDS.  k_gemm_std: the same products with element loads, for
 // operands that are not 16-byte aligned.  k_gemm_bf16 (bf16 MFMA on FP32
-// operands staged through registers) and k_gemm_dl (the same bf16 products
-// with the operands copied straight into LDS).  Operands are column-major
+// operands staged through registers), k_gemm_dl (the same bf16 products with
+// the operands copied straight into LDS, split as they are read) and
+// k_gemm_x3 (256 x 256 tiles, split as they are staged); all three give the
+// same bits.  Operands are column-major
 // (LAPACK layout); M and N need only be multiples of 64 (a larger tile on the
 // edge is masked).  Triangular operands are exploited twice: the K range of
 // each output tile is clipped to where both operands can be nonzero, and
@@ -259,50 +261,87 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_std(const GemmProb* __restric
 // ------------------------------------------------------------------------
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// Epilogue of MB x NB accumulator blocks of 32 x 32: register v of lane l in
-// block (mi, ni) is D(r0 + 32 mi + l % 32, c0 + 32 ni + 8 (v / 4) + 4 (l / 32) + v % 4),
-// and D = C0 -/+ acc.  Whole tiles (full) load C0 in batches of 16.
-template <int MB, int NB>
+// Where a block of rows [r, r + nr) and columns [c, c + nc) lies: 0 nothing of
+// it is stored (outside the problem, whose sides are multiples of the block's,
+// or on the other side of a D_UP / D_LO diagonal), 1 all of it, 2 the
+// diagonal crosses it.
+__device__ __forceinline__ int store_block(const GemmProb& P, int r, int c, int nr, int nc) {
+  if (r >= P.M || c >= P.N) return 0;
+  if (P.flags & G_D_UP) return r > c + nc - 1 ? 0 : r + nr - 1 <= c ? 1 : 2;
+  if (P.flags & G_D_LO) return r + nr - 1 < c ? 0 : r >= c + nc - 1 ? 1 : 2;
+  return 1;
+}
+
+// Epilogue of MB x NB accumulator blocks of 32 x 32, RS rows and CS columns
+// apart: register v of lane l in block (mi, ni) is D(r0 + RS (mi ^ flip) +
+// l % 32, c0 + CS ni + 8 (v / 4) + 4 (l / 32) + v % 4), and D = C0 -/+ acc.
+// C0 is loaded one row block (NB blocks) at a time before the first store: C0
+// and D may be the same entries, so the loads cannot move above stores by
+// themselves, and one by one each waits for the memory's latency.  Addresses
+// are a wave-uniform part and one 32-bit lane offset.
+template <int MB, int NB, int RS = 32, int CS = 32>
 __device__ __forceinline__ void store_tile32(const GemmProb& P, const f32x16 (&acc)[MB][NB], int r0, int c0,
-                                             int lane, bool full) {
+                                             int lane, int flip = 0) {
   gptr<float> C0 = (gptr<float>)P.C0;
   gmut<float> D = (gmut<float>)P.D;
   const bool has_c0 = P.flags & G_C0;
   const float sg = (P.flags & G_NEG) ? -1.f : 1.f;
-  if (full && !(P.flags & (G_D_UP | G_D_LO))) {
+  const uint32_t lc = (4u * (lane >> 5) * (uint32_t)P.ldc0 + (lane & 31)) * 4u;
+  const uint32_t ld = (4u * (lane >> 5) * (uint32_t)P.ldd + (lane & 31)) * 4u;
+  auto at = [&](int mi, int ni, int v, int ldx) -> int64_t {
+    return (int64_t)(c0 + CS * ni + 8 * (v >> 2) + (v & 3)) * ldx + r0 + RS * (mi ^ flip);
+  };
 #pragma unroll
-    for (int mi = 0; mi < MB; ++mi)
+  for (int mi = 0; mi < MB; ++mi) {
+    const int r = r0 + RS * (mi ^ flip);
+    int how[NB];
+    bool whole = true;
 #pragma unroll
-      for (int ni = 0; ni < NB; ++ni) {
-        const int r = r0 + mi * 32 + (lane & 31);
-        const int c = c0 + ni * 32 + 4 * (lane >> 5);
-        if (has_c0) {
-          float cv[16];
+    for (int ni = 0; ni < NB; ++ni) {
+      how[ni] = store_block(P, r, c0 + CS * ni, 32, 32);
+      whole = whole && how[ni] == 1;
+    }
+    if (whole) {
+      if (has_c0) {
+        float cv[NB][16];
 #pragma unroll
-          for (int v = 0; v < 16; ++v) cv[v] = C0[(int64_t)(c + 8 * (v >> 2) + (v & 3)) * P.ldc0 + r];
+        for (int ni = 0; ni < NB; ++ni)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) D[(int64_t)(c + 8 * (v >> 2) + (v & 3)) * P.ldd + r] = sg * acc[mi][ni][v] + cv[v];
-        } else {
+          for (int v = 0; v < 16; ++v) cv[ni][v] = *(gptr<float>)((gptr<char>)(C0 + at(mi, ni, v, P.ldc0)) + lc);
 #pragma unroll
-          for (int v = 0; v < 16; ++v) D[(int64_t)(c + 8 * (v >> 2) + (v & 3)) * P.ldd + r] = sg * acc[mi][ni][v];
-        }
+        for (int ni = 0; ni < NB; ++ni)
+#pragma unroll
+          for (int v = 0; v < 16; ++v)
+            *(gmut<float>)((gmut<char>)(D + at(mi, ni, v, P.ldd)) + ld) = sg * acc[mi][ni][v] + cv[ni][v];
+      } else {
+#pragma unroll
+        for (int ni = 0; ni < NB; ++ni)
+#pragma unroll
+          for (int v = 0; v < 16; ++v)
+            *(gmut<float>)((gmut<char>)(D + at(mi, ni, v, P.ldd)) + ld) = sg * acc[mi][ni][v];
       }
-    return;
+      continue;
+    }
+#pragma unroll
+    for (int ni = 0; ni < NB; ++ni) {
+      if (how[ni] == 0) continue;
+      auto ok = [&](int v) {
+        return store_ok(P.flags, r + (lane & 31), c0 + CS * ni + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3));
+      };
+      float cv[16];
+      if (has_c0) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          cv[v] = ok(v) ? *(gptr<float>)((gptr<char>)(C0 + at(mi, ni, v, P.ldc0)) + lc) : 0.f;
+      }
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (ok(v)) {
+          const float val = sg * acc[mi][ni][v];
+          *(gmut<float>)((gmut<char>)(D + at(mi, ni, v, P.ldd)) + ld) = has_c0 ? val + cv[v] : val;
+        }
+    }
   }
-#pragma unroll
-  for (int mi = 0; mi < MB; ++mi)
-#pragma unroll
-    for (int ni = 0; ni < NB; ++ni)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int r = r0 + mi * 32 + (lane & 31);
-        const int c = c0 + ni * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        if (r < P.M && c < P.N && store_ok(P.flags, r, c)) {
-          float val = sg * acc[mi][ni][v];
-          if (has_c0) val += C0[(int64_t)c * P.ldc0 + r];
-          D[(int64_t)c * P.ldd + r] = val;
-        }
-      }
 }
 
 template <bool SPLIT, int BM, int BN, int OCC = 1, int ST = 1, int BK = 32, int NW = 4>
@@ -321,7 +360,8 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(const GemmProb* __re
   const TileCoord tc = tile_of<BM, BN>(P, wg);
   const int I0 = tc.I0, J0 = tc.J0, kb = tc.kb, ke = tc.ke;
   const int fl = P.flags;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave & 1, wn = wave >> 1;
   const float* __restrict__ A = (const float*)P.A;
   const float* __restrict__ B = (const float*)P.B;
@@ -467,7 +507,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(const GemmProb* __re
     }
   }
 
-  store_tile32<MB, NB>(P, acc, I0 + wm * (BM / 2), J0 + wn * (2 * BN / NW), lane, !a_edge && !b_edge);
+  store_tile32<MB, NB>(P, acc, I0 + wm * (BM / 2), J0 + wn * (2 * BN / NW), lane);
 }
 
 
@@ -676,8 +716,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_dl(const GemmProb* __rest
       st ^= 1;
     }
   }
-  store_tile32<MB, NB>(P, acc, I0 + wm * (BM / 2), J0 + wn * (2 * BN / NW), lane,
-                       I0 + BM <= P.M && J0 + BN <= P.N);
+  store_tile32<MB, NB>(P, acc, I0 + wm * (BM / 2), J0 + wn * (2 * BN / NW), lane);
 }
 
 // ------------------------------------------------------------------------
@@ -880,16 +919,16 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_dma(const GemmProb* __restric
   // whole pairs in one access where the addresses allow it
   const uintptr_t al = (uintptr_t)P.D | (uintptr_t)P.ldd * sizeof(T) |
                        (has_c0 ? (uintptr_t)P.C0 | (uintptr_t)P.ldc0 * sizeof(T) : 0);
-  const bool vec = (al & (2 * sizeof(T) - 1)) == 0 && !(fl & (G_D_UP | G_D_LO));
+  const bool vec = (al & (2 * sizeof(T) - 1)) == 0;
 #pragma unroll
   for (int h = 0; h < D::H; ++h) {
     const int r = I0 + ((64 * h) ^ flip) + 32 * wm + 2 * li;
-    if (r >= P.M) continue;
 #pragma unroll
     for (int n = 0; n < 2 * D::HN; ++n) {
       const int c = J0 + 64 * (n >> 1) + 32 * wn + 16 * (n & 1);
-      if (c >= P.N) continue;
-      if (vec) {
+      const int how = store_block(P, r - 2 * li, c, 32, 16);
+      if (how == 0) continue;
+      if (vec && how == 1) {
         vec2 cv[4];
         if (has_c0) {
 #pragma unroll
@@ -917,9 +956,336 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_dma(const GemmProb* __restric
   }
 }
 
+// ------------------------------------------------------------------------
+// k_gemm_x3: the bf16 products on 256 x 256 tiles, one workgroup of 8 waves
+// (2 x 4) per CU, each FP32 operand entry split once per tile.
+//
+// K advances in steps of 16.  Waves 0-3 stage A, waves 4-7 B: 16 entries per
+// thread loaded into registers three steps ahead, split into hi and lo while
+// the current step multiplies (two pairs of entries under each three
+// products, so that both waves of a SIMD keep the matrix pipe busy), and
+// written to the other of two LDS stages as bf16 in the fragments' layout,
+// so that a fragment is one 16-byte read.  One barrier per step, placed
+// before the last row block: the products of that block cover the reads of
+// the next step's first fragments.  Wave (wm, wn) owns the 32-row blocks 64
+// mi + 32 wm and the 32-column blocks 128 ni + 32 wn: a tile at the edge of
+// the problem, or crossing the diagonal of a triangular A, does only the
+// products of the 64-row groups that have any, on all eight waves alike.
+//
+// Bound: power.  A 16-deep step takes about 1970 cycles of the 1536 its
+// products take on the matrix pipe, at a clock of 1.45 GHz instead of 2.4 (the
+// same kernel without the split: 1640 cycles); the energy of a product, not
+// its issue, sets the rate.  32 problems, TF/s of FP32 products, the kernel
+// that split every fragment it read (256 x 256 tiles) -> this one: dense
+// 1600^3 225 -> 277, 2048^2 x 1024 325 -> 383, upper triangle times 1600 x
+// 3200 230 -> 285, rank-256 update of 1344^2 104 -> 161.
+// ------------------------------------------------------------------------
+// LDS image of one 16-deep K step of one operand: row (column) r holds four
+// 16-byte units, the hi halves of k 0-7 and 8-15, then the lo halves; four
+// rows share 256 bytes, in which unit (r & 3) * 4 + u is stored at that index
+// XOR ((r >> 2) & 3 | (r >> 4 & 1) << 2).  With it the fragment reads (32
+// consecutive rows, one unit) and both operands' writes touch every bank of
+// a 256-byte pass once.
+__device__ __forceinline__ int x3_addr(int r, int u) {
+  const int g = ((r >> 2) & 3) | (((r >> 4) & 1) << 2);
+  return (r >> 2) * 256 + ((((r & 3) * 4 + u) ^ g) << 4);
+}
+
+struct X3Tile {
+  int fl, I0, J0, kb, ke, M, N;
+  int flip;   // 3: the tile's four 64-row groups are taken in reverse order (lower triangular A), else 0
+};
+
+__device__ __forceinline__ int x3_flip(const GemmProb& P, int I0) {
+  return (P.flags & G_A_LO) && I0 + 256 <= P.M ? 3 : 0;
+}
+
+// State of one wave in the K loop.  ISA: the wave stages A (waves 0-3), else B.
+template <bool SPLIT, bool ISA>
+struct X3Wave {
+  static constexpr int kStage = 32768, kB = 16384;
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+  const X3Tile& T;
+  const float* X;
+  int64_t ldx;
+  char* lds;
+  // Staging: a thread holds 16 entries of one operand's step.
+  //   A (rows contiguous in memory): rows R, R + 1 at 8 consecutive k (8
+  //     eight-byte loads; a wave load covers 512 contiguous bytes of one k);
+  //   B (k contiguous): 4 consecutive k of 4 columns 16 apart (4 sixteen-byte
+  //     loads; 4 lanes cover the 64 bytes of one column).
+  int r0, q0;        // A: row R, first k;  B: first column, first k
+  uint32_t ld4;
+  uint32_t off[4];   // byte offsets of the lane's loads from the step's first element
+  int wa[2];         // LDS write addresses
+  int fa, fb;        // LDS fragment addresses (hi; lo at ^ 32)
+  uint32_t hq[8], lq[8];
+  bf16x8 ah[2], al[2], bh[2], bl[2];   // A of the current and the next 32-row block (slots mi & 1), both B blocks
+
+  __device__ __forceinline__ X3Wave(const X3Tile& T_, const float* X_, int64_t ldx_, char* lds_, int lane, int w4, int wm,
+                                    int wn)
+      : T(T_), X(X_), ldx(ldx_), lds(lds_) {
+    const int li = lane & 31, half = lane >> 5;
+    ld4 = (uint32_t)ldx * 4u;
+    // rows and columns past the problem re-read its last ones (they only feed
+    // outputs that are not stored)
+    if (ISA) {
+      const int oct = w4 & 1, R = 128 * (w4 >> 1) + 2 * lane;
+      r0 = T.I0 + R;
+      q0 = 8 * oct;
+      wa[0] = x3_addr(R, oct) ^ (T.flip << 12);   // 64 rows are 4 KiB
+      wa[1] = x3_addr(R + 1, oct) ^ (T.flip << 12);
+      off[0] = (uint32_t)(min(r0, T.M - 2) - T.I0) * 4u + 8u * oct * ld4;
+    } else {
+      const int nq = lane >> 2, kq = lane & 3;
+      const int cb = 64 * w4 + ((nq & 3) | (((nq >> 3) & 1) << 2) | (((nq >> 2) & 1) << 3));
+      r0 = T.J0 + cb;
+      q0 = 4 * kq;
+      wa[0] = kB + x3_addr(cb, kq >> 1) + (kq & 1) * 8;
+      wa[1] = kB + x3_addr(cb + 16, kq >> 1) + (kq & 1) * 8;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) off[i] = (uint32_t)(min(r0 + 16 * i, T.N - 1) - T.J0) * ld4 + 16u * kq;
+    }
+    fa = x3_addr(32 * wm + li, half);
+    fb = kB + x3_addr(32 * wn + li, half);
+  }
+  // half j of a step's entries (A: 4 of the 8 k of both rows; B: 2 of the 4 columns)
+  __device__ __forceinline__ void load(float (&s)[16], int k, int j) {
+    const auto rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(ISA ? X + (int64_t)k * ldx + T.I0 : X + (int64_t)T.J0 * ldx + k), 0, 0xffffffffu, 0x00027000);
+    if (ISA) {
+#pragma unroll
+      for (int i = 4 * j; i < 4 * j + 4; ++i) {
+        const f32x2 v = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(rs, off[0], i * ld4, 0));
+        s[2 * i] = v[0];
+        s[2 * i + 1] = v[1];
+      }
+    } else {
+#pragma unroll
+      for (int i = 2 * j; i < 2 * j + 2; ++i) {
+        const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off[i], 0, 0));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s[4 * i + e] = v[e];
+      }
+    }
+  }
+  // packed-triangle masks on the staged entries of step k (where it crosses the diagonal)
+  __device__ __forceinline__ void mask(float (&s)[16], int k) {
+    const int fl = T.fl;
+    const bool lu = fl & (ISA ? G_A_MLU : G_B_MLU), up = fl & (ISA ? G_A_MUP : G_B_MUP),
+               lo = fl & (ISA ? G_A_MLO : G_B_MLO);
+    const int d0 = ISA ? T.I0 : T.J0;
+    if (!(lu || up || lo) || k + 16 <= d0 || k >= d0 + 256) return;
+    if (ISA) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          s[2 * i + j] = select_op(s[2 * i + j], r0 + j, k + q0 + i, lu, up, lo, 1 << 30, 1 << 30);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          s[4 * i + e] = select_op(s[4 * i + e], k + q0 + e, r0 + 16 * i, lu, up, lo, 1 << 30, 1 << 30);
+    }
+  }
+  // pair q (0 .. 7) of the staged entries split: hi and lo packed in hq[q], lq[q]
+  __device__ __forceinline__ void split2(const float (&s)[16], int q) {
+    // A: pair q = k 2(q & 3), + 1 of row q >> 2;  B: k 2(q & 1), + 1 of column q >> 1
+    const float x0 = ISA ? s[4 * (q & 3) + (q >> 2)] : s[2 * q], x1 = ISA ? s[4 * (q & 3) + 2 + (q >> 2)] : s[2 * q + 1];
+    const bf16x2 hv = __builtin_convertvector((f32x2{x0, x1}), bf16x2);
+    hq[q] = __builtin_bit_cast(uint32_t, hv);
+    if (SPLIT) {
+      const bf16x2 lv = __builtin_convertvector((f32x2{x0 - (float)hv[0], x1 - (float)hv[1]}), bf16x2);
+      lq[q] = __builtin_bit_cast(uint32_t, lv);
+    }
+  }
+  // writes of the split entries: A row j, B columns j and j + 2 ... (pairs 4j .. 4j + 3)
+  __device__ __forceinline__ void put(int st, int j) {
+    char* base = lds + st * kStage;
+    if (ISA) {
+      *(u32x4*)(base + wa[j]) = u32x4{hq[4 * j], hq[4 * j + 1], hq[4 * j + 2], hq[4 * j + 3]};
+      if (SPLIT) *(u32x4*)(base + (wa[j] ^ 32)) = u32x4{lq[4 * j], lq[4 * j + 1], lq[4 * j + 2], lq[4 * j + 3]};
+    } else {
+#pragma unroll
+      for (int i = 2 * j; i < 2 * j + 2; ++i) {
+        *(u32x2*)(base + wa[i & 1] + (i >> 1) * 2048) = u32x2{hq[2 * i], hq[2 * i + 1]};
+        if (SPLIT) *(u32x2*)(base + (wa[i & 1] ^ 32) + (i >> 1) * 2048) = u32x2{lq[2 * i], lq[2 * i + 1]};
+      }
+    }
+  }
+  __device__ __forceinline__ void read_a(int mi, int st) {
+    ah[mi & 1] = *(const bf16x8*)(lds + st * kStage + mi * 4096 + fa);
+    if (SPLIT) al[mi & 1] = *(const bf16x8*)(lds + st * kStage + mi * 4096 + (fa ^ 32));
+  }
+  __device__ __forceinline__ void read_b(int ni, int st) {
+    bh[ni] = *(const bf16x8*)(lds + st * kStage + ni * 8192 + fb);
+    if (SPLIT) bl[ni] = *(const bf16x8*)(lds + st * kStage + ni * 8192 + (fb ^ 32));
+  }
+  __device__ __forceinline__ void mma(f32x16& c, int mi, int ni) {
+    if (SPLIT) {
+      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bl[ni], ah[mi & 1], c, 0, 0, 0);
+      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bh[ni], al[mi & 1], c, 0, 0, 0);
+    }
+    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bh[ni], ah[mi & 1], c, 0, 0, 0);
+  }
+  __device__ __forceinline__ void sync() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  // Body of step k (fragments in stage st): its products by 32-row block,
+  // with step k + 16 split and staged into stage st ^ 1 under the first ones
+  // (free: every wave waited for its last reads of it before the last
+  // barrier), step k + 48 then loaded into the same registers, and after the
+  // barrier before the last row block the first fragments of step k + 16
+  // read.  MB x NB: the tile's 64-row and 128-column groups inside the
+  // problem.
+  template <int MB, int NB>
+  __device__ __forceinline__ void body(int k, int klast, int st, float (&s)[16], f32x16 (&acc)[4][2]) {
+    constexpr int H = MB > 1 ? MB / 2 : 1;   // row blocks that carry the split
+    mask(s, k + 16);
+#pragma unroll
+    for (int mi = 0; mi < MB; ++mi) {
+      if (mi == MB - 1 && MB > 1) {
+        if (MB <= 2) {
+          put(st ^ 1, 0);
+          put(st ^ 1, 1);
+        }
+        sync();
+        if ((MB & 1) == 0) read_a(0, st ^ 1);
+      }
+      if (mi + 1 < MB) read_a(mi + 1, st);
+      if (mi < H) {
+#pragma unroll
+        for (int q = 8 * mi / H; q < 8 * (mi + 1) / H; ++q) split2(s, ISA ? (q >> 1) + 4 * (q & 1) : q);
+      }
+      if (MB == 1 || (mi == H && MB > 2)) {
+        put(st ^ 1, 0);
+        put(st ^ 1, 1);
+      }
+      if (mi == H || MB == 1) {
+        load(s, min(k + 48, klast), 0);
+        load(s, min(k + 48, klast), 1);
+      }
+      const bf16x8 yh = ah[mi & 1], yl = al[mi & 1];
+      if (SPLIT) {
+#pragma unroll
+        for (int ni = 0; ni < NB; ++ni)
+          acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bl[ni], yh, acc[mi][ni], 0, 0, 0);
+#pragma unroll
+        for (int ni = 0; ni < NB; ++ni)
+          acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bh[ni], yl, acc[mi][ni], 0, 0, 0);
+      }
+#pragma unroll
+      for (int ni = 0; ni < NB; ++ni)
+        acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bh[ni], yh, acc[mi][ni], 0, 0, 0);
+      if (mi < H) {
+#pragma unroll
+        for (int q = 0; q < 3 * NB; ++q) {
+          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, 16 / H / NB, 0);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (MB == 1) sync();
+#pragma unroll
+    for (int ni = 0; ni < NB; ++ni) read_b(ni, st ^ 1);
+    if (MB & 1) read_a(0, st ^ 1);
+  }
+  // K steps [k, kend) with the first 64 MB rows
+  template <int MB, int NB>
+  __device__ __forceinline__ void steps(int& k, int kend, float (&s0)[16], float (&s1)[16], f32x16 (&acc)[4][2]) {
+    const int klast = T.ke - 16;
+    for (; k < kend; k += 32) {
+      body<MB, NB>(k, klast, 0, s1, acc);
+      body<MB, NB>(k + 16, klast, 1, s0, acc);
+    }
+  }
+  template <int NB>
+  __device__ __forceinline__ void run(f32x16 (&acc)[4][2]) {
+    float s0[16], s1[16];
+    // the first three steps on the way, the first staged, its first fragments read
+    load(s0, T.kb, 0);
+    load(s0, T.kb, 1);
+    load(s1, T.kb + 16, 0);
+    load(s1, T.kb + 16, 1);
+    mask(s0, T.kb);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) split2(s0, q);
+    put(0, 0);
+    put(0, 1);
+    load(s0, T.kb + 32, 0);
+    load(s0, T.kb + 32, 1);
+    sync();
+    read_a(0, 0);
+#pragma unroll
+    for (int ni = 0; ni < NB; ++ni) read_b(ni, 0);
+    // 64-row groups inside the problem; with an upper A a group joins when k
+    // reaches its rows, with a lower A (groups in reverse order) the last
+    // one leaves when k passes them
+    const int mb = (min(T.M - T.I0, 256) + 63) >> 6;
+    const int up = T.fl & G_A_UP ? T.I0 : -256;
+    int k = T.kb;
+    steps<1, NB>(k, min(T.ke, mb > 1 ? up + 64 : T.ke), s0, s1, acc);
+    steps<2, NB>(k, min(T.ke, mb > 2 ? up + 128 : T.ke), s0, s1, acc);
+    steps<3, NB>(k, min(T.ke, mb > 3 ? up + 192 : T.ke), s0, s1, acc);
+    steps<4, NB>(k, T.flip ? min(T.ke, T.I0 + 64) : T.ke, s0, s1, acc);
+    steps<3, NB>(k, min(T.ke, T.I0 + 128), s0, s1, acc);
+    steps<2, NB>(k, min(T.ke, T.I0 + 192), s0, s1, acc);
+    steps<1, NB>(k, T.ke, s0, s1, acc);
+  }
+  __device__ __forceinline__ void tile(f32x16 (&acc)[4][2]) {
+    if (T.N - T.J0 > 128) run<2>(acc);
+    else run<1>(acc);
+  }
+};
+
+template <bool SPLIT>
+__global__ __launch_bounds__(512, 2) void k_gemm_x3(const GemmProb* __restrict__ probs, int nprob,
+                                                    const int32_t* __restrict__ order) {
+  __shared__ __attribute__((aligned(256))) char lds[2 * X3Wave<SPLIT, true>::kStage];
+  const int wg = order ? order[xcd_swizzle(blockIdx.x, gridDim.x)] : xcd_swizzle(blockIdx.x, gridDim.x);
+  int pi = find_prob(probs, nprob, wg);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 2, wn = wave & 3;
+  f32x16 acc[4][2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  {
+    const GemmProb& P = probs[pi];
+    const TileCoord tc = tile_of<256, 256>(P, wg);
+    if (tc.kb < tc.ke) {
+      const X3Tile T{P.flags, tc.I0, tc.J0, tc.kb, tc.ke, P.M, P.N, x3_flip(P, tc.I0)};
+      if (wave < 4) {
+        X3Wave<SPLIT, true> W(T, (const float*)P.A, P.lda, lds, lane, wave, wm, wn);
+        W.tile(acc);
+      } else {
+        X3Wave<SPLIT, false> W(T, (const float*)P.B, P.ldb, lds, lane, wave - 4, wm, wn);
+        W.tile(acc);
+      }
+    }
+  }
+  // the record is read again for the epilogue instead of being held in
+  // scalar registers through the K loop
+  asm volatile("" : "+s"(pi));
+  const GemmProb P = probs[pi];
+  const TileCoord tc = tile_of<256, 256>(P, wg);
+  store_tile32<4, 2, 64, 128>(P, acc, tc.I0 + 32 * wm, tc.J0 + 32 * wn, lane, x3_flip(P, tc.I0));
+}
+
 // mode: 0 = 64 x 64 tiles, 1 = 128 x 128 tiles, 2 = 256 x 128 tiles (bf16 only),
 // 3 = 128 x 128 tiles with direct LDS loads (bf16 only; otherwise as 1),
-// 4 = 256 x 256 tiles on 8 waves with direct LDS loads (bf16 only; otherwise as 1),
+// 4 = 256 x 256 tiles on 8 waves (bf16 only; otherwise as 1),
 // -1 = f64 / f32 operands that are not 16-byte aligned (64 x 64 tiles, element loads)
 void launch_gemm(int dtype, int mode, const GemmProb* probs, int nprob, int nwg, hipStream_t s,
                  const int32_t* order) {
@@ -941,8 +1307,8 @@ void launch_gemm(int dtype, int mode, const GemmProb* probs, int nprob, int nwg,
   const bool split = dtype == 2;
   switch (mode) {
     case 4:
-      if (split) hipLaunchKernelGGL((k_gemm_dl<true, 256, 256, 8, 1>), g, dim3(512), 0, s, probs, nprob, order);
-      else hipLaunchKernelGGL((k_gemm_dl<false, 256, 256, 8, 1>), g, dim3(512), 0, s, probs, nprob, order);
+      if (split) hipLaunchKernelGGL((k_gemm_x3<true>), g, dim3(512), 0, s, probs, nprob, order);
+      else hipLaunchKernelGGL((k_gemm_x3<false>), g, dim3(512), 0, s, probs, nprob, order);
       break;
     case 3:
       if (split) hipLaunchKernelGGL((k_gemm_dl<true, 128, 128, 4, 2>), g, b, 0, s, probs, nprob, order);
