@@ -145,7 +145,7 @@ struct ddps_ctx {
   std::vector<int64_t> lu_off;
   bool spikes_zeroed = false;   // the whole spike array has been zeroed once (by an executed fill)
   void* d_tips = nullptr;   // spike tips packed row-major (rows of G^), 2(p-1) parts of t x 2t
-  int tip_nseg = 0;         // > 0: reduced products on the packed tips (R <= 2 and 2t short enough)
+  bool tip_packed = false;  // reduced products on the packed tips (R <= 2 and 2t short enough)
   unsigned long long *d_colnorm = nullptr, *d_bad = nullptr, *d_band = nullptr;
   unsigned int* d_flags = nullptr;
   double* d_thresh = nullptr;   // per padded row: pivot threshold
@@ -1160,7 +1160,7 @@ void build_solve_schedules(ddps_ctx* h, ScheduleBuilder& sb) {
   // block against its left-coupling columns, bottom rows against its right
   // ones), Y = X - N X
   auto reduced = [&](const double* X, double* Y, const double* dotv, int dflags, bool local = false) {
-    sb.begin(h->tip_nseg > 0 ? LK_TIPMV : LK_GEMV);
+    sb.begin(h->tip_packed ? LK_TIPMV : LK_GEMV);
     for (int i = 0; i < p && p > 1; ++i) {
       const BlockInfo& B = h->blk[i];
       for (int part = 0; part < 2; ++part) {
@@ -1168,7 +1168,7 @@ void build_solve_schedules(ddps_ctx* h, ScheduleBuilder& sb) {
         if (part == 1 && i == p - 1) continue;
         const int64_t ro = part == 0 ? (int64_t)(2 * i - 1) * t : (int64_t)2 * i * t;
         GemvProb G{};
-        if (h->tip_nseg > 0) {
+        if (h->tip_packed) {
           // packed part q = 2i - 1 (first t rows of block i) or 2i (last t rows)
           const int64_t q = part == 0 ? 2 * i - 1 : 2 * i;
           G.A = (const char*)h->d_tips + (size_t)q * t * 2 * t * h->elt;
@@ -1211,7 +1211,7 @@ void build_solve_schedules(ddps_ctx* h, ScheduleBuilder& sb) {
     h->l_pvh = reduced(h->d_mp, h->d_v, h->d_rt, V_DOT);
     h->l_sth = reduced(h->d_ms, h->d_tv, h->d_s, V_DOT | V_DOT2);
   }
-  h->W1 = h->l_pv.nwg;
+  h->W1 = h->l_pv.nwg * (h->tip_packed ? tipmv_split(h->sdt, h->l_pv.nwg) : 1);
 }
 
 int run_launch(ddps_ctx* h, const Launch& L, int R, int64_t ldx, int64_t ldy, const double* dotv,
@@ -1229,7 +1229,7 @@ int run_launch(ddps_ctx* h, const Launch& L, int R, int64_t ldx, int64_t ldy, co
       break;
     }
     case LK_TIPMV:
-      launch_tipmv(h->sdt, R, h->tip_nseg, h->d_gemv + L.off, L.nprob, L.nwg, ldx, ldy, dotv, partial, stop, s);
+      launch_tipmv(h->sdt, R, h->t, h->d_gemv + L.off, L.nprob, L.nwg, ldx, ldy, dotv, partial, stop, s);
       break;
     default:
       launch_gemv(h->sdt, R, L.mode, h->d_gemv + L.off, L.nprob, L.nwg, ldx, ldy, dotv, partial, stop, s);
@@ -1333,7 +1333,7 @@ int enqueue_factor(ddps_ctx* h) {
   if (G <= 1 || serial) {
     for (int g = 0; g < G; ++g)
       if ((rc = run_schedule(h, h->sch_group[g], 1, 0, 0, TK_GEMM, f))) return rc;
-    if (h->tip_nseg > 0) pack_tips(h->sdt, h->p, h->t, h->d_blk, h->d_spikes, h->d_tips, f);
+    if (h->tip_packed) pack_tips(h->sdt, h->p, h->t, h->d_blk, h->d_spikes, h->d_tips, f);
     if ((rc = run_schedule(h, h->sch_rfac, 1, 0, 0, TK_GEMM, f, TK_RFAC))) return rc;
     HIPCHK(hipGetLastError());
     return DDPS_OK;
@@ -1349,7 +1349,7 @@ int enqueue_factor(ddps_ctx* h) {
     HIPCHK(hipEventRecord(gev[g - 1], h->gstream[g - 1]));
   }
   for (int g = 1; g < G; ++g) HIPCHK(hipStreamWaitEvent(f, gev[g - 1], 0));
-  if (h->tip_nseg > 0) pack_tips(h->sdt, h->p, h->t, h->d_blk, h->d_spikes, h->d_tips, f);
+  if (h->tip_packed) pack_tips(h->sdt, h->p, h->t, h->d_blk, h->d_spikes, h->d_tips, f);
   if ((rc = run_schedule(h, h->sch_rfac, 1, 0, 0, TK_GEMM, f, TK_RFAC))) return rc;
   HIPCHK(hipGetLastError());
   return DDPS_OK;
@@ -1452,7 +1452,8 @@ int build_schedules(ddps_ctx* h) {
     h->gevent.push_back(ge);
   }
   h->drop_graph();
-  if ((int64_t)h->W1 * h->R * 2 > h->part_cap) return DDPS_E_ARG;
+  // the inner iteration's three sets of partial sums (product, two vector kernels)
+  if (((int64_t)h->W1 + 2 * vec_grid(h->m)) * h->R * 2 > h->part_cap) return DDPS_E_ARG;
   return DDPS_OK;
 }
 
@@ -1510,6 +1511,17 @@ int inner_solve(ddps_ctx* h, int k, int use_guess, double tol, int maxit, std::v
   bicg_init(R, m, use_guess, h->d_gh, h->d_zh, h->d_v, h->d_r, h->d_rt, h->d_p, h->d_part_buf, W2, s);
   reduce2(R, W2, h->d_part_buf, S0, nullptr, s);
   bicg_init_state(R, k, tol, S0, h->d_state, s);
+  // Partial sums of the products (A) and of the vector kernels (B: s.s, C: r.r
+  // and r~.r).  Few of them are added up by the kernel that needs the sums,
+  // more by a reduction of their own.
+  double* partA = h->d_part_buf;
+  double* partB = partA + (int64_t)h->W1 * R * 2;
+  double* partC = partB + (int64_t)W2 * R * 2;
+  auto sums = [&](int W, const double* part, double* out, const int32_t* stop) {
+    if (W * R <= kFuseParts) return PartSums{W, part, out};
+    reduce2(R, W, part, out, stop, s, h->d_red1);
+    return PartSums{0, part, out};
+  };
   std::vector<int> restarts(k, 0);
   int it = 1;
   const int batch = 4;
@@ -1521,17 +1533,14 @@ int inner_solve(ddps_ctx* h, int k, int use_guess, double tol, int maxit, std::v
       const int32_t* stop = &h->d_state->status[it & 1][0];
       // right preconditioning: v = G^ M^{-1} p, t = G^ M^{-1} s, x += a M^{-1} p + w M^{-1} s
       if (prec) run_launch(h, h->l_lp, R, m, m, nullptr, nullptr, stop, TK_RSPMV);
-      run_launch(h, prec ? h->l_pvh : h->l_pv, R, m, m, h->d_rt, h->d_part_buf, stop, TK_RSPMV);
-      reduce2(R, h->W1, h->d_part_buf, S1, stop, s, h->d_red1);
-      bicg_s(R, it, m, S1, h->d_state, h->d_r, h->d_v, h->d_s, h->d_part_buf, W2, s);
-      reduce2(R, W2, h->d_part_buf, S2, stop, s, h->d_red1);
+      run_launch(h, prec ? h->l_pvh : h->l_pv, R, m, m, h->d_rt, partA, stop, TK_RSPMV);
+      bicg_s(R, it, m, sums(h->W1, partA, S1, stop), h->d_state, h->d_r, h->d_v, h->d_s, partB, W2, s);
+      const PartSums q2 = sums(W2, partB, S2, stop);
       if (prec) run_launch(h, h->l_ls, R, m, m, nullptr, nullptr, stop, TK_RSPMV);
-      run_launch(h, prec ? h->l_sth : h->l_st, R, m, m, h->d_s, h->d_part_buf, stop, TK_RSPMV);
-      reduce2(R, h->W1, h->d_part_buf, S3, stop, s, h->d_red1);
-      bicg_xr(R, it, m, tol, S1, S2, S3, h->d_state, h->d_zh, h->d_p, h->d_s, h->d_tv, h->d_r, h->d_rt,
-              h->d_part_buf, W2, s, prec ? h->d_mp : nullptr, prec ? h->d_ms : nullptr);
-      reduce2(R, W2, h->d_part_buf, S4, stop, s, h->d_red1);
-      bicg_p(R, it, maxit, m, tol, S1, S2, S3, S4, h->d_state, h->d_r, h->d_p, h->d_v, W2, s);
+      run_launch(h, prec ? h->l_sth : h->l_st, R, m, m, h->d_s, partA, stop, TK_RSPMV);
+      bicg_xr(R, it, m, tol, S1, q2, sums(h->W1, partA, S3, stop), h->d_state, h->d_zh, h->d_p, h->d_s, h->d_tv,
+              h->d_r, h->d_rt, partC, W2, s, prec ? h->d_mp : nullptr, prec ? h->d_ms : nullptr);
+      bicg_p(R, it, maxit, m, tol, S1, S2, S3, sums(W2, partC, S4, stop), h->d_state, h->d_r, h->d_p, h->d_v, W2, s);
     }
     HIPCHK(hipGetLastError());
     HIPCHK(hipMemcpyAsync(h->h_state, h->d_state, sizeof(KState), hipMemcpyDeviceToHost, s));
@@ -2099,8 +2108,8 @@ int ddps_setup(ddps_handle* out, int64_t n, int32_t p, const int64_t* part_ptr, 
   // packed tips (2(p-1) parts of t x 2t = m x 2t) for one or two right-hand
   // sides, or the column-major tips that are all the tips-only form keeps,
   // and that form's compact store of the coupling entries
-  h->tip_nseg = (R <= 2 && p > 1 && !h->tips_only) ? tipmv_segments(h->sdt, t) : 0;
-  if (h->tip_nseg > 0 || h->tips_only) need += (size_t)m * 2 * t * h->elt;
+  h->tip_packed = R <= 2 && p > 1 && !h->tips_only && tipmv_packs(h->sdt, t);
+  if (h->tip_packed || h->tips_only) need += (size_t)m * 2 * t * h->elt;
   if (h->tips_only) need += (size_t)p * h->pair_elems() * h->elt;
   const bool direct = o.reduced_solve == 1 && p > 1;
   const size_t rw_elems = 5 * (size_t)t * t + 2 * (size_t)t * (t / 2 + 64);
@@ -2161,7 +2170,7 @@ int ddps_setup(ddps_handle* out, int64_t n, int32_t p, const int64_t* part_ptr, 
   if ((rc = h->alloc_raw(vp, (size_t)std::max<int64_t>(h->nspike, 1) * h->elt))) return fail(rc);
   h->d_spikes = vp;
   h->spikes_zeroed = false;
-  if (h->tip_nseg > 0) {
+  if (h->tip_packed) {
     if ((rc = h->alloc_raw(vp, (size_t)h->m * 2 * t * h->elt))) return fail(rc);
     h->d_tips = vp;
   }

@@ -184,11 +184,12 @@ void launch_panel(int dtype, const PanelProb* probs, int nprob, const double* th
 void launch_gemv(int dtype, int nrhs, int form, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
                  int64_t ldy, const double* dotv, double* partial, const int32_t* stop, hipStream_t s);
 // reduced-matrix product on the packed tips (same records as launch_gemv,
-// A = first packed row, lda = 2t; nrhs 1 or 2; nseg from tipmv_segments, 0 if
-// 2t is too long for the register-held right-hand side) and the packing of
-// the tips after a factorisation
-int tipmv_segments(int dtype, int t);
-void launch_tipmv(int dtype, int nrhs, int nseg, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
+// A = first packed row, lda = 2t; nrhs 1 or 2; one partial per workgroup,
+// tipmv_split(nwg) of them per 64 rows), whether tips of this size are packed
+// for it, and the packing of the tips after a factorisation
+bool tipmv_packs(int dtype, int t);
+int tipmv_split(int dtype, int nwg);
+void launch_tipmv(int dtype, int nrhs, int t, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
                   int64_t ldy, const double* dotv, double* partial, const int32_t* stop, hipStream_t s);
 void pack_tips(int dtype, int p, int t, const BlockInfo* blocks, const void* spikes, void* tips, hipStream_t s);
 
@@ -234,15 +235,24 @@ void reduce2(int R, int W, const double* part, double* out, const int32_t* stop,
 void bicg_init(int R, int64_t m, int use_guess, const double* gh, double* x, const double* v, double* r,
                double* rt, double* p, double* part, int W, hipStream_t s);
 void bicg_init_state(int R, int k, double tol, const double* sums, KState* st, hipStream_t s);
-void bicg_s(int R, int it, int64_t m, const double* s1, KState* st, const double* r, const double* v,
+// Sums of a reduction as a kernel takes them: reduced already (W = 0, in
+// sums), or W partials of R columns at part, which the kernel adds up itself
+// and workgroup 0 leaves in sums (worth it up to kFuseParts values)
+struct PartSums {
+  int W;
+  const double* part;
+  double* sums;
+};
+constexpr int kFuseParts = 2048;
+void bicg_s(int R, int it, int64_t m, PartSums s1, KState* st, const double* r, const double* v,
             double* sv, double* part, int W, hipStream_t s);
 // px, sx (may be null = p, sv): directions added to x, M^{-1}p and M^{-1}s when preconditioned
-void bicg_xr(int R, int it, int64_t m, double tol, const double* s1, const double* s2, const double* s3,
+void bicg_xr(int R, int it, int64_t m, double tol, const double* s1, PartSums s2, PartSums s3,
              KState* st, double* x, const double* p, const double* sv, const double* t, double* r,
              const double* rt, double* part, int W, hipStream_t s, const double* px = nullptr,
              const double* sx = nullptr);
 void bicg_p(int R, int it, int maxit, int64_t m, double tol, const double* s1, const double* s2,
-            const double* s3, const double* s4, KState* st, const double* r, double* p, const double* v,
+            const double* s3, PartSums s4, KState* st, const double* r, double* p, const double* v,
             int W, hipStream_t s);
 void bicg_restart(int R, int it, int64_t m, const int32_t* flag, const double* r, double* rt, double* p,
                   double* part, int W, double* sums, KState* st, hipStream_t s);

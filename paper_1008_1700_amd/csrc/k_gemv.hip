@@ -12,7 +12,13 @@
 
 namespace ddps {
 
-__device__ __forceinline__ int find_gemv(const GemvProb* __restrict__ probs, int nprob, int wg) {
+// Problem of workgroup wg of nwg.  Most launches hold problems of equal size,
+// where the proportional guess is right and the dependent loads of a search
+// (a microsecond or more of a short kernel) are saved.
+__device__ __forceinline__ int find_gemv(const GemvProb* __restrict__ probs, int nprob, int wg, int nwg) {
+  const int gs = (int)((int64_t)wg * nprob / nwg);
+  const int b0 = probs[gs].wg0, b1 = gs + 1 < nprob ? probs[gs + 1].wg0 : nwg;
+  if (b0 <= wg && wg < b1) return gs;
   int lo = 0, hi = nprob - 1;
   while (lo < hi) {
     const int mid = (lo + hi + 1) >> 1;
@@ -35,7 +41,7 @@ __global__ __launch_bounds__(256) void k_gemv(const GemvProb* __restrict__ probs
     if (all) return;
   }
   const int wg = blockIdx.x;
-  const GemvProb& Pg = probs[find_gemv(probs, nprob, wg)];
+  const GemvProb& Pg = probs[find_gemv(probs, nprob, wg, gridDim.x)];
   const GemvProb P = Pg;
   const int r0 = (wg - P.wg0) * 64;
   int cb = P.cb, ce = P.ce;
@@ -115,7 +121,8 @@ __global__ __launch_bounds__(256) void k_gemv(const GemvProb* __restrict__ probs
 }
 
 // ------------------------------------------------------------------------
-// Wide-load form of k_gemv for 16-byte aligned problems: a lane reads VEC
+// Wide-load form of k_gemv for 16-byte aligned problems and many right-hand
+// sides: a lane reads VEC
 // consecutive rows of one column in one 16-byte load, so one wave load
 // covers 64 rows of VEC columns (1 KB) instead of 64 rows of one column.
 // The VEC column slots of a wave are summed by lane shuffles, the 4 waves
@@ -139,7 +146,7 @@ __global__ __launch_bounds__(256) void k_gemv_w(const GemvProb* __restrict__ pro
     if (all) return;
   }
   const int wg = blockIdx.x;
-  const GemvProb& Pg = probs[find_gemv(probs, nprob, wg)];
+  const GemvProb& Pg = probs[find_gemv(probs, nprob, wg, gridDim.x)];
   const GemvProb P = Pg;
   const int r0 = (wg - P.wg0) * 64;
   int cb = P.cb, ce = P.ce;
@@ -161,71 +168,44 @@ __global__ __launch_bounds__(256) void k_gemv_w(const GemvProb* __restrict__ pro
 #pragma unroll
     for (int j = 0; j < R; ++j) acc[e][j] = 0.0;
 
-  auto add = [&](const vec_t& a, int cc) __attribute__((always_inline)) {
-    double xv[R];
-#pragma unroll
-    for (int j = 0; j < R; ++j) xv[j] = cc < split ? P.x1[cc + j * ldx] : P.x2[(cc - split) + j * ldx];
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      const int rr = r0 + rl + e;
-      double av = (double)a[e];
-      if (mlu) av = rr > cc ? av : (rr == cc ? 1.0 : 0.0);
-      if (mup) av = rr <= cc ? av : 0.0;
-      if (mlo) av = rr >= cc ? av : 0.0;
-#pragma unroll
-      for (int j = 0; j < R; ++j) acc[e][j] += av * xv[j];
+  // many right-hand sides: the vector entries of each round of U STEP
+  // columns are staged once per workgroup in LDS (double-buffered), so a
+  // lane reads its columns' R entries as 16-byte LDS reads instead of R
+  // separate global loads
+  constexpr int U = 8;           // loads in flight per lane (four: 521 us for 2.5 GB of f64, 8 rhs; eight: 479 us)
+  constexpr int RC = U * STEP;   // columns per round
+  __shared__ __attribute__((aligned(16))) double xs[2][RC][R];
+  int buf = 0;
+  for (int c0 = cb; c0 < ce; c0 += RC) {
+    for (int i = tid; i < RC * R; i += 256) {
+      const int cc = c0 + i / R, j = i % R;
+      xs[buf][i / R][j] = cc < ce ? (cc < split ? P.x1[cc + j * ldx] : P.x2[(cc - split) + j * ldx]) : 0.0;
     }
-  };
-  if constexpr (R >= 4) {
-    // many right-hand sides: the vector entries of each round of 4 STEP
-    // columns are staged once per workgroup in LDS (double-buffered), so a
-    // lane reads its columns' R entries as 16-byte LDS reads instead of R
-    // separate global loads
-    constexpr int RC = 4 * STEP;   // columns per round
-    __shared__ __attribute__((aligned(16))) double xs[2][RC][R];
-    int buf = 0;
-    for (int c0 = cb; c0 < ce; c0 += RC) {
-      for (int i = tid; i < RC * R; i += 256) {
-        const int cc = c0 + i / R, j = i % R;
-        xs[buf][i / R][j] = cc < ce ? (cc < split ? P.x1[cc + j * ldx] : P.x2[(cc - split) + j * ldx]) : 0.0;
-      }
-      __syncthreads();
-      vec_t a[4];
+    __syncthreads();
+    vec_t a[U];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int cc = c0 + g * VEC + q + u * STEP;
-        a[u] = cc < ce ? *(const vec_t*)(A + (int64_t)cc * lda) : vec_t{};
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int cl = g * VEC + q + u * STEP, cc = c0 + cl;
-        double xv[R];
-#pragma unroll
-        for (int j = 0; j < R; ++j) xv[j] = xs[buf][cl][j];
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          const int rr = r0 + rl + e;
-          double av = (double)a[u][e];
-          if (mlu) av = rr > cc ? av : (rr == cc ? 1.0 : 0.0);
-          if (mup) av = rr <= cc ? av : 0.0;
-          if (mlo) av = rr >= cc ? av : 0.0;
-#pragma unroll
-          for (int j = 0; j < R; ++j) acc[e][j] += av * xv[j];
-        }
-      }
-      buf ^= 1;
+    for (int u = 0; u < U; ++u) {
+      const int cc = c0 + g * VEC + q + u * STEP;
+      a[u] = cc < ce ? *(const vec_t*)(A + (int64_t)cc * lda) : vec_t{};
     }
-  } else {
-    int c = cb + g * VEC + q;
-    // four independent columns per lane per step for memory-level parallelism
-    for (; c + 3 * STEP < ce; c += 4 * STEP) {
-      vec_t a[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) a[u] = *(const vec_t*)(A + (int64_t)(c + u * STEP) * lda);
+    for (int u = 0; u < U; ++u) {
+      const int cl = g * VEC + q + u * STEP, cc = c0 + cl;
+      double xv[R];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) add(a[u], c + u * STEP);
+      for (int j = 0; j < R; ++j) xv[j] = xs[buf][cl][j];
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        const int rr = r0 + rl + e;
+        double av = (double)a[u][e];
+        if (mlu) av = rr > cc ? av : (rr == cc ? 1.0 : 0.0);
+        if (mup) av = rr <= cc ? av : 0.0;
+        if (mlo) av = rr >= cc ? av : 0.0;
+#pragma unroll
+        for (int j = 0; j < R; ++j) acc[e][j] += av * xv[j];
+      }
     }
-    for (; c < ce; c += STEP) add(*(const vec_t*)(A + (int64_t)c * lda), c);
+    buf ^= 1;
   }
   // sum the column slots of the wave (lanes with equal lane % LPC)
 #pragma unroll
@@ -271,28 +251,34 @@ __global__ __launch_bounds__(256) void k_gemv_w(const GemvProb* __restrict__ pro
 }
 
 // ------------------------------------------------------------------------
-// Reduced-matrix product on packed spike tips.  The rows of G^ are the
-// first and last t rows of each spike G_i (2t columns each), which inside
-// the column-major spikes are 4t-byte column pieces N_i apart.  After every
-// factorisation they are packed row-major (k_pack_tips), and the product
-// streams each row as one contiguous run: a wave owns a row at a time, its
-// lanes read consecutive 16-byte pieces of it, the right-hand-side entries
-// come from L1/L2 (2t values shared by every row of the part), and the row
-// sum is a wave reduction.  Lane rr keeps the sum of the wave's row rr,
-// and one epilogue per wave then serves its 16 rows at once.  Same problem
-// records, flags and partial-sum layout as k_gemv (A = first packed row,
-// lda = row length 2t).
+// One or two right-hand sides, 16-byte aligned problems: the column range's
+// vector entries are staged in LDS once per workgroup (CH columns at a time), and the NW waves take
+// interleaved groups of columns, U loads of 1 KiB each in flight per wave (a
+// lane reads VEC consecutive rows of one column, a wave load 64 rows of VEC
+// columns).  The packed-triangle masks
+// change only a slab's diagonal columns [r0, r0 + 64).  Epilogue, flags and
+// partial sums as in k_gemv.
+//
+// Bound: HBM for long launches; the sweeps are chains of short launches, so
+// latency: with four loads in flight on four waves and the vector entries
+// loaded beside every matrix entry, a 1024-wide triangle took 59 us (f32, 64
+// blocks) and a 512-wide f64 one of 16 blocks 20.1 us; this form takes 31 us,
+// and 7 us with sixteen waves.
 // ------------------------------------------------------------------------
-template <typename T, int R, int NSEG>
-__global__ __launch_bounds__(256) void k_tipmv(const GemvProb* __restrict__ probs, int nprob,
-                                               int64_t ldx, int64_t ldy,
-                                               const double* __restrict__ dotv,
-                                               double* __restrict__ partial,
-                                               const int32_t* __restrict__ stop) {
-  constexpr int VEC = 16 / sizeof(T);
-  constexpr int RPW = 16;                       // rows per wave (64 per workgroup)
+template <typename T, int R, int NW>
+__global__ __launch_bounds__(64 * NW) void k_gemv_n(const GemvProb* __restrict__ probs, int nprob,
+                                                    int64_t ldx, int64_t ldy,
+                                                    const double* __restrict__ dotv,
+                                                    double* __restrict__ partial,
+                                                    const int32_t* __restrict__ stop) {
+  constexpr int VEC = 16 / sizeof(T);   // rows per lane
+  constexpr int LPC = 64 / VEC;         // lanes per column
+  constexpr int U = 8;                  // loads in flight per lane
+  constexpr int CH = 2048 / R;          // columns staged at a time
   typedef T vec_t __attribute__((ext_vector_type(VEC)));
-  __shared__ double red[4][R][2];
+  // the vector entries, then the waves' sums
+  __shared__ __attribute__((aligned(16))) double xs[CH * R > NW * 64 * R ? CH * R : NW * 64 * R];
+  double (*red)[64][R] = (double (*)[64][R])xs;
   if (stop) {
     bool all = true;
 #pragma unroll
@@ -300,53 +286,208 @@ __global__ __launch_bounds__(256) void k_tipmv(const GemvProb* __restrict__ prob
     if (all) return;
   }
   const int wg = blockIdx.x;
-  const GemvProb& P = probs[find_gemv(probs, nprob, wg)];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const GemvProb P = probs[find_gemv(probs, nprob, wg, gridDim.x)];
+  const int r0 = (wg - P.wg0) * 64;
+  int cb = P.cb, ce = P.ce;
+  if (P.tri == 1) ce = min(ce, r0 + 64);
+  if (P.tri == 2) cb = max(cb, r0);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int g = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q = lane / LPC;             // column slot of this lane
+  const int rl = (lane % LPC) * VEC;    // first local row of this lane
   const int fl = P.flags;
-  const int cb = P.cb, ce = P.ce, split = P.split;
-  const int rbase = (wg - P.wg0) * 64 + wave * RPW;
-  // the right-hand-side entries of this lane's columns, once for all rows
-  double xr[NSEG][VEC][R];
+  const bool mlu = fl & V_A_MLU, mup = fl & V_A_MUP, mlo = fl & V_A_MLO;
+  const bool masked = mlu || mup || mlo;
+  const T* __restrict__ A = (const T*)P.A + r0 + rl;
+  const int64_t lda = P.lda;
+  const int split = P.split;
+  double acc[VEC][R];
 #pragma unroll
-  for (int sg = 0; sg < NSEG; ++sg)
+  for (int e = 0; e < VEC; ++e)
 #pragma unroll
-    for (int e = 0; e < VEC; ++e) {
-      const int c = cb + (sg * 64 + lane) * VEC + e;
+    for (int j = 0; j < R; ++j) acc[e][j] = 0.0;
+  for (int c0 = cb; c0 < ce; c0 += CH) {
+    const int c1 = min(ce, c0 + CH);
+    if (c0 > cb) __syncthreads();   // every wave is done with the previous columns
+    for (int i = tid; i < (c1 - c0) * R; i += 64 * NW) {
+      const int cc = c0 + i % (c1 - c0), j = i / (c1 - c0);
+      xs[(cc - c0) * R + j] = cc < split ? P.x1[cc + j * ldx] : P.x2[(cc - split) + j * ldx];
+    }
+    __syncthreads();
+    // wave g takes the column groups c0 + VEC (g + NW s), s = 0, 1, ...
+    for (int c = c0 + g * VEC + q; c - q < c1; c += U * NW * VEC) {
+      vec_t a[U];
 #pragma unroll
-      for (int j = 0; j < R; ++j) {
-        double v = 0.0;
-        if (c < ce) v = c < split ? P.x1[c + j * ldx] : P.x2[(c - split) + j * ldx];
-        xr[sg][e][j] = v;
+      for (int u = 0; u < U; ++u) {
+        const int cc = c + u * NW * VEC;
+        a[u] = cc < c1 ? *(const vec_t*)(A + (int64_t)cc * lda) : vec_t{};
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int cc = c + u * NW * VEC;
+        if (cc >= c1) continue;
+        if (masked && cc >= r0 && cc < r0 + 64) {
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) {
+            const int rr = r0 + rl + e;
+            if (mlu) a[u][e] = rr > cc ? a[u][e] : (rr == cc ? T(1) : T(0));
+            if (mup) a[u][e] = rr <= cc ? a[u][e] : T(0);
+            if (mlo) a[u][e] = rr >= cc ? a[u][e] : T(0);
+          }
+        }
+#pragma unroll
+        for (int j = 0; j < R; ++j) {
+          const double xv = xs[(cc - c0) * R + j];
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) acc[e][j] += (double)a[u][e] * xv;
+        }
       }
     }
-  // row rr's sum is kept by lane rr; one epilogue per wave for its 16 rows
-  double mine[R];
+  }
+  // sum the column slots of the wave (lanes with equal lane % LPC)
 #pragma unroll
-  for (int j = 0; j < R; ++j) mine[j] = 0.0;
-#pragma unroll 2
-  for (int rr = 0; rr < RPW; ++rr) {
-    const int r = rbase + rr;
-    const T* __restrict__ Arow = (const T*)P.A + (int64_t)r * P.lda + cb;
-    vec_t a[NSEG];
+  for (int e = 0; e < VEC; ++e)
 #pragma unroll
-    for (int sg = 0; sg < NSEG; ++sg) {
-      const int c0 = (sg * 64 + lane) * VEC;
-      if (cb + c0 < ce) a[sg] = *(const vec_t*)(Arow + c0);
-      else a[sg] = vec_t{};
-    }
-    double acc[R];
+    for (int j = 0; j < R; ++j)
+      for (int off = LPC; off < 64; off <<= 1) acc[e][j] += __shfl_xor(acc[e][j], off, 64);
+  __syncthreads();   // every wave is done with the vector entries
+  if (lane < LPC) {
 #pragma unroll
-    for (int j = 0; j < R; ++j) acc[j] = 0.0;
+    for (int e = 0; e < VEC; ++e)
 #pragma unroll
-    for (int sg = 0; sg < NSEG; ++sg)
-#pragma unroll
-      for (int e = 0; e < VEC; ++e)
-#pragma unroll
-        for (int j = 0; j < R; ++j) acc[j] += (double)a[sg][e] * xr[sg][e][j];
+      for (int j = 0; j < R; ++j) red[g][rl + e][j] = acc[e][j];
+  }
+  __syncthreads();
+  if (tid < 64) {
+    const int r = r0 + lane;
+    double dot[R], dd[R];
 #pragma unroll
     for (int j = 0; j < R; ++j) {
-      for (int off = 32; off > 0; off >>= 1) acc[j] += __shfl_xor(acc[j], off, 64);
-      mine[j] = lane == rr ? acc[j] : mine[j];
+      double s = 0.0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) s += red[w][lane][j];
+      if (fl & V_MASK) s *= P.mask[r];
+      if (fl & V_NEG) s = -s;
+      if (fl & V_YIN) s += P.yin[r + j * ldy];
+      if (r >= P.row_skip) P.yout[r + j * ldy] = s;
+      dot[j] = (fl & V_DOT) ? dotv[P.dot_off + r + j * ldy] * s : 0.0;
+      dd[j] = (fl & V_DOT2) ? s * s : 0.0;
+    }
+    if (fl & V_DOT) {
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        double v = dot[j], w = dd[j];
+        for (int off = 32; off > 0; off >>= 1) {
+          v += __shfl_xor(v, off, 64);
+          w += __shfl_xor(w, off, 64);
+        }
+        if (lane == 0) {
+          partial[((int64_t)wg * R + j) * 2 + 0] = v;
+          partial[((int64_t)wg * R + j) * 2 + 1] = w;
+        }
+      }
+    }
+  }
+}
+
+// ------------------------------------------------------------------------
+// Reduced-matrix product on packed spike tips.  The rows of G^ are the
+// first and last t rows of each spike G_i (2t columns each), which inside
+// the column-major spikes are 4t-byte column pieces N_i apart.  After every
+// factorisation they are packed row-major (k_pack_tips), and the product
+// streams each row as one contiguous run: a wave takes four rows at a time,
+// its lanes read consecutive 16-byte pieces of them, the right-hand-side
+// entries (2t values shared by every row of the part) come from LDS, once
+// for the four rows, and the four row sums are reduced over the wave
+// together.  Lane 16 i of a group of four rows ends with row i's sum; one
+// epilogue per wave serves its RPW rows.  Same problem records, flags and
+// partial-sum layout as k_gemv (A = first packed row, lda = row length 2t),
+// a workgroup of 4 RPW rows and one partial per workgroup.
+//
+// Bound: HBM (2.1 GB of f64 tips in 355 us, 6.0 TB/s; splitting the columns
+// over the waves as k_tipmv_c does takes 398 us); launches of a few workgroups:
+// latency, so RPW is 4 instead of 16 where 64-row workgroups would leave CUs
+// idle.  With one row at a time and the vector entries in registers, reloaded by
+// every wave, six workgroups of 128-entry rows took 8.7 us, now 4.2 us.
+// ------------------------------------------------------------------------
+template <typename T, int R, int RPW>
+__global__ __launch_bounds__(256) void k_tipmv(const GemvProb* __restrict__ probs, int nprob,
+                                               int64_t ldx, int64_t ldy,
+                                               const double* __restrict__ dotv,
+                                               double* __restrict__ partial,
+                                               const int32_t* __restrict__ stop) {
+  constexpr int VEC = 16 / sizeof(T);
+  constexpr int SB = 16 / RPW;                  // workgroups per 64 rows
+  typedef T vec_t __attribute__((ext_vector_type(VEC)));
+  extern __shared__ __attribute__((aligned(16))) double xs[];   // [columns][R]
+  __shared__ double red[4][R][2];
+  if (stop) {
+    bool all = true;
+#pragma unroll
+    for (int j = 0; j < R; ++j) all &= stop[j] != KS_RUNNING;
+    if (all) return;
+  }
+  const int wg = blockIdx.x / SB;
+  const GemvProb& P = probs[find_gemv(probs, nprob, wg, gridDim.x / SB)];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int fl = P.flags;
+  const int cb = P.cb, ce = P.ce, split = P.split, nc = ce - cb;
+  const int rbase = (wg - P.wg0) * 64 + (blockIdx.x % SB) * (64 / SB) + wave * RPW;
+  for (int i = tid; i < nc * R; i += 256) {
+    const int c = cb + i % nc, j = i / nc;
+    xs[(c - cb) * R + j] = c < split ? P.x1[c + j * ldx] : P.x2[(c - split) + j * ldx];
+  }
+  __syncthreads();
+  const T* __restrict__ A0 = (const T*)P.A + cb;
+  const int64_t lda = P.lda;
+  double mine[R];   // lane rr < RPW: the sum of the wave's row rr
+#pragma unroll
+  for (int j = 0; j < R; ++j) mine[j] = 0.0;
+#pragma unroll 1
+  for (int rr = 0; rr < RPW; rr += 4) {
+    const T* __restrict__ Arow = A0 + (int64_t)(rbase + rr) * lda;
+    double acc[4][R];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < R; ++j) acc[i][j] = 0.0;
+    // 2t and the column range are multiples of 64, so a lane's piece lies
+    // inside the row or outside it
+    for (int c0 = lane * VEC; c0 < nc; c0 += 2 * 64 * VEC) {
+      vec_t a[2][4];
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int c = c0 + h * 64 * VEC;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) a[h][i] = c < nc ? *(const vec_t*)(Arow + i * lda + c) : vec_t{};
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int c = c0 + h * 64 * VEC;
+        if (c >= nc) continue;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e)
+#pragma unroll
+          for (int j = 0; j < R; ++j) {
+            const double xv = xs[(c + e) * R + j];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[i][j] += (double)a[h][i][e] * xv;
+          }
+      }
+    }
+    // four sums at once: lanes with bit 5 set continue with rows 2 and 3,
+    // then lanes with bit 4 set with the odd row of the pair
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      const bool h5 = lane & 32, h4 = lane & 16;
+      const double s0 = (h5 ? acc[2][j] : acc[0][j]) + __shfl_xor(h5 ? acc[0][j] : acc[2][j], 32, 64);
+      const double s1 = (h5 ? acc[3][j] : acc[1][j]) + __shfl_xor(h5 ? acc[1][j] : acc[3][j], 32, 64);
+      double v = (h4 ? s1 : s0) + __shfl_xor(h4 ? s0 : s1, 16, 64);
+      for (int off = 8; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+      // row i's sum is in lanes 16 i .. 16 i + 15
+      const double w = __shfl(v, (lane & 3) * 16, 64);
+      mine[j] = (lane >= rr && lane < rr + 4) ? w : mine[j];
     }
   }
   double dot[R], dd[R];
@@ -381,8 +522,114 @@ __global__ __launch_bounds__(256) void k_tipmv(const GemvProb* __restrict__ prob
     __syncthreads();
     if (tid < R) {
       const int j = tid;
-      partial[((int64_t)wg * R + j) * 2 + 0] = (red[0][j][0] + red[1][j][0]) + (red[2][j][0] + red[3][j][0]);
-      partial[((int64_t)wg * R + j) * 2 + 1] = (red[0][j][1] + red[1][j][1]) + (red[2][j][1] + red[3][j][1]);
+      partial[((int64_t)blockIdx.x * R + j) * 2 + 0] = (red[0][j][0] + red[1][j][0]) + (red[2][j][0] + red[3][j][0]);
+      partial[((int64_t)blockIdx.x * R + j) * 2 + 1] = (red[0][j][1] + red[1][j][1]) + (red[2][j][1] + red[3][j][1]);
+    }
+  }
+}
+
+// The same product for launches that fill the GPU: the four waves of a
+// workgroup split the columns instead of the rows, so that the workgroup
+// streams its 64 rows one after another as one contiguous run, and a wave's
+// vector entries (NS pieces of 64 VEC columns) stay in registers.  A wave
+// reduces its part of eight rows at a time; the four parts of a row are added
+// in LDS.  1.06 GB of f32 tips take 175 us (6.0 TB/s; by rows 187 us).
+template <typename T, int R, int NS>
+__global__ __launch_bounds__(256) void k_tipmv_c(const GemvProb* __restrict__ probs, int nprob,
+                                                 int64_t ldx, int64_t ldy,
+                                                 const double* __restrict__ dotv,
+                                                 double* __restrict__ partial,
+                                                 const int32_t* __restrict__ stop) {
+  constexpr int VEC = 16 / sizeof(T);
+  constexpr int RB = NS * R <= 2 ? 8 : 4;       // rows in flight
+  typedef T vec_t __attribute__((ext_vector_type(VEC)));
+  __shared__ double red[4][64][R];
+  if (stop) {
+    bool all = true;
+#pragma unroll
+    for (int j = 0; j < R; ++j) all &= stop[j] != KS_RUNNING;
+    if (all) return;
+  }
+  const int wg = blockIdx.x;
+  const GemvProb& P = probs[find_gemv(probs, nprob, wg, gridDim.x)];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int cb = P.cb, split = P.split, nc = P.ce - cb;
+  const int r0 = (wg - P.wg0) * 64;
+  const int64_t lda = P.lda;
+  const T* __restrict__ A0 = (const T*)P.A + (int64_t)r0 * lda + cb;
+  // this lane's columns: piece s starts at (4 s + wave) * 64 VEC + lane VEC
+  int c[NS];
+  double x[NS][VEC][R];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    c[s] = ((4 * s + wave) * 64 + lane) * VEC;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e)
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        const int cc = cb + c[s] + e;
+        x[s][e][j] = c[s] < nc ? (cc < split ? P.x1[cc + j * ldx] : P.x2[(cc - split) + j * ldx]) : 0.0;
+      }
+    c[s] = c[s] < nc ? c[s] : 0;   // past the row: any of its pieces, times zero
+  }
+#pragma unroll 1
+  for (int rr = 0; rr < 64; rr += RB) {
+    const T* __restrict__ Arow = A0 + (int64_t)rr * lda;
+    vec_t a[RB][NS];
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int s = 0; s < NS; ++s) a[i][s] = *(const vec_t*)(Arow + i * lda + c[s]);
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      double v[RB];
+#pragma unroll
+      for (int i = 0; i < RB; ++i) {
+        v[i] = 0.0;
+#pragma unroll
+        for (int s = 0; s < NS; ++s)
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) v[i] += (double)a[i][s][e] * x[s][e][j];
+      }
+      // RB sums at once: at each step a lane keeps half of its rows and hands
+      // the other half's sums to its partner
+      int off = 32;
+#pragma unroll
+      for (int n = RB / 2; n > 0; n >>= 1, off >>= 1) {
+        const bool up = lane & off;
+#pragma unroll
+        for (int i = 0; i < n; ++i) {
+          const double keep = up ? v[i + n] : v[i], give = up ? v[i] : v[i + n];
+          v[i] = keep + __shfl_xor(give, off, 64);
+        }
+      }
+      for (; off > 0; off >>= 1) v[0] += __shfl_xor(v[0], off, 64);
+      // lanes with equal lane / (64 / RB) hold row rr + lane / (64 / RB)
+      if (lane % (64 / RB) == 0) red[wave][rr + lane / (64 / RB)][j] = v[0];
+    }
+  }
+  __syncthreads();
+  if (tid < 64) {
+    const int fl = P.flags, r = r0 + lane;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      double v = (red[0][lane][j] + red[1][lane][j]) + (red[2][lane][j] + red[3][lane][j]);
+      if (fl & V_MASK) v *= P.mask[r];
+      if (fl & V_NEG) v = -v;
+      if (fl & V_YIN) v += P.yin[r + j * ldy];
+      P.yout[r + j * ldy] = v;
+      if (fl & (V_DOT | V_DOT2)) {
+        double d = (fl & V_DOT) ? dotv[P.dot_off + r + j * ldy] * v : 0.0, dd = (fl & V_DOT2) ? v * v : 0.0;
+        for (int off = 32; off > 0; off >>= 1) {
+          d += __shfl_xor(d, off, 64);
+          dd += __shfl_xor(dd, off, 64);
+        }
+        if (lane == 0) {
+          partial[((int64_t)wg * R + j) * 2 + 0] = d;
+          partial[((int64_t)wg * R + j) * 2 + 1] = dd;
+        }
+      }
     }
   }
 }
@@ -416,36 +663,50 @@ __global__ __launch_bounds__(256) void k_pack_tips(const BlockInfo* __restrict__
   }
 }
 
-// segments of 64 x (16-byte piece) per row: 2t elements need ceil(2t / (64 VEC))
-int tipmv_segments(int dtype, int t) {
-  const int vec = dtype == 0 ? 2 : 4;
-  const int need = (2 * t + 64 * vec - 1) / (64 * vec);
-  for (int n : {4, 8, 16})
-    if (need <= n) return n;
-  return 0;   // longer rows: the product on the spikes themselves
-}
+// whether rows of 2t entries are kept packed (at most 16 KiB each)
+bool tipmv_packs(int dtype, int t) { return 2 * t * (dtype == 0 ? 8 : 4) <= 16384; }
 
-template <typename T, int NSEG>
-static void tipmv_dispatch(int nrhs, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
-                           int64_t ldy, const double* dotv, double* partial, const int32_t* stop,
-                           hipStream_t s) {
-  if (nrhs == 1)
-    hipLaunchKernelGGL((k_tipmv<T, 1, NSEG>), dim3(nwg), dim3(256), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop);
-  else
-    hipLaunchKernelGGL((k_tipmv<T, 2, NSEG>), dim3(nwg), dim3(256), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop);
-}
+// Workgroups (and partial sums) per 64 rows: four of 16 rows each where
+// 64-row workgroups would leave CUs idle.  Four against one, in us: f64 rows of
+// 512 entries on 120 workgroups 5.8 / 8.3, but of 2048 on 224 47.7 / 39.6 (a
+// CU's workgroups read the same vector entries again); f32 (one: the column
+// split) 1024 entries on 240 16.9 / 20.5, on 496 27.4 / 24.6.
+int tipmv_split(int dtype, int nwg) { return nwg <= (dtype == 0 ? 128 : 256) ? 4 : 1; }
 
-void launch_tipmv(int dtype, int nrhs, int nseg, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
+void launch_tipmv(int dtype, int nrhs, int t, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
                   int64_t ldy, const double* dotv, double* partial, const int32_t* stop, hipStream_t s) {
   if (nwg <= 0 || nprob <= 0) return;
-#define DDPS_TIPMV(T)                                                                                   \
-  switch (nseg) {                                                                                       \
-    case 4: tipmv_dispatch<T, 4>(nrhs, probs, nprob, nwg, ldx, ldy, dotv, partial, stop, s); break;     \
-    case 8: tipmv_dispatch<T, 8>(nrhs, probs, nprob, nwg, ldx, ldy, dotv, partial, stop, s); break;     \
-    default: tipmv_dispatch<T, 16>(nrhs, probs, nprob, nwg, ldx, ldy, dotv, partial, stop, s); break;   \
+  const int sb = tipmv_split(dtype, nwg);
+  const size_t lds = (size_t)2 * t * (nrhs == 1 ? 1 : 2) * sizeof(double);
+#define DDPS_TIPMV(...) \
+  hipLaunchKernelGGL((__VA_ARGS__), dim3(nwg), dim3(256), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop)
+#define DDPS_TIPMV_S(...) \
+  hipLaunchKernelGGL((__VA_ARGS__), dim3(nwg * sb), dim3(256), lds, s, probs, nprob, ldx, ldy, dotv, partial, stop)
+#define DDPS_TIPMV_C(T, R)                                 \
+  switch (ns) {                                            \
+    case 1: DDPS_TIPMV(k_tipmv_c<T, R, 1>); break;         \
+    case 2: DDPS_TIPMV(k_tipmv_c<T, R, 2>); break;         \
+    case 3: DDPS_TIPMV(k_tipmv_c<T, R, 3>); break;         \
+    default: DDPS_TIPMV(k_tipmv_c<T, R, 4>); break;        \
   }
-  if (dtype == 0) { DDPS_TIPMV(double) }
-  else { DDPS_TIPMV(float) }
+  if (dtype == 0) {
+    if (nrhs == 1) {
+      if (sb == 4) DDPS_TIPMV_S(k_tipmv<double, 1, 4>);
+      else DDPS_TIPMV_S(k_tipmv<double, 1, 16>);
+    } else {
+      if (sb == 4) DDPS_TIPMV_S(k_tipmv<double, 2, 4>);
+      else DDPS_TIPMV_S(k_tipmv<double, 2, 16>);
+    }
+  } else if (sb == 4) {
+    if (nrhs == 1) DDPS_TIPMV_S(k_tipmv<float, 1, 4>);
+    else DDPS_TIPMV_S(k_tipmv<float, 2, 4>);
+  } else {
+    const int ns = (2 * t + 1023) / 1024;
+    if (nrhs == 1) { DDPS_TIPMV_C(float, 1) }
+    else { DDPS_TIPMV_C(float, 2) }
+  }
+#undef DDPS_TIPMV_C
+#undef DDPS_TIPMV_S
 #undef DDPS_TIPMV
 }
 
@@ -488,7 +749,7 @@ __global__ __launch_bounds__(256) void k_gemv_mf32(const GemvProb* __restrict__ 
     if (all) return;
   }
   const int wg = blockIdx.x;
-  const GemvProb P = probs[find_gemv(probs, nprob, wg)];
+  const GemvProb P = probs[find_gemv(probs, nprob, wg, gridDim.x)];
   const int r0 = (wg - P.wg0) * 64;
   int cb = P.cb, ce = P.ce;
   if (P.tri == 1) ce = min(ce, r0 + 64);
@@ -596,15 +857,30 @@ template <typename T>
 static void gemv_dispatch(int nrhs, bool wide, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
                           int64_t ldy, const double* dotv, double* partial, const int32_t* stop,
                           hipStream_t s) {
-#define DDPS_GEMV(K)                                                                                           \
-  switch (nrhs) {                                                                                              \
-    case 1: hipLaunchKernelGGL((K<T, 1>), dim3(nwg), dim3(256), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop); break; \
-    case 2: hipLaunchKernelGGL((K<T, 2>), dim3(nwg), dim3(256), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop); break; \
-    case 4: hipLaunchKernelGGL((K<T, 4>), dim3(nwg), dim3(256), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop); break; \
-    default: hipLaunchKernelGGL((K<T, 8>), dim3(nwg), dim3(256), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop); break; \
+#define DDPS_GEMV(...) \
+  hipLaunchKernelGGL((__VA_ARGS__), dim3(nwg), dim3(threads), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop)
+  // one workgroup per CU or fewer: sixteen waves each, so that a short launch
+  // has all its loads in flight at once; beyond, four fill the CUs with less
+  // to add up.  Sixteen against four on f64 triangles of 512 rows, in us: 128
+  // workgroups 7.0 / 11.9, 512 workgroups 20.8 / 19.3 (f32 14.2 / 11.7); of 64
+  // rows on 2000 23.8 / 12.7
+  const bool big = wide && nrhs <= 2 && nwg <= 256;
+  const int threads = big ? 1024 : 256;
+  if (wide) {
+    switch (nrhs) {
+      case 1: if (big) DDPS_GEMV(k_gemv_n<T, 1, 16>); else DDPS_GEMV(k_gemv_n<T, 1, 4>); break;
+      case 2: if (big) DDPS_GEMV(k_gemv_n<T, 2, 16>); else DDPS_GEMV(k_gemv_n<T, 2, 4>); break;
+      case 4: DDPS_GEMV(k_gemv_w<T, 4>); break;
+      default: DDPS_GEMV(k_gemv_w<T, 8>); break;
+    }
+    return;
   }
-  if (wide) { DDPS_GEMV(k_gemv_w) }
-  else { DDPS_GEMV(k_gemv) }
+  switch (nrhs) {
+    case 1: DDPS_GEMV(k_gemv<T, 1>); break;
+    case 2: DDPS_GEMV(k_gemv<T, 2>); break;
+    case 4: DDPS_GEMV(k_gemv<T, 4>); break;
+    default: DDPS_GEMV(k_gemv<T, 8>); break;
+  }
 #undef DDPS_GEMV
 }
 
@@ -613,9 +889,9 @@ void launch_gemv(int dtype, int nrhs, int form, const GemvProb* probs, int nprob
   if (nwg <= 0 || nprob <= 0) return;
   if (dtype == 1 && form == 2 && nrhs >= 4) {
     if (nrhs == 4)
-      hipLaunchKernelGGL((k_gemv_mf32<4>), dim3(nwg), dim3(256), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop);
+      hipLaunchKernelGGL(k_gemv_mf32<4>, dim3(nwg), dim3(256), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop);
     else
-      hipLaunchKernelGGL((k_gemv_mf32<8>), dim3(nwg), dim3(256), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop);
+      hipLaunchKernelGGL(k_gemv_mf32<8>, dim3(nwg), dim3(256), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop);
     return;
   }
   if (dtype == 0) gemv_dispatch<double>(nrhs, form >= 1, probs, nprob, nwg, ldx, ldy, dotv, partial, stop, s);

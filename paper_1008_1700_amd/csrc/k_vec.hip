@@ -99,6 +99,53 @@ __device__ __forceinline__ double sum_of(const double* __restrict__ sums, int j,
   return sums[2 * j + q];
 }
 
+// The sums of a reduction in every thread of a workgroup: read from `sums`
+// when they have been reduced (W = 0), else added up from the [W][R][2]
+// partials in the order of k_reduce2, the same in every workgroup, with
+// workgroup 0 leaving them in `sums` for later kernels.  For few partials
+// this is quicker than a launch of its own (4.7 us and the gap before it).
+template <int R>
+__device__ __forceinline__ void take_sums(int W, const double* __restrict__ part, double* __restrict__ sums,
+                                          double (&v)[R][2], double (*sh)[R][2]) {
+  if (W == 0) {
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      v[j][0] = sums[2 * j];
+      v[j][1] = sums[2 * j + 1];
+    }
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < R; ++j) v[j][0] = v[j][1] = 0.0;
+  for (int w = threadIdx.x; w < W; w += 256)
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      v[j][0] += part[((int64_t)w * R + j) * 2 + 0];
+      v[j][1] += part[((int64_t)w * R + j) * 2 + 1];
+    }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int j = 0; j < R; ++j)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      double x = v[j][q];
+      for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+      if (lane == 0) sh[wave][j][q] = x;
+    }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < R; ++j)
+#pragma unroll
+    for (int q = 0; q < 2; ++q) v[j][q] = sh[0][j][q] + sh[1][j][q] + sh[2][j][q] + sh[3][j][q];
+  __syncthreads();
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      sums[2 * j] = v[j][0];
+      sums[2 * j + 1] = v[j][1];
+    }
+}
+
 // ------------------------------------------------------------ layout moves
 __device__ __forceinline__ int find_voff(const BlockInfo* __restrict__ b, int p, int64_t q) {
   int lo = 0, hi = p - 1;
@@ -204,17 +251,18 @@ __device__ __forceinline__ bool s_ok(const KState* st, int it, int j, double rtv
 
 // s = r - alpha v, alpha = rho / (r~.v); partial s.s
 template <int R>
-__global__ __launch_bounds__(256) void k_bicg_s(int it, int64_t m, const double* __restrict__ s1,
-                                                KState* __restrict__ st, const double* __restrict__ r,
+__global__ __launch_bounds__(256) void k_bicg_s(int it, int64_t m, int w1, const double* __restrict__ p1,
+                                                double* __restrict__ s1, KState* __restrict__ st, const double* __restrict__ r,
                                                 const double* __restrict__ v, double* __restrict__ s,
                                                 double* __restrict__ part) {
   __shared__ double sh[4][R][2];
-  double al[R];
+  double al[R], v1[R][2];
   bool run[R];
   bool any = false;
+  take_sums<R>(w1, p1, s1, v1, sh);
 #pragma unroll
   for (int j = 0; j < R; ++j) {
-    run[j] = s_ok(st, it, j, sum_of(s1, j, 0), al[j]);
+    run[j] = s_ok(st, it, j, v1[j][0], al[j]);
     any |= run[j];
   }
   __syncthreads();
@@ -249,8 +297,8 @@ __global__ __launch_bounds__(256) void k_bicg_s(int it, int64_t m, const double*
 // x += alpha p + omega s, r = s - omega t; partials (r.r, r~.r)
 template <int R>
 __global__ __launch_bounds__(256) void k_bicg_xr(int it, int64_t m, double tol, const double* __restrict__ s1,
-                                                 const double* __restrict__ s2,
-                                                 const double* __restrict__ s3,
+                                                 int w2, const double* __restrict__ p2, double* __restrict__ s2,
+                                                 int w3, const double* __restrict__ p3, double* __restrict__ s3,
                                                  KState* __restrict__ st, double* __restrict__ x,
                                                  const double* __restrict__ /*p: the update uses px*/,
                                                  const double* __restrict__ s,
@@ -259,13 +307,15 @@ __global__ __launch_bounds__(256) void k_bicg_xr(int it, int64_t m, double tol, 
                                                  const double* __restrict__ px, const double* __restrict__ sx) {
   // px, sx: the directions added to x (M^{-1}p, M^{-1}s when preconditioned, else p, s)
   __shared__ double sh[4][R][2];
-  double al[R], om[R];
+  double al[R], om[R], v2[R][2], v3[R][2];
   bool run[R], half[R];
+  take_sums<R>(w2, p2, s2, v2, sh);
+  take_sums<R>(w3, p3, s3, v3, sh);
 #pragma unroll
   for (int j = 0; j < R; ++j) {
     const bool ok = s_ok(st, it, j, sum_of(s1, j, 0), al[j]);
-    const double ts = sum_of(s3, j, 0), tt = sum_of(s3, j, 1);
-    half[j] = ok && sqrt(sum_of(s2, j, 0)) / st->ref[j] <= tol;
+    const double ts = v3[j][0], tt = v3[j][1];
+    half[j] = ok && sqrt(v2[j][0]) / st->ref[j] <= tol;
     run[j] = ok && !half[j];
     om[j] = tt != 0.0 ? ts / tt : 0.0;
   }
@@ -309,10 +359,13 @@ template <int R>
 __global__ __launch_bounds__(256) void k_bicg_p(int it, int maxit, int64_t m, double tol,
                                                 const double* __restrict__ s1,
                                                 const double* __restrict__ s2,
-                                                const double* __restrict__ s3,
-                                                const double* __restrict__ s4,
+                                                const double* __restrict__ s3, int w4,
+                                                const double* __restrict__ p4, double* __restrict__ s4,
                                                 KState* __restrict__ st, const double* __restrict__ r,
                                                 double* __restrict__ p, const double* __restrict__ v) {
+  __shared__ double sh[4][R][2];
+  double v4[R][2];
+  take_sums<R>(w4, p4, s4, v4, sh);
   double be[R], om[R], rho_new[R], res[R];
   int32_t nst[R], it2[R];
   bool cont[R];
@@ -326,7 +379,7 @@ __global__ __launch_bounds__(256) void k_bicg_p(int it, int maxit, int64_t m, do
     const double ress = sqrt(sum_of(s2, j, 0)) / ref;
     const double ts = sum_of(s3, j, 0), tt = sum_of(s3, j, 1);
     om[j] = tt != 0.0 ? ts / tt : 0.0;
-    rho_new[j] = sum_of(s4, j, 1);
+    rho_new[j] = v4[j][1];
     const double rho_old = st->rho[it & 1][j];
     be[j] = (rho_new[j] / rho_old) * (al / om[j]);
     res[j] = st->res[j];
@@ -338,7 +391,7 @@ __global__ __launch_bounds__(256) void k_bicg_p(int it, int maxit, int64_t m, do
     } else if (ress <= tol) {
       nst[j] = KS_CONVERGED; it2[j] = 2 * it - 1; res[j] = ress;
     } else {
-      res[j] = sqrt(sum_of(s4, j, 0)) / ref;
+      res[j] = sqrt(v4[j][0]) / ref;
       it2[j] = 2 * it;
       if (res[j] <= tol) nst[j] = KS_CONVERGED;
       else if (om[j] == 0.0 || rho_new[j] == 0.0 || !isfinite(be[j])) nst[j] = KS_BREAKDOWN;
@@ -537,17 +590,37 @@ __global__ __launch_bounds__(256) void k_sum_parts(int rows, int R, int ns, cons
   }
 }
 
-// Reduce [W][R][4] residual partials to out[R][4] (max, sum, max, sum).
+// Reduce [W][R][4] residual partials to out[R][4] (max, sum, max, sum): one
+// workgroup; thread (g, c) takes component c of w = g, g + G, ... in order,
+// eight loads at a time, then the G groups are added in a fixed tree.  (One
+// thread per column walking all 1024 partials took 144 us for one column,
+// 243 us for eight.)
 template <int R>
-__global__ void k_resid_reduce(int W, const double* __restrict__ part, double* __restrict__ out) {
-  const int j = threadIdx.x;
-  if (j >= R) return;
-  double a0 = 0, a1 = 0, a2 = 0, a3 = 0;
-  for (int w = 0; w < W; ++w) {
-    const double* o = part + ((int64_t)w * R + j) * 4;
-    a0 = fmax(a0, o[0]); a1 += o[1]; a2 = fmax(a2, o[2]); a3 += o[3];
+__global__ __launch_bounds__(1024) void k_resid_reduce(int W, const double* __restrict__ part,
+                                                       double* __restrict__ out) {
+  constexpr int C = 4 * R, G = 1024 / C;
+  __shared__ double sh[1024];
+  const int tid = threadIdx.x, c = tid % C, g = tid / C;
+  const bool mx = (c & 1) == 0;
+  double a = 0.0;
+  for (int w0 = g; w0 < W; w0 += 8 * G) {
+    double x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = w0 + u * G < W ? part[(int64_t)(w0 + u * G) * C + c] : 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) a = mx ? fmax(a, x[u]) : a + x[u];
   }
-  out[j * 4 + 0] = a0; out[j * 4 + 1] = a1; out[j * 4 + 2] = a2; out[j * 4 + 3] = a3;
+  sh[tid] = a;
+  __syncthreads();
+  for (int h = G / 2; h > 0; h >>= 1) {
+    if (g < h) {
+      const double b = sh[tid + h * C];
+      a = mx ? fmax(a, b) : a + b;
+      sh[tid] = a;
+    }
+    __syncthreads();
+  }
+  if (g == 0) out[c] = a;
 }
 
 // out = a X + b Y + c Z (per column coefficients); Z may be null
@@ -653,20 +726,20 @@ void bicg_init(int R, int64_t m, int use_guess, const double* gh, double* x, con
 void bicg_init_state(int R, int k, double tol, const double* sums, KState* st, hipStream_t s) {
   DDPS_R_DISPATCH(R, hipLaunchKernelGGL(k_bicg_init_state<RR>, dim3(1), dim3(64), 0, s, k, tol, sums, st));
 }
-void bicg_s(int R, int it, int64_t m, const double* s1, KState* st, const double* r, const double* v,
+void bicg_s(int R, int it, int64_t m, PartSums s1, KState* st, const double* r, const double* v,
             double* sv, double* part, int W, hipStream_t s) {
-  DDPS_R_DISPATCH(R, hipLaunchKernelGGL(k_bicg_s<RR>, dim3(W), dim3(256), 0, s, it, m, s1, st, r, v, sv, part));
+  DDPS_R_DISPATCH(R, hipLaunchKernelGGL(k_bicg_s<RR>, dim3(W), dim3(256), 0, s, it, m, s1.W, s1.part, s1.sums, st, r, v, sv, part));
 }
-void bicg_xr(int R, int it, int64_t m, double tol, const double* s1, const double* s2, const double* s3,
+void bicg_xr(int R, int it, int64_t m, double tol, const double* s1, PartSums s2, PartSums s3,
              KState* st, double* x, const double* p, const double* sv, const double* t, double* r,
              const double* rt, double* part, int W, hipStream_t s, const double* px, const double* sx) {
-  DDPS_R_DISPATCH(R, hipLaunchKernelGGL(k_bicg_xr<RR>, dim3(W), dim3(256), 0, s, it, m, tol, s1, s2, s3, st, x, p, sv, t, r, rt, part,
+  DDPS_R_DISPATCH(R, hipLaunchKernelGGL(k_bicg_xr<RR>, dim3(W), dim3(256), 0, s, it, m, tol, s1, s2.W, s2.part, s2.sums, s3.W, s3.part, s3.sums, st, x, p, sv, t, r, rt, part,
                                         px ? px : p, sx ? sx : sv));
 }
 void bicg_p(int R, int it, int maxit, int64_t m, double tol, const double* s1, const double* s2,
-            const double* s3, const double* s4, KState* st, const double* r, double* p, const double* v,
+            const double* s3, PartSums s4, KState* st, const double* r, double* p, const double* v,
             int W, hipStream_t s) {
-  DDPS_R_DISPATCH(R, hipLaunchKernelGGL(k_bicg_p<RR>, dim3(W), dim3(256), 0, s, it, maxit, m, tol, s1, s2, s3, s4, st, r, p, v));
+  DDPS_R_DISPATCH(R, hipLaunchKernelGGL(k_bicg_p<RR>, dim3(W), dim3(256), 0, s, it, maxit, m, tol, s1, s2, s3, s4.W, s4.part, s4.sums, st, r, p, v));
 }
 void bicg_restart(int R, int it, int64_t m, const int32_t* flag, const double* r, double* rt, double* p,
                   double* part, int W, double* sums, KState* st, hipStream_t s) {
@@ -678,7 +751,7 @@ void csr_resid(int R, int64_t n, const int64_t* row_ptr, const int32_t* col, con
                const double* x, int64_t ldx, const double* f, int64_t ldf, double* r, int64_t ldr,
                double* part, int W, double* out, hipStream_t s) {
   DDPS_R_DISPATCH(R, hipLaunchKernelGGL(k_csr_resid<RR>, dim3(W), dim3(256), 0, s, n, row_ptr, col, val, x, ldx, f, ldf, r, ldr, part));
-  DDPS_R_DISPATCH(R, hipLaunchKernelGGL(k_resid_reduce<RR>, dim3(1), dim3(64), 0, s, W, part, out));
+  DDPS_R_DISPATCH(R, hipLaunchKernelGGL(k_resid_reduce<RR>, dim3(1), dim3(1024), 0, s, W, part, out));
 }
 // Residual norms of k <= 8 columns in column groups of 8, 4, 2 and 1 (the
 // kernels' widths), each group through the same two kernels as the outer
