@@ -123,12 +123,14 @@ struct ddps_ctx {
   // ilu_batches lists the blocks batch after batch (d_ibatch, same order)
   bool ilu = false;
   double* d_fv = nullptr;
+  void* d_ipack = nullptr;      // factors in level order, for solves in LDS (null: not kept)
   int64_t *d_ilo = nullptr, *d_idg = nullptr, *d_ihi = nullptr, *d_lptr = nullptr, *d_uptr = nullptr;
   int32_t *d_lrows = nullptr, *d_urows = nullptr, *d_ibatch = nullptr;
   int64_t *d_lq = nullptr, *d_uq = nullptr;   // entry ranges per level-ordered row (pairs)
   IluBlock* d_iblk = nullptr;
   void* d_iws = nullptr;
   int64_t ilu_nmax = 0, ilu_nnz = 0, ilu_levels = 0;
+  int ilu_wmax = 0;   // rows of the widest level
   std::vector<std::pair<int, int>> ilu_batches;   // (first entry in d_ibatch, blocks)
   int R = 1;
   // device data
@@ -1308,6 +1310,9 @@ int enqueue_factor_ilu(ddps_ctx* h) {
   if (rc) return rc;
   ilu_factor(h->p, h->d_iblk, h->d_lrows, h->d_lptr, h->d_ilo, h->d_idg, h->d_ihi, h->d_col, h->d_val, h->d_fv,
              h->d_thresh, h->d_bad, f);
+  if (h->d_ipack)
+    ilu_pack(h->p, h->ilu_nmax, h->n, h->d_iblk, h->d_lrows, h->d_lq, h->d_urows, h->d_uq, h->d_col, h->d_fv,
+             ilu_packed(h->d_ipack, h->n), f);
   if (h->tips_only)
     for (const auto& b : h->ilu_batches)
       ilu_spikes(h->sdt, b.second, h->d_iblk, h->d_ibatch + b.first, h->p, h->t, h->d_rhs, h->d_ilo, h->d_idg,
@@ -1469,8 +1474,13 @@ int block_solves(ddps_ctx* h, int tk) {
   }
   hipEvent_t a;
   h->tim_begin(tk, a);
-  ilu_solve(h->p, h->d_iblk, h->d_lrows, h->d_lptr, h->d_lq, h->d_urows, h->d_uptr, h->d_uq, h->d_col, h->d_fv,
-            h->d_ypad, h->Np, R, h->d_vpad, h->stream);
+  if (h->d_ipack)
+    ilu_solve_packed(h->p, h->ilu_nmax, h->n, h->ilu_wmax, h->d_iblk, h->d_lrows, h->d_lptr, h->d_lq, h->d_urows,
+                     h->d_uptr, h->d_uq, h->d_col, h->d_fv, ilu_packed(h->d_ipack, h->n), h->d_ypad, h->Np, R,
+                     h->stream);
+  else
+    ilu_solve(h->p, h->d_iblk, h->d_lrows, h->d_lptr, h->d_lq, h->d_urows, h->d_uptr, h->d_uq, h->d_col, h->d_fv,
+              h->d_ypad, h->Np, R, h->d_vpad, h->stream);
   // both triangles once (values and column indices), each vector entry read and written per sweep
   h->tim_end(tk, a, 2.0 * (double)h->ilu_nnz * R, 12.0 * (double)h->ilu_nnz + 32.0 * (double)h->n * R);
   HIPCHK(hipGetLastError());
@@ -1884,6 +1894,7 @@ int ilu_plan(ddps_ctx* h, IluPlan& P) {
   P.blk.assign(p, IluBlock{});
   std::vector<int64_t> lev(n, 0), cnt;
   h->ilu_nmax = 0;
+  h->ilu_wmax = 0;
   h->ilu_nnz = 0;
   h->ilu_levels = 0;
   for (int i = 0; i < p; ++i) {
@@ -1924,6 +1935,7 @@ int ilu_plan(ddps_ctx* h, IluPlan& P) {
       beg = (int64_t)ptr.size();
       num = top;
       for (int64_t l = 0; l <= top; ++l) ptr.push_back(s0 + cnt[l]);
+      for (int64_t l = 0; l < top; ++l) h->ilu_wmax = std::max(h->ilu_wmax, (int)(cnt[l + 1] - cnt[l]));
       for (int64_t k = 0; k < B.n; ++k) {
         const int64_t r = fwd ? s0 + k : s1 - 1 - k;
         rows[s0 + cnt[lev[r]]++] = (int32_t)r;
@@ -2160,7 +2172,12 @@ int ddps_setup(ddps_handle* out, int64_t n, int32_t p, const int64_t* part_ptr, 
   }
   const size_t lu_bytes = (size_t)nlu * h->elt;
   const bool sep_lu = !h->ilu && nlu > 0 && need + lu_bytes <= budget;
+  const bool sep_ilu = h->ilu && ilu_packs(h->ilu_nmax) && need + (size_t)ilu_packed_bytes(n) <= budget;
   void* vp;
+  if (sep_ilu) {
+    if ((rc = h->alloc_raw(vp, (size_t)ilu_packed_bytes(n)))) return fail(rc);
+    h->d_ipack = vp;
+  }
   if (sep_lu) {
     if ((rc = h->alloc_raw(vp, lu_bytes))) return fail(rc);
     h->d_lu = vp;

@@ -138,6 +138,21 @@ void ilu_spikes(int dtype, int nb, const IluBlock* blocks, const int32_t* batch,
 void ilu_solve(int p, const IluBlock* blocks, const int32_t* lrows, const int64_t* lptr, const void* lq,
                const int32_t* urows, const int64_t* uptr, const void* uq, const int32_t* col, const double* fv,
                double* y, int64_t ldy, int R, double* yt, hipStream_t s);
+// The same on vectors held in LDS (blocks of up to nmax rows, ilu_packs(nmax);
+// wmax: rows of the widest level), from factors copied in level order by
+// ilu_pack after every factorisation into ilu_packed_bytes(n_all) bytes.
+struct IluPacked {
+  void *lpat, *upat, *lval, *uval;
+  double* piv;
+};
+int64_t ilu_packed_bytes(int64_t n_all);
+IluPacked ilu_packed(void* buf, int64_t n_all);
+bool ilu_packs(int64_t nmax);
+void ilu_pack(int p, int64_t nmax, int64_t n_all, const IluBlock* blocks, const int32_t* lrows, const void* lq,
+              const int32_t* urows, const void* uq, const int32_t* col, const double* fv, IluPacked P, hipStream_t s);
+void ilu_solve_packed(int p, int64_t nmax, int64_t n_all, int wmax, const IluBlock* blocks, const int32_t* lrows,
+                      const int64_t* lptr, const void* lq, const int32_t* urows, const int64_t* uptr, const void* uq,
+                      const int32_t* col, const double* fv, IluPacked P, double* y, int64_t ldy, int R, hipStream_t s);
 
 // ---------------------------------------------------------------- Krylov state
 constexpr int kMaxRhs = 8;

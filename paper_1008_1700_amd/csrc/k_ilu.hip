@@ -186,6 +186,7 @@ __global__ __launch_bounds__(kIluThreads) void k_ilu_tips(const IluBlock* __rest
 // then the vector entries), so a row costs three dependent loads, not two
 // per entry.
 constexpr int kSolveThreads = 1024;
+constexpr int64_t kIluLds = 160 * 1024;   // LDS of a workgroup
 
 // acc - sum over q in [q0, q1) of fv[q] * Yc[(col[q] - s) * R]
 __device__ __forceinline__ double row_dot(double acc, int64_t q0, int64_t q1, const int32_t* __restrict__ col,
@@ -256,6 +257,166 @@ __global__ __launch_bounds__(kSolveThreads) void k_ilu_solve(const IluBlock* __r
   }
 }
 
+// The same solves with one workgroup per block and right-hand side, for blocks
+// whose vector fits in LDS.  A level is then a few LDS reads, the rows'
+// arithmetic and a barrier.  What it reads from memory does not depend on the
+// solution and is loaded D levels ahead into registers; it is stored in level
+// order for that (k_ilu_pack), so that a wave reads consecutive pieces: read at
+// the CSR positions, a level of 200 rows moves some 1500 cache lines to one CU
+// and takes 1.07 us, packed see below.  Per slot of the level order
+//   pat: the block-local columns of the first four entries (n, where the LDS
+//        vector holds a zero, for entries the row does not have), the row, the
+//        entry count, 16 bits each
+//   val: two entries at slot j and two at slot n_all + j, then (backward) the
+//        pivots
+// Rows beyond the first NT of a level and entries beyond the fourth of a row
+// are read in place.  Every row's sum is taken in the order of k_ilu_solve, so
+// that both give the same bits.
+typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
+typedef double f64x2_t __attribute__((ext_vector_type(2)));
+
+__global__ __launch_bounds__(kIluThreads) void k_ilu_pack(const IluBlock* __restrict__ blocks, int64_t n_all,
+                                                            const int32_t* __restrict__ lrows,
+                                                            const longlong2* __restrict__ lq,
+                                                            const int32_t* __restrict__ urows,
+                                                            const longlong2* __restrict__ uq,
+                                                            const int32_t* __restrict__ col,
+                                                            const double* __restrict__ fv, IluPacked P) {
+  const IluBlock B = blocks[blockIdx.y];
+  const int64_t i = (int64_t)blockIdx.x * kIluThreads + threadIdx.x;
+  if (i >= B.n) return;
+  const int64_t j = B.s + i;
+#pragma unroll
+  for (int up = 0; up < 2; ++up) {
+    const longlong2 q = up ? uq[j] : lq[j];
+    const int64_t row = (up ? urows[j] : lrows[j]) - B.s, cnt = q.y - q.x;
+    unsigned c[4];
+    double v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      c[u] = u < cnt ? (unsigned)(col[q.x + u] - B.s) : (unsigned)B.n;
+      v[u] = u < cnt ? fv[q.x + u] : 0.0;
+    }
+    u32x4_t* pat = (u32x4_t*)(up ? P.upat : P.lpat);
+    f64x2_t* val = (f64x2_t*)(up ? P.uval : P.lval);
+    pat[j] = u32x4_t{c[0] | c[1] << 16, c[2] | c[3] << 16, (unsigned)row | (unsigned)(cnt < 65535 ? cnt : 65535) << 16, 0u};
+    val[j] = f64x2_t{v[0], v[1]};
+    val[n_all + j] = f64x2_t{v[2], v[3]};
+    if (up) P.piv[j] = fv[q.x - 1];
+  }
+}
+
+template <bool UP, int NT>
+__device__ __forceinline__ void ilu_sweep(double* Y, int64_t s, int n, int64_t n_all, int64_t num,
+                                          const int64_t* __restrict__ ptr, const int32_t* __restrict__ rows,
+                                          const longlong2* __restrict__ rq, const int32_t* __restrict__ col,
+                                          const double* __restrict__ fv, const u32x4_t* __restrict__ pat,
+                                          const f64x2_t* __restrict__ val, const double* __restrict__ piv) {
+  constexpr int D = 8;   // levels between loads and use
+  struct Row {
+    u32x4_t p;
+    f64x2_t v[2];
+    double piv;
+  };
+  const int tid = threadIdx.x, lane = tid & 63;
+  rows += s;
+  rq += s;
+  pat += s;
+  val += s;
+  piv += s;
+  // the level pointers of 128 levels from l0 on sit in two registers of a wave
+  auto offs = [&](int64_t l) __attribute__((always_inline)) { return (int)ptr[l < num ? l : num]; };
+  int cur = offs(lane), nxt = offs(64 + lane);
+  // first slot of level l0 + k, k < 128
+  auto at = [&](int k) __attribute__((always_inline)) {
+    const int a = __builtin_amdgcn_readlane(cur, k & 63), b = __builtin_amdgcn_readlane(nxt, k & 63);
+    return (k < 64 ? a : b) - (int)s;
+  };
+  auto fetch = [&](Row& F, int k) __attribute__((always_inline)) {
+    const int j = min(at(k) + tid, n - 1);
+    F.p = pat[j];
+    F.v[0] = val[j];
+    F.v[1] = val[n_all + j];
+    if (UP) F.piv = piv[j];
+  };
+  auto in_place = [&](double acc, int64_t q0, int64_t q1) __attribute__((always_inline)) {
+#pragma unroll 1
+    for (int64_t q = q0; q < q1; ++q) acc -= fv[q] * Y[col[q] - s];
+    return acc;
+  };
+  auto compute = [&](const Row& F, int k) __attribute__((always_inline)) {
+    const int e = at(k + 1);
+    int j = at(k) + tid;
+    if (j < e) {
+      const int y = F.p.z & 0xffff, cnt = F.p.z >> 16;
+      double acc = Y[y];
+      const double x0 = Y[F.p.x & 0xffff], x1 = Y[F.p.x >> 16], x2 = Y[F.p.y & 0xffff], x3 = Y[F.p.y >> 16];
+      acc -= F.v[0].x * x0;
+      acc -= F.v[0].y * x1;
+      acc -= F.v[1].x * x2;
+      acc -= F.v[1].y * x3;
+      if (cnt > 4) {
+        const longlong2 q = rq[j];
+        acc = in_place(acc, q.x + 4, q.y);
+      }
+      Y[y] = UP ? acc / F.piv : acc;
+#pragma unroll 1
+      for (j += NT; j < e; j += NT) {
+        const longlong2 q = rq[j];
+        const int yj = rows[j] - (int)s;
+        const double a = in_place(Y[yj], q.x, q.y);
+        Y[yj] = UP ? a / fv[q.x - 1] : a;
+      }
+    }
+  };
+  Row F[D];
+#pragma unroll
+  for (int u = 0; u < D; ++u) fetch(F[u], u);
+  int64_t l0 = 0;
+#pragma unroll 1
+  for (int64_t lv = 0; lv < num; lv += D) {
+    if (lv - l0 == 64) {
+      l0 = lv;
+      cur = nxt;
+      nxt = offs(l0 + 64 + lane);
+    }
+    const int k = (int)(lv - l0);
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      compute(F[u], k + u);
+      fetch(F[u], k + u + D);
+      // LDS writes done, then every wave; loads from memory stay in flight
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    }
+  }
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT) void k_ilu_solve_lds(const IluBlock* __restrict__ blocks, int p, int64_t n_all,
+                                                      const int32_t* __restrict__ lrows,
+                                                      const int64_t* __restrict__ lptr,
+                                                      const longlong2* __restrict__ lq,
+                                                      const int32_t* __restrict__ urows,
+                                                      const int64_t* __restrict__ uptr,
+                                                      const longlong2* __restrict__ uq,
+                                                      const int32_t* __restrict__ col,
+                                                      const double* __restrict__ fv, IluPacked P, double* y,
+                                                      int64_t ldy) {
+  extern __shared__ __attribute__((aligned(16))) double Y[];
+  const IluBlock B = blocks[blockIdx.x % p];
+  double* __restrict__ yc = y + (int64_t)(blockIdx.x / p) * ldy + B.vbase;
+  const int n = (int)B.n;
+  for (int r = threadIdx.x; r < n; r += NT) Y[r] = yc[r];
+  if (threadIdx.x == 0) Y[n] = 0.0;
+  __syncthreads();
+  ilu_sweep<false, NT>(Y, B.s, n, n_all, B.lnum, lptr + B.lbeg, lrows, lq, col, fv, (const u32x4_t*)P.lpat,
+                       (const f64x2_t*)P.lval, P.piv);
+  ilu_sweep<true, NT>(Y, B.s, n, n_all, B.unum, uptr + B.ubeg, urows, uq, col, fv, (const u32x4_t*)P.upat,
+                      (const f64x2_t*)P.uval, P.piv);
+  __syncthreads();
+  for (int r = threadIdx.x; r < n; r += NT) yc[r] = Y[r];
+}
+
 }  // namespace
 
 void ilu_factor(int p, const IluBlock* blocks, const int32_t* lrows, const int64_t* lptr, const int64_t* lo,
@@ -282,6 +443,37 @@ void ilu_spikes(int dtype, int nb, const IluBlock* blocks, const int32_t* batch,
     hipLaunchKernelGGL(k_ilu_tips<float>, g2, dim3(kIluThreads), 0, s, blocks, batch, p, t, (const float*)ws,
                        slot_elems, (float*)tips);
   }
+}
+
+int64_t ilu_packed_bytes(int64_t n_all) { return n_all * (2 * 16 + 4 * 16 + 8); }
+
+IluPacked ilu_packed(void* buf, int64_t n_all) {
+  char* c = (char*)buf;
+  return {c, c + 16 * n_all, c + 32 * n_all, c + 64 * n_all, (double*)(c + 96 * n_all)};
+}
+
+bool ilu_packs(int64_t nmax) { return (nmax + 1) * (int64_t)sizeof(double) <= kIluLds; }
+
+void ilu_pack(int p, int64_t nmax, int64_t n_all, const IluBlock* blocks, const int32_t* lrows, const void* lq,
+              const int32_t* urows, const void* uq, const int32_t* col, const double* fv, IluPacked P,
+              hipStream_t s) {
+  hipLaunchKernelGGL(k_ilu_pack, dim3((unsigned)((nmax + kIluThreads - 1) / kIluThreads), (unsigned)p),
+                     dim3(kIluThreads), 0, s, blocks, n_all, lrows, (const longlong2*)lq, urows,
+                     (const longlong2*)uq, col, fv, P);
+}
+
+void ilu_solve_packed(int p, int64_t nmax, int64_t n_all, int wmax, const IluBlock* blocks, const int32_t* lrows,
+                      const int64_t* lptr, const void* lq, const int32_t* urows, const int64_t* uptr, const void* uq,
+                      const int32_t* col, const double* fv, IluPacked P, double* y, int64_t ldy, int R,
+                      hipStream_t s) {
+  const size_t lds = (size_t)(nmax + 1) * sizeof(double);
+#define DDPS_ILU_LDS(NT)                                                                                              \
+  hipLaunchKernelGGL(k_ilu_solve_lds<NT>, dim3((unsigned)(p * R)), dim3(NT), lds, s, blocks, p, n_all, lrows, lptr, \
+                     (const longlong2*)lq, urows, uptr, (const longlong2*)uq, col, fv, P, y, ldy)
+  if (wmax <= 64) DDPS_ILU_LDS(64);
+  else if (wmax <= 256) DDPS_ILU_LDS(256);
+  else DDPS_ILU_LDS(512);
+#undef DDPS_ILU_LDS
 }
 
 void ilu_solve(int p, const IluBlock* blocks, const int32_t* lrows, const int64_t* lptr, const void* lq,
