@@ -16,10 +16,10 @@
 //
 // Spikes.  G_i = D~_i^{-1} R~_i has 2t dense columns per block; one thread
 // owns one column and runs both triangular solves down and up the block in
-// row order (no barriers: the columns are independent), in a row-major
-// workspace so that a wave's 64 columns of one row are one coalesced access.
-// Only the spike tips (first and last t rows) are kept, transposed into the
-// column-major tip store by an LDS-tiled copy.
+// row order (no barriers between waves: the columns are independent), in a
+// row-major workspace so that a wave's 64 columns of one row are one coalesced
+// access.  Only the spike tips (first and last t rows) are kept, transposed
+// into the column-major tip store by an LDS-tiled copy.
 #include "ddps_internal.h"
 
 namespace ddps {
@@ -72,69 +72,219 @@ __global__ __launch_bounds__(kIluThreads) void k_ilu0(const IluBlock* __restrict
 }
 
 // Spike columns of a batch of blocks: workgroup (x = position in the batch,
-// y = chunk of kIluThreads columns).  Column c < t is the left coupling
-// column c (right-hand side C_i(:, c) on the block's first t rows, upper
-// triangular: rows <= c), column c >= t the right coupling column c - t
-// (B_i(:, c - t) on the last t rows, lower triangular: rows >= c - t).  The
-// right-hand sides come from the compact coupling store, one t x (t+1) pair
-// per block (C_i at offset t, B_i at offset 0, leading dimension t).
+// y = chunk of 64 columns), one wave, a lane per column.  Column c < t is the
+// left coupling column c (right-hand side C_i(:, c) on the block's first t
+// rows, upper triangular: rows <= c), column c >= t the right coupling column
+// c - t (B_i(:, c - t) on the last t rows, lower triangular: rows >= c - t).
+// The right-hand sides come from the compact coupling store, one t x (t+1)
+// pair per block (C_i at offset t, B_i at offset 0, leading dimension t).
+//
+// The rows of a column are a serial chain; what a row needs besides the row
+// just finished is brought up before it.  The factor's rows are copied to LDS
+// kChunk at a time (a lane per row), each row's entries split by their distance:
+// entries up to kNear rows away are read from a ring of the last kNear rows in
+// LDS a row early, the row just finished from a register, farther ones from the
+// workspace kAhead rows early.  Rows with more than kNearMax or kFarMax of them
+// are read in place.  Values are always taken as stored (rounded to T), and each
+// row's entries in their stored order.
+//
+// Bound: one wave's instruction rate (a row is some 150 instructions), so the
+// waves are made small and many; up to 16 share a CU's LDS.  2048 columns of 32
+// blocks of 8192 rows take 5.9 ms, 24.1 ms with a load of every entry in the
+// chain; of 512 blocks 47 and 77 ms.
+constexpr int kNear = 16, kAhead = 8, kNearMax = 2, kFarMax = 4, kChunk = 32;
+
 template <typename T>
-__global__ __launch_bounds__(kIluThreads) void k_ilu_spikes(const IluBlock* __restrict__ blocks,
-                                                              const int32_t* __restrict__ batch, int t,
-                                                              const T* __restrict__ rhs, const int64_t* __restrict__ lo,
-                                                              const int64_t* __restrict__ dg,
-                                                              const int64_t* __restrict__ hi,
-                                                              const int32_t* __restrict__ col,
-                                                              const double* __restrict__ fv, T* ws,
-                                                              int64_t slot_elems) {
-  const int c = blockIdx.y * kIluThreads + threadIdx.x;
+struct IluRows {
+  int fk[2 * kChunk][kFarMax], nk[2 * kChunk][kNearMax], meta[2 * kChunk];
+  double fv[2 * kChunk][kFarMax], nv[2 * kChunk][kNearMax], piv[2 * kChunk];
+  T ring[kNear][64];
+};
+
+// One sweep over the rows row(s) = UP ? r1 - 1 - s : r0 + s, s < r1 - r0.
+// SRC: what a row starts from, 0: zero, 1: the right-hand side src (column
+// entry of row r at src[r]), rows with r < lo_ok or r > hi_ok zero, 2: the
+// workspace row itself.  last: the value of the row finished before.
+template <bool UP, int SRC, typename T>
+__device__ __forceinline__ void ilu_column_sweep(IluRows<T>& L, int r0, int r1, int kmin,
+                                                 const IluBlock& B, const int64_t* __restrict__ lo,
+                                                 const int64_t* __restrict__ dg, const int64_t* __restrict__ hi,
+                                                 const int32_t* __restrict__ col, const double* __restrict__ fv,
+                                                 const T* __restrict__ src, int lo_ok, int hi_ok, T* W, unsigned t2,
+                                                 T& last) {
+  const int lane = threadIdx.x;
+  const int len = r1 - r0;
+  if (len <= 0) return;
+  auto row = [&](int s) __attribute__((always_inline)) { return UP ? r1 - 1 - s : r0 + s; };
+  // rows s .. s + kChunk - 1 to LDS, one per lane, from their entry ranges
+  // [qa, qe) loaded before (those of the next rows are loaded here); more than
+  // kWide entries: read in place
+  constexpr int kWide = 8;
+  int64_t qa = 0, qe = 0;
+  auto range = [&](int s) __attribute__((always_inline)) {
+    const int64_t R = B.s + row(min(s + (lane & (kChunk - 1)), len - 1));
+    qa = UP ? dg[R] : lo[R];
+    qe = UP ? hi[R] : dg[R];
+  };
+  auto stage = [&](int s) __attribute__((always_inline)) {
+    int k[kWide];
+    double v[kWide];
+    const int64_t q0 = qa + (UP ? 1 : 0);
+    const int cnt = (int)min(qe - q0, (int64_t)kWide + 1);
+    const double pivot = UP ? fv[qa] : 0.0;
+#pragma unroll
+    for (int u = 0; u < kWide; ++u) {
+      const int64_t q = u < cnt ? q0 + u : qa;   // qa: the pivot or an entry before it
+      k[u] = col[q] - (int)B.s;
+      v[u] = fv[q];
+    }
+    range(s + kChunk);
+    __syncthreads();
+    if (lane < kChunk && s + lane < len) {
+      const int i = (s + lane) & (2 * kChunk - 1);
+      const int r = row(s + lane);
+      int nf = 0, nn = 0;
+      bool slow = cnt > kWide;
+#pragma unroll
+      for (int u = 0; u < kWide; ++u) {
+        if (u >= cnt || k[u] < kmin) continue;
+        if ((UP ? k[u] - r : r - k[u]) <= kNear) {
+          if (nn < kNearMax) {
+            L.nk[i][nn] = k[u];
+            L.nv[i][nn] = v[u];
+          } else slow = true;
+          ++nn;
+        } else {
+          if (nf < kFarMax) {
+            L.fk[i][nf] = k[u];
+            L.fv[i][nf] = v[u];
+          } else slow = true;
+          ++nf;
+        }
+      }
+      for (int u = min(nf, kFarMax); u < kFarMax; ++u) L.fk[i][u] = r, L.fv[i][u] = 0.0;
+      for (int u = min(nn, kNearMax); u < kNearMax; ++u) L.nk[i][u] = UP ? r + 1 : r - 1, L.nv[i][u] = 0.0;
+      L.meta[i] = slow ? kFarMax + 1 : nf;
+      if (UP) L.piv[i] = pivot;
+    }
+    __syncthreads();
+  };
+  struct Far {
+    T w[kFarMax], src;
+  };
+  typedef int i32x4_t __attribute__((ext_vector_type(4)));
+  static_assert(kFarMax == 4, "far rows are read as one piece");
+  i32x4_t fk;   // far rows of the next fetch
+  auto far_rows = [&](int s) __attribute__((always_inline)) {
+    fk = *(const i32x4_t*)L.fk[min(s, len - 1) & (2 * kChunk - 1)];
+  };
+  auto fetch = [&](Far& F, int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < kFarMax; ++u) F.w[u] = W[(uint64_t)(unsigned)__builtin_amdgcn_readfirstlane(fk[u]) * t2 + lane];
+    const int r = row(min(s, len - 1));
+    if (SRC == 1) F.src = src[r];
+    if (SRC == 2) F.src = W[(uint64_t)(unsigned)r * t2 + lane];
+  };
+  struct Rec {
+    int nk[kNearMax], meta;
+    double fv[kFarMax], nv[kNearMax], piv;
+  };
+  auto record = [&](Rec& C, int s) __attribute__((always_inline)) {
+    const int i = min(s, len - 1) & (2 * kChunk - 1);
+#pragma unroll
+    for (int u = 0; u < kNearMax; ++u) C.nk[u] = L.nk[i][u], C.nv[u] = L.nv[i][u];
+#pragma unroll
+    for (int u = 0; u < kFarMax; ++u) C.fv[u] = L.fv[i][u];
+    C.meta = L.meta[i];
+    if (UP) C.piv = L.piv[i];
+  };
+  T near[2][kNearMax];   // ring values of the current row and the next
+  auto read_near = [&](const Rec& C, T* w) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < kNearMax; ++u) w[u] = L.ring[C.nk[u] & (kNear - 1)][lane];
+  };
+  auto solve = [&](const Far& F, const Rec& C, const T* w, int s) __attribute__((always_inline)) {
+    const int r = row(s);
+    const int nf = __builtin_amdgcn_readfirstlane(C.meta);
+    const double b = SRC == 0 || (SRC == 1 && (r < lo_ok || r > hi_ok)) ? 0.0 : (double)F.src;
+    double acc = b;
+    auto far = [&]() __attribute__((always_inline)) {
+#pragma unroll
+      for (int u = 0; u < kFarMax; ++u) acc -= C.fv[u] * (double)(u < nf ? F.w[u] : T(0));
+    };
+    if (!UP) far();
+#pragma unroll
+    for (int u = 0; u < kNearMax; ++u) acc -= C.nv[u] * (double)(C.nk[u] == (UP ? r + 1 : r - 1) ? last : w[u]);
+    if (UP) far();
+    if (nf > kFarMax) {
+      const int64_t R = B.s + r, d = dg[R], q1 = UP ? hi[R] : d;
+      acc = b;
+#pragma unroll 1
+      for (int64_t q = UP ? d + 1 : lo[R]; q < q1; ++q) {
+        const int k = col[q] - (int)B.s;
+        if (k >= kmin) acc -= fv[q] * (double)W[(uint64_t)(unsigned)k * t2 + lane];
+      }
+    }
+    last = (T)(UP ? acc / C.piv : acc);
+    W[(uint64_t)(unsigned)r * t2 + lane] = last;
+    L.ring[r & (kNear - 1)][lane] = last;
+  };
+  range(0);
+  stage(0);
+  stage(kChunk);
+  Far F[kAhead];
+  Rec C[4];
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) {
+    far_rows(u);
+    fetch(F[u], u);
+  }
+  record(C[0], 0);
+  record(C[1], 1);
+  read_near(C[0], near[0]);
+#pragma unroll 1
+  for (int s = 0; s < len; s += kAhead) {
+    if ((s & (kChunk - 1)) == 0 && s > 0) stage(s + kChunk);
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      record(C[(u + 2) % 4], s + u + 2);
+      read_near(C[(u + 1) % 4], near[(u + 1) % 2]);
+      far_rows(s + u + kAhead);
+      if (s + u < len) solve(F[u], C[u % 4], near[u % 2], s + u);
+      fetch(F[u], s + u + kAhead);
+    }
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(64) void k_ilu_spikes(const IluBlock* __restrict__ blocks,
+                                                     const int32_t* __restrict__ batch, int t,
+                                                     const T* __restrict__ rhs, const int64_t* __restrict__ lo,
+                                                     const int64_t* __restrict__ dg,
+                                                     const int64_t* __restrict__ hi,
+                                                     const int32_t* __restrict__ col,
+                                                     const double* __restrict__ fv, T* ws, int64_t slot_elems) {
+  __shared__ __attribute__((aligned(16))) IluRows<T> L;
+  const int c0 = blockIdx.y * 64;
   const int t2 = 2 * t;
-  if (c >= t2) return;
   const int bi = batch[blockIdx.x];
   const IluBlock B = blocks[bi];
-  const bool left = c < t;
+  const bool left = c0 < t;
   if (left ? !B.left : !B.right) return;
-  T* __restrict__ W = ws + (int64_t)blockIdx.x * slot_elems;
+  T* W = ws + (int64_t)blockIdx.x * slot_elems + c0;
   const int64_t pt = (int64_t)t * t + t;
-  const T* __restrict__ P = rhs + (int64_t)bi * pt;
-  const int64_t n = B.n;
-  const int64_t r0 = left ? 0 : n - t;   // rows above r0 stay zero in the forward solve
-  const int j = left ? c : c - t;
-  // the row just finished (r - 1 down the block, r + 1 up it) is taken from
-  // a register, as stored (rounded to T), instead of being loaded back right
-  // after its store; the row index is the same in every lane, so the choice
-  // does not diverge
-  double prev = 0.0;
-  for (int64_t r = r0; r < n; ++r) {
-    const int64_t R = B.s + r;
-    double acc;
-    if (left) acc = (r < t && r <= j) ? (double)P[t + (int64_t)j * t + r] : 0.0;
-    else {
-      const int64_t rr = r - r0;
-      acc = rr >= j ? (double)P[(int64_t)j * t + rr] : 0.0;
-    }
-    const int64_t qe = dg[R];
-    for (int64_t q = lo[R]; q < qe; ++q) {
-      const int64_t k = col[q] - B.s;
-      if (k >= r0) acc -= fv[q] * (k == r - 1 ? prev : (double)W[k * t2 + c]);
-    }
-    const T y = (T)acc;
-    W[r * t2 + c] = y;
-    prev = (double)y;
-  }
-  double next = 0.0;
-  for (int64_t r = n - 1; r >= 0; --r) {
-    const int64_t R = B.s + r;
-    const int64_t d = dg[R];
-    double acc = r >= r0 ? (double)W[r * t2 + c] : 0.0;
-    for (int64_t q = d + 1; q < hi[R]; ++q) {
-      const int64_t k = col[q] - B.s;
-      acc -= fv[q] * (k == r + 1 ? next : (double)W[k * t2 + c]);
-    }
-    const T x = (T)(acc / fv[d]);
-    W[r * t2 + c] = x;
-    next = (double)x;
-  }
+  const int n = (int)B.n;
+  const int r0 = left ? 0 : n - t;   // rows above r0 stay zero in the forward solve
+  const int j = (left ? c0 : c0 - t) + (int)threadIdx.x;
+  // entry of row r in this lane's column: rows r0 .. r0 + t - 1
+  const T* __restrict__ P = rhs + (int64_t)bi * pt + (left ? t : 0) + (int64_t)j * t - r0;
+  T last = T(0);
+  ilu_column_sweep<false, 1>(L, r0, r0 + t, r0, B, lo, dg, hi, col, fv, P, left ? r0 : r0 + j, left ? r0 + j : n, W,
+                             t2, last);
+  if (left) ilu_column_sweep<false, 0>(L, t, n, r0, B, lo, dg, hi, col, fv, P, 0, 0, W, t2, last);
+  last = T(0);
+  ilu_column_sweep<true, 2>(L, r0, n, 0, B, lo, dg, hi, col, fv, P, 0, 0, W, t2, last);
+  if (!left) ilu_column_sweep<true, 0>(L, 0, r0, 0, B, lo, dg, hi, col, fv, P, 0, 0, W, t2, last);
 }
 
 // Tips of a batch: rows [0, t) of block i's spikes into tip part 2i - 1 and
@@ -175,7 +325,7 @@ __global__ __launch_bounds__(kIluThreads) void k_ilu_tips(const IluBlock* __rest
 }
 
 // D~^{-1} y for every block, in place on the padded vector (R columns,
-// column stride ldy), one workgroup of kSolveThreads per block: forward
+// column stride ldy), for blocks that k_ilu_solve_lds cannot take, one workgroup of kSolveThreads per block: forward
 // solve with L~ level by level, then backward with U~.  The solve is bound
 // by the latency of its dependent loads (level list -> row -> entries ->
 // vector), so each level-ordered slot carries its row's entry range (lq:
@@ -263,7 +413,7 @@ __global__ __launch_bounds__(kSolveThreads) void k_ilu_solve(const IluBlock* __r
 // solution and is loaded D levels ahead into registers; it is stored in level
 // order for that (k_ilu_pack), so that a wave reads consecutive pieces: read at
 // the CSR positions, a level of 200 rows moves some 1500 cache lines to one CU
-// and takes 1.07 us, packed see below.  Per slot of the level order
+// and takes 1.07 us, packed 0.35 us.  Per slot of the level order
 //   pat: the block-local columns of the first four entries (n, where the LDS
 //        vector holds a zero, for entries the row does not have), the row, the
 //        entry count, 16 bits each
@@ -430,15 +580,15 @@ void ilu_spikes(int dtype, int nb, const IluBlock* blocks, const int32_t* batch,
                 const int64_t* lo, const int64_t* dg, const int64_t* hi, const int32_t* col, const double* fv,
                 void* ws, int64_t slot_elems, void* tips, hipStream_t s) {
   if (nb <= 0) return;
-  const dim3 g1((unsigned)nb, (unsigned)((2 * t + kIluThreads - 1) / kIluThreads));
+  const dim3 g1((unsigned)nb, (unsigned)(2 * t / 64));
   const dim3 g2((unsigned)nb, 2u, (unsigned)((t / 64) * (2 * t / 64)));
   if (dtype == 0) {
-    hipLaunchKernelGGL(k_ilu_spikes<double>, g1, dim3(kIluThreads), 0, s, blocks, batch, t, (const double*)rhs, lo, dg,
+    hipLaunchKernelGGL(k_ilu_spikes<double>, g1, dim3(64), 0, s, blocks, batch, t, (const double*)rhs, lo, dg,
                        hi, col, fv, (double*)ws, slot_elems);
     hipLaunchKernelGGL(k_ilu_tips<double>, g2, dim3(kIluThreads), 0, s, blocks, batch, p, t, (const double*)ws,
                        slot_elems, (double*)tips);
   } else {
-    hipLaunchKernelGGL(k_ilu_spikes<float>, g1, dim3(kIluThreads), 0, s, blocks, batch, t, (const float*)rhs, lo, dg,
+    hipLaunchKernelGGL(k_ilu_spikes<float>, g1, dim3(64), 0, s, blocks, batch, t, (const float*)rhs, lo, dg,
                        hi, col, fv, (float*)ws, slot_elems);
     hipLaunchKernelGGL(k_ilu_tips<float>, g2, dim3(kIluThreads), 0, s, blocks, batch, p, t, (const float*)ws,
                        slot_elems, (float*)tips);
