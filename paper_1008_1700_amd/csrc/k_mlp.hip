@@ -14,57 +14,105 @@ namespace ddps {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// Tile T x T (T = 64 or 128), 256 threads = 4 waves (2 x 2), each a
-// (T/2) x (T/2) sub-tile of 32 x 32 MFMA blocks; K advances in chunks of 32
-// through LDS in layout [row][k] (k contiguous, padded by 8), and the next
-// chunk's global loads are held in registers while the current one is
-// multiplied.  Every operand is read in segments of 8 elements along its
-// contiguous dimension: one 16-byte load when the leading dimension and the
-// base allow it and the segment is inside the matrix, four 4-byte loads when
-// only 4-byte alignment holds, else one element at a time with zero fill.
+// Tile T x T (T = 32, 64 or 128), 256 threads = 4 waves (2 x 2), each a
+// (T/2) x (T/2) sub-tile of 32 x 32 MFMA blocks (T = 32: one block, the first
+// wave's; the other waves only bring its operands); K advances in chunks of
+// BK = 8192 / T through LDS in layout [row][k] (k contiguous, padded by 4).  The
+// products are small (a 512 x 512 layer is 64 tiles), so what bounds them is the
+// latency of their loads: every thread has four 16-byte pieces of each operand
+// of each of the next two chunks in flight.  With one chunk of 32 ahead the first
+// layer of 512 rows (4098 x 512) took 73 us, the others 20 us; now 30 and 8 us.
+// Every operand is read in pieces of 8 elements along its contiguous dimension:
+// one 16-byte load where the base and the leading dimension keep 4-byte
+// alignment and the piece is inside the matrix, else one element at a time.
+// Rows past the edge are read from the last row and not stored; k past the edge
+// is zero.
 // Per output element the products are summed in the same K order whatever
-// T is (chunks of 32, two 16-deep MFMAs each).
+// T is (16-deep MFMAs).
 // MFMA operand X = A block (32 m x 16 k): lane l holds A[l%32][8(l/32)..+8);
 // operand Y = B block (16 k x 32 n): lane l holds B[8(l/32)..+8)[l%32];
 // register v of lane l is C[8(v/4) + 4(l/32) + v%4][l%32].
 typedef unsigned short u16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
+typedef u16x8 __attribute__((aligned(4))) u16x8_a4;
 
-// 8 elements p[0..8) (contiguous), the first `valid` of them in range;
-// vw: 8 = 16-byte loads allowed, 2 = 4-byte loads allowed, 1 = elements.
-__device__ __forceinline__ u16x8 load_seg(const unsigned short* __restrict__ p, int valid, int vw) {
+// 8 elements p[0..8) (contiguous), the first `valid` of them in range
+__device__ __forceinline__ u16x8 load_seg(const unsigned short* __restrict__ p, int valid, bool wide) {
+  if (wide && valid >= 8) return *(const u16x8_a4*)p;
   u16x8 r;
-  if (valid >= 8 && vw == 8) return *(const u16x8*)p;
-  if (valid >= 8 && vw == 2) {
-    const unsigned int* q = (const unsigned int*)p;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const unsigned int w = q[e];
-      r[2 * e] = (unsigned short)(w & 0xffffu);
-      r[2 * e + 1] = (unsigned short)(w >> 16);
-    }
-    return r;
-  }
 #pragma unroll
   for (int e = 0; e < 8; ++e) r[e] = e < valid ? p[e] : (unsigned short)0;
   return r;
 }
 
+// The four pieces a thread takes of an operand's chunk [k0, k0 + BK): k
+// contiguous (KC): row q / (BK/8), k 8 (q % (BK/8)), q = tid + 256 j; rows
+// contiguous: k 4 (tid / (T/8)) + j, rows 8 (tid % (T/8)) .. + 7, so that a
+// thread's pieces transpose into four-k pieces of eight rows.
+template <bool KC, int T>
+struct MlpOperand {
+  static constexpr int BK = 8192 / T, LDK = BK + 4;
+  u16x8 r[4];
+  __device__ __forceinline__ void fetch(const unsigned short* __restrict__ X, int ld, int row0, int rows, int k0,
+                                        int K, bool wide) {
+    const int tid = threadIdx.x;
+    const unsigned short* p[4];
+    int valid[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (KC) {
+        const int q = tid + 256 * j, m = min(row0 + q / (BK / 8), rows - 1), k = k0 + 8 * (q % (BK / 8));
+        p[j] = X + (int64_t)m * ld + k;
+        valid[j] = K - k;
+      } else {
+        const int k = k0 + 4 * (tid / (T / 8)) + j, m = row0 + 8 * (tid % (T / 8));
+        p[j] = X + (int64_t)k * ld + m;
+        valid[j] = k < K ? rows - m : 0;
+      }
+    }
+    if (wide && k0 + BK <= K && (KC || row0 + T <= rows)) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) r[j] = *(const u16x8_a4*)p[j];
+    } else {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) r[j] = load_seg(p[j], valid[j], wide);
+    }
+  }
+  __device__ __forceinline__ void stage(unsigned short (*S)[LDK]) const {
+    const int tid = threadIdx.x;
+    if (KC) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int q = tid + 256 * j;
+        unsigned short* d = &S[q / (BK / 8)][8 * (q % (BK / 8))];
+        *(u16x4*)d = __builtin_shufflevector(r[j], r[j], 0, 1, 2, 3);
+        *(u16x4*)(d + 4) = __builtin_shufflevector(r[j], r[j], 4, 5, 6, 7);
+      }
+    } else {
+      const int k = 4 * (tid / (T / 8)), m = 8 * (tid % (T / 8));
+#pragma unroll
+      for (int e = 0; e < 8; ++e) *(u16x4*)&S[m + e][k] = u16x4{r[0][e], r[1][e], r[2][e], r[3][e]};
+    }
+  }
+};
+
 template <bool TA, bool TB, int T>
 __global__ __launch_bounds__(256) void k_mlp_gemm(int M, int N, int K, const __bf16* __restrict__ A_, int lda,
                                                   const __bf16* __restrict__ B_, int ldb,
-                                                  const float* __restrict__ bias, int epi,
-                                                  float* __restrict__ Cf, __bf16* __restrict__ Cb, int ldc,
-                                                  int va, int vb) {
-  constexpr int BK = 32, LDK = BK + 8;
-  constexpr int SEG = T * BK / 8 / 256;   // segments per thread and operand
-  constexpr int WB = T / 64;              // 32 x 32 blocks per wave and dimension
+                                                  const float* __restrict__ bias, const float* __restrict__ gate,
+                                                  int epi, float* __restrict__ Cf, __bf16* __restrict__ Cb, int ldc,
+                                                  bool wa, bool wb) {
+  constexpr int BK = 8192 / T, LDK = BK + 4;
+  constexpr int WB = T == 128 ? 2 : 1;    // 32 x 32 blocks per wave and dimension
+  constexpr int WS = 32 * WB;             // rows and columns of a wave's sub-tile
   __shared__ __attribute__((aligned(16))) unsigned short As[T][LDK];
   __shared__ __attribute__((aligned(16))) unsigned short Bs[T][LDK];
   const unsigned short* A = (const unsigned short*)A_;
   const unsigned short* B = (const unsigned short*)B_;
   const int m0 = blockIdx.x * T, n0 = blockIdx.y * T;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave & 1, wn = wave >> 1;
+  const int wm = T == 32 ? 0 : wave & 1, wn = T == 32 ? 0 : wave >> 1;
+  const bool works = T > 32 || wave == 0;
   f32x16 acc[WB][WB];
 #pragma unroll
   for (int i = 0; i < WB; ++i)
@@ -73,86 +121,72 @@ __global__ __launch_bounds__(256) void k_mlp_gemm(int M, int N, int K, const __b
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
-  // Segment q of a chunk: with the operand's k contiguous (A, or B stored
-  // transposed) it is (row q / 4, k 8 (q % 4)); with rows contiguous (A
-  // stored transposed, or B) it is (k q / (T/8), row 8 (q % (T/8))).
-  u16x8 ra[SEG], rb[SEG];
-  auto fetch = [&](int k0) __attribute__((always_inline)) {
-#pragma unroll
-    for (int j = 0; j < SEG; ++j) {
-      const int q = tid + 256 * j;
-      if (!TA) {
-        const int r = q >> 2, k = k0 + 8 * (q & 3), m = m0 + r;
-        ra[j] = load_seg(A + (int64_t)m * lda + k, m < M ? K - k : 0, va);
-      } else {
-        const int k = k0 + q / (T / 8), r = 8 * (q % (T / 8)), m = m0 + r;
-        ra[j] = load_seg(A + (int64_t)k * lda + m, k < K ? M - m : 0, va);
-      }
-      if (TB) {
-        const int r = q >> 2, k = k0 + 8 * (q & 3), n = n0 + r;
-        rb[j] = load_seg(B + (int64_t)n * ldb + k, n < N ? K - k : 0, vb);
-      } else {
-        const int k = k0 + q / (T / 8), r = 8 * (q % (T / 8)), n = n0 + r;
-        rb[j] = load_seg(B + (int64_t)k * ldb + n, k < K ? N - n : 0, vb);
-      }
-    }
+  MlpOperand<!TA, T> ra[2];
+  MlpOperand<TB, T> rb[2];
+  auto fetch = [&](int s, int k0) __attribute__((always_inline)) {
+    ra[s].fetch(A, lda, m0, M, k0, K, wa);
+    rb[s].fetch(B, ldb, n0, N, k0, K, wb);
   };
-  auto stage = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int j = 0; j < SEG; ++j) {
-      const int q = tid + 256 * j;
-      if (!TA) {
-        *(u16x8*)&As[q >> 2][8 * (q & 3)] = ra[j];
-      } else {
-        const int k = q / (T / 8), r = 8 * (q % (T / 8));
-#pragma unroll
-        for (int e = 0; e < 8; ++e) As[r + e][k] = ra[j][e];
-      }
-      if (TB) {
-        *(u16x8*)&Bs[q >> 2][8 * (q & 3)] = rb[j];
-      } else {
-        const int k = q / (T / 8), r = 8 * (q % (T / 8));
-#pragma unroll
-        for (int e = 0; e < 8; ++e) Bs[r + e][k] = rb[j][e];
-      }
-    }
+  auto frag = [&](const unsigned short* p) __attribute__((always_inline)) {
+    const u16x4 a = *(const u16x4*)p, b = *(const u16x4*)(p + 4);
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7));
   };
-  if (K > 0) fetch(0);
-  for (int k0 = 0; k0 < K; k0 += BK) {
+  auto chunk = [&](int s, int k0) __attribute__((always_inline)) {
     __syncthreads();   // every wave is done with the previous chunk
-    stage();
+    ra[s].stage(As);
+    rb[s].stage(Bs);
     __syncthreads();
-    if (k0 + BK < K) fetch(k0 + BK);
+    if (k0 + 2 * BK < K) fetch(s, k0 + 2 * BK);
+    const int ke = works ? min(BK, K - k0) : 0;
 #pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      const int kk = ks * 16 + 8 * (lane >> 5);
+    for (int ks = 0; ks < BK; ks += 16) {
+      if (ks >= ke) break;
+      const int kk = ks + 8 * (lane >> 5);
       bf16x8 x[WB], y[WB];
 #pragma unroll
-      for (int i = 0; i < WB; ++i) x[i] = *(const bf16x8*)&As[wm * (T / 2) + 32 * i + (lane & 31)][kk];
+      for (int i = 0; i < WB; ++i) x[i] = frag(&As[wm * WS + 32 * i + (lane & 31)][kk]);
 #pragma unroll
-      for (int j = 0; j < WB; ++j) y[j] = *(const bf16x8*)&Bs[wn * (T / 2) + 32 * j + (lane & 31)][kk];
+      for (int j = 0; j < WB; ++j) y[j] = frag(&Bs[wn * WS + 32 * j + (lane & 31)][kk]);
 #pragma unroll
       for (int i = 0; i < WB; ++i)
 #pragma unroll
         for (int j = 0; j < WB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[i], y[j], acc[i][j], 0, 0, 0);
     }
+  };
+  if (K > 0) fetch(0, 0);
+  if (K > BK) fetch(1, BK);
+  for (int k0 = 0; k0 < K; k0 += 2 * BK) {
+    chunk(0, k0);
+    if (k0 + BK < K) chunk(1, k0 + BK);
   }
+  if (!works) return;
 #pragma unroll
   for (int i = 0; i < WB; ++i)
 #pragma unroll
-    for (int j = 0; j < WB; ++j)
+    for (int j = 0; j < WB; ++j) {
+      const int n = n0 + wn * WS + 32 * j + (lane & 31);
+      const int mb = m0 + wm * WS + 32 * i + 4 * (lane >> 5);
+      float zg[16];
+      if (epi & MLP_GATE) {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int m = m0 + wm * (T / 2) + 32 * i + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        const int n = n0 + wn * (T / 2) + 32 * j + (lane & 31);
-        if (m < M && n < N) {
-          float z = acc[i][j][v];
-          if (epi & MLP_BIAS) z += bias[n];
-          if (epi & MLP_F32) Cf[(int64_t)m * ldc + n] = z;
-          if (epi & MLP_RELU_BF16) Cb[(int64_t)m * ldc + n] = (__bf16)fmaxf(z, 0.f);
-          else if (epi & MLP_BF16) Cb[(int64_t)m * ldc + n] = (__bf16)z;
+        for (int v = 0; v < 16; ++v) {
+          const int m = mb + 8 * (v >> 2) + (v & 3);
+          zg[v] = m < M && n < N ? gate[(int64_t)m * ldc + n] : 0.f;
         }
       }
+      const float bn = (epi & MLP_BIAS) && n < N ? bias[n] : 0.f;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int m = mb + 8 * (v >> 2) + (v & 3);
+        if (m < M && n < N) {
+          float z = acc[i][j][v];
+          if (epi & MLP_BIAS) z += bn;
+          if (epi & MLP_F32) Cf[(int64_t)m * ldc + n] = z;
+          if (epi & MLP_RELU_BF16) Cb[(int64_t)m * ldc + n] = (__bf16)fmaxf(z, 0.f);
+          if (epi & MLP_GATE) Cb[(int64_t)m * ldc + n] = (__bf16)(zg[v] > 0.f ? z : 0.f);
+        }
+      }
+    }
 }
 
 __global__ void k_f32_to_bf16(int64_t n, const float* __restrict__ x, __bf16* __restrict__ y) {
@@ -180,13 +214,6 @@ __global__ __launch_bounds__(256) void k_mse(int64_t n, float scale, const float
   if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
 }
 
-// dZ = bf16(dA * (Z > 0))
-__global__ void k_relu_bwd(int64_t n, const float* __restrict__ dA, const float* __restrict__ Z,
-                           __bf16* __restrict__ dZ) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-    dZ[i] = (__bf16)(Z[i] > 0.f ? dA[i] : 0.f);
-}
-
 // db[c] = sum over rows of dZ[r][c] (bf16 input, FP32 sums).  A workgroup
 // takes 64 columns (one wave reads 64 consecutive entries of a row); its 16
 // row groups g sum rows g, g + 16, ... in order, and the 16 partial sums are
@@ -199,6 +226,7 @@ __global__ __launch_bounds__(64 * kBiasGroups) void k_bias_grad(int rows, int co
   const int c = blockIdx.x * 64 + lc;
   float s = 0.f;
   if (c < cols)
+#pragma unroll 8
     for (int r = g; r < rows; r += kBiasGroups) s += (float)dZ[(int64_t)r * cols + c];
   part[g][lc] = s;
   __syncthreads();
@@ -289,41 +317,38 @@ __global__ void k_target(int64_t m, int64_t mc, int t2, const double* __restrict
 // ------------------------------------------------------------ launchers
 static unsigned grid1(int64_t n) { return (unsigned)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 4096)); }
 
-// widest load along an operand's contiguous dimension that every segment
-// start allows: 16 bytes (leading dimension a multiple of 8 elements, base
-// 16-byte aligned), 4 bytes, or single elements
-static int seg_width(const void* p, int ld) {
-  const uintptr_t a = (uintptr_t)p;
-  if (ld % 8 == 0 && a % 16 == 0) return 8;
-  if (ld % 2 == 0 && a % 4 == 0) return 2;
-  return 1;
-}
-
 template <bool TA, bool TB>
 static void mlp_gemm_t(int M, int N, int K, const __bf16* A, int lda, const __bf16* B, int ldb, const float* bias,
-                       int epi, float* Cf, __bf16* Cb, int ldc, hipStream_t s) {
-  const int va = seg_width(A, lda), vb = seg_width(B, ldb);
-  // 128 x 128 tiles where they still give every CU at least two
-  // workgroups, else 64 x 64
+                       const float* gate, int epi, float* Cf, __bf16* Cb, int ldc, hipStream_t s) {
+  // wide loads: every piece starts on 4 bytes
+  const bool wa = lda % 2 == 0 && (uintptr_t)A % 4 == 0, wb = ldb % 2 == 0 && (uintptr_t)B % 4 == 0;
+  // 128 x 128 tiles where they still give every CU at least two workgroups;
+  // 32 x 32 where 64 x 64 would leave half of the CUs idle (a 512 x 512 layer
+  // with 4098 inputs takes 40 us on 64 tiles of 64, 30 us on 256 of 32; a whole
+  // epoch of 32 steps of 512 rows 6.90 and 6.42 ms, of 700 rows, where the
+  // layers have 88 tiles of 64, 7.96 and 7.57 ms)
   const int64_t big = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
   if (big >= 512) {
     const dim3 g((M + 127) / 128, (N + 127) / 128);
-    hipLaunchKernelGGL((k_mlp_gemm<TA, TB, 128>), g, dim3(256), 0, s, M, N, K, A, lda, B, ldb, bias, epi, Cf, Cb, ldc,
-                       va, vb);
+    hipLaunchKernelGGL((k_mlp_gemm<TA, TB, 128>), g, dim3(256), 0, s, M, N, K, A, lda, B, ldb, bias, gate, epi, Cf, Cb,
+                       ldc, wa, wb);
+  } else if ((int64_t)((M + 63) / 64) * ((N + 63) / 64) <= 128) {
+    const dim3 g((M + 31) / 32, (N + 31) / 32);
+    hipLaunchKernelGGL((k_mlp_gemm<TA, TB, 32>), g, dim3(256), 0, s, M, N, K, A, lda, B, ldb, bias, gate, epi, Cf, Cb,
+                       ldc, wa, wb);
   } else {
     const dim3 g((M + 63) / 64, (N + 63) / 64);
-    hipLaunchKernelGGL((k_mlp_gemm<TA, TB, 64>), g, dim3(256), 0, s, M, N, K, A, lda, B, ldb, bias, epi, Cf, Cb, ldc,
-                       va, vb);
+    hipLaunchKernelGGL((k_mlp_gemm<TA, TB, 64>), g, dim3(256), 0, s, M, N, K, A, lda, B, ldb, bias, gate, epi, Cf, Cb,
+                       ldc, wa, wb);
   }
 }
 
 void mlp_gemm(bool ta, bool tb, int M, int N, int K, const __bf16* A, int lda, const __bf16* B, int ldb,
-              const float* bias, int epi, float* Cf, __bf16* Cb, int ldc, hipStream_t s) {
+              const float* bias, const float* gate, int epi, float* Cf, __bf16* Cb, int ldc, hipStream_t s) {
   if (M <= 0 || N <= 0) return;
-  if (!ta && !tb) mlp_gemm_t<false, false>(M, N, K, A, lda, B, ldb, bias, epi, Cf, Cb, ldc, s);
-  else if (ta && !tb) mlp_gemm_t<true, false>(M, N, K, A, lda, B, ldb, bias, epi, Cf, Cb, ldc, s);
-  else if (!ta && tb) mlp_gemm_t<false, true>(M, N, K, A, lda, B, ldb, bias, epi, Cf, Cb, ldc, s);
-  else mlp_gemm_t<true, true>(M, N, K, A, lda, B, ldb, bias, epi, Cf, Cb, ldc, s);
+  if (!ta && !tb) mlp_gemm_t<false, false>(M, N, K, A, lda, B, ldb, bias, gate, epi, Cf, Cb, ldc, s);
+  else if (ta && !tb) mlp_gemm_t<true, false>(M, N, K, A, lda, B, ldb, bias, gate, epi, Cf, Cb, ldc, s);
+  else mlp_gemm_t<false, true>(M, N, K, A, lda, B, ldb, bias, gate, epi, Cf, Cb, ldc, s);
 }
 void mlp_to_bf16(int64_t n, const float* x, __bf16* y, hipStream_t s) {
   hipLaunchKernelGGL(k_f32_to_bf16, dim3(grid1(n)), dim3(256), 0, s, n, x, y);
@@ -332,9 +357,6 @@ int mlp_mse(int64_t n, float scale, const float* Y, const float* T, __bf16* dY, 
   const int W = (int)std::min<int64_t>((n + 255) / 256, 256);
   hipLaunchKernelGGL(k_mse, dim3(W), dim3(256), 0, s, n, scale, Y, T, dY, part);
   return W;
-}
-void mlp_relu_bwd(int64_t n, const float* dA, const float* Z, __bf16* dZ, hipStream_t s) {
-  hipLaunchKernelGGL(k_relu_bwd, dim3(grid1(n)), dim3(256), 0, s, n, dA, Z, dZ);
 }
 void mlp_bias_grad(int rows, int cols, const __bf16* dZ, float* db, hipStream_t s) {
   hipLaunchKernelGGL(k_bias_grad, dim3((cols + 63) / 64), dim3(64 * kBiasGroups), 0, s, rows, cols, dZ, db);

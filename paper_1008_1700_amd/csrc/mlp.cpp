@@ -23,9 +23,10 @@ struct ddps_mlp_ctx {
   float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
   __bf16* pb = nullptr;
   __bf16 *X0 = nullptr, *A1 = nullptr, *A2 = nullptr, *A3 = nullptr, *dYb = nullptr, *dZ = nullptr;
-  float *Z1 = nullptr, *Z2 = nullptr, *Z3 = nullptr, *Y = nullptr, *dA = nullptr;
+  float *Z1 = nullptr, *Z2 = nullptr, *Z3 = nullptr, *Y = nullptr;
   double* part = nullptr;
   double* h_part = nullptr;
+  hipEvent_t loss_ev = nullptr;   // the loss's partial sums have reached h_part
   int adam_t = 0;
   std::vector<void*> allocs;
   template <typename T>
@@ -55,22 +56,28 @@ uint64_t splitmix(uint64_t& s) {
 int forward(ddps_mlp_ctx* M, int B, const float* X) {
   hipStream_t s = M->stream;
   mlp_to_bf16((int64_t)B * M->d_in, X, M->X0, s);
-  mlp_gemm(false, false, B, M->H, M->d_in, M->X0, M->d_in, M->W(0), M->H, M->b(0), MLP_BIAS | MLP_F32 | MLP_RELU_BF16,
-           M->Z1, M->A1, M->H, s);
-  mlp_gemm(false, false, B, M->H, M->H, M->A1, M->H, M->W(1), M->H, M->b(1), MLP_BIAS | MLP_F32 | MLP_RELU_BF16,
+  mlp_gemm(false, false, B, M->H, M->d_in, M->X0, M->d_in, M->W(0), M->H, M->b(0), nullptr,
+           MLP_BIAS | MLP_F32 | MLP_RELU_BF16, M->Z1, M->A1, M->H, s);
+  mlp_gemm(false, false, B, M->H, M->H, M->A1, M->H, M->W(1), M->H, M->b(1), nullptr, MLP_BIAS | MLP_F32 | MLP_RELU_BF16,
            M->Z2, M->A2, M->H, s);
-  mlp_gemm(false, false, B, M->H, M->H, M->A2, M->H, M->W(2), M->H, M->b(2), MLP_BIAS | MLP_F32 | MLP_RELU_BF16,
+  mlp_gemm(false, false, B, M->H, M->H, M->A2, M->H, M->W(2), M->H, M->b(2), nullptr, MLP_BIAS | MLP_F32 | MLP_RELU_BF16,
            M->Z3, M->A3, M->H, s);
-  mlp_gemm(false, false, B, M->d_out, M->H, M->A3, M->H, M->W(3), M->d_out, M->b(3), MLP_BIAS | MLP_F32, M->Y,
+  mlp_gemm(false, false, B, M->d_out, M->H, M->A3, M->H, M->W(3), M->d_out, M->b(3), nullptr, MLP_BIAS | MLP_F32, M->Y,
            nullptr, M->d_out, s);
   return hipGetLastError() == hipSuccess ? DDPS_OK : DDPS_E_HIP;
 }
 
-// gradients of mean((Y - T)^2) into M->g; returns the loss through *loss
-int backward(ddps_mlp_ctx* M, int B, const float* T, double* loss) {
+// gradients of mean((Y - T)^2) into M->g; *W: partial sums of the loss on their
+// way to h_part, if it is wanted (read_loss).  They are copied before the
+// products, so that the caller's wait for them does not leave the GPU idle.
+int backward(ddps_mlp_ctx* M, int B, const float* T, bool want_loss, int* W) {
   hipStream_t s = M->stream;
   const int64_t ny = (int64_t)B * M->d_out;
-  const int W = mlp_mse(ny, 1.f / (float)ny, M->Y, T, M->dYb, M->part, s);
+  *W = mlp_mse(ny, 1.f / (float)ny, M->Y, T, M->dYb, M->part, s);
+  if (want_loss &&
+      (hipMemcpyAsync(M->h_part, M->part, sizeof(double) * *W, hipMemcpyDeviceToHost, s) != hipSuccess ||
+       hipEventRecord(M->loss_ev, s) != hipSuccess))
+    return DDPS_E_HIP;
   float* g = M->g;
   const __bf16* acts[4] = {M->X0, M->A1, M->A2, M->A3};
   const float* Zs[3] = {M->Z1, M->Z2, M->Z3};
@@ -78,24 +85,23 @@ int backward(ddps_mlp_ctx* M, int B, const float* T, double* loss) {
   for (int l = 3; l >= 0; --l) {
     const int fi = M->fan_in(l), fo = M->fan_out(l);
     // dW_l = act_{l}^T dZ_l   (fan_in x fan_out)
-    mlp_gemm(true, false, fi, fo, B, acts[l], fi, dcur, fo, nullptr, MLP_F32, g + M->off[2 * l], nullptr, fo, s);
+    mlp_gemm(true, false, fi, fo, B, acts[l], fi, dcur, fo, nullptr, nullptr, MLP_F32, g + M->off[2 * l], nullptr, fo, s);
     mlp_bias_grad(B, fo, dcur, g + M->off[2 * l + 1], s);
     if (l == 0) break;
-    // dA_{l-1} = dZ_l W_l^T  (batch x fan_in), then dZ_{l-1} = dA * (Z_{l-1} > 0)
-    mlp_gemm(false, true, B, fi, fo, dcur, fo, M->W(l), fo, nullptr, MLP_F32, M->dA, nullptr, fi, s);
+    // dZ_{l-1} = dZ_l W_l^T (batch x fan_in) where Z_{l-1} > 0
     __bf16* dz = (l % 2 == 1) ? M->dZ : M->dZ + (int64_t)M->max_batch * M->H;
-    mlp_relu_bwd((int64_t)B * fi, M->dA, Zs[l - 1], dz, s);
+    mlp_gemm(false, true, B, fi, fo, dcur, fo, M->W(l), fo, nullptr, Zs[l - 1], MLP_GATE, nullptr, dz, fi, s);
     dcur = dz;
   }
-  if (hipGetLastError() != hipSuccess) return DDPS_E_HIP;
-  if (loss) {
-    if (hipMemcpyAsync(M->h_part, M->part, sizeof(double) * W, hipMemcpyDeviceToHost, s) != hipSuccess ||
-        hipStreamSynchronize(s) != hipSuccess)
-      return DDPS_E_HIP;
-    double acc = 0;
-    for (int i = 0; i < W; ++i) acc += M->h_part[i];
-    *loss = acc / (double)ny;
-  }
+  return hipGetLastError() == hipSuccess ? DDPS_OK : DDPS_E_HIP;
+}
+
+int read_loss(ddps_mlp_ctx* M, int B, int W, double* loss) {
+  if (!loss) return DDPS_OK;
+  if (hipEventSynchronize(M->loss_ev) != hipSuccess) return DDPS_E_HIP;
+  double acc = 0;
+  for (int i = 0; i < W; ++i) acc += M->h_part[i];
+  *loss = acc / (double)((int64_t)B * M->d_out);
   return DDPS_OK;
 }
 
@@ -133,13 +139,14 @@ int ddps_mlp_create(ddps_mlp* out, int32_t d_in, int32_t hidden, int32_t d_out, 
     o += M->fan_out(l);
   }
   M->count = o;
-  const int64_t B = max_batch, wide = std::max<int64_t>(std::max(hidden, d_in), d_out);
+  const int64_t B = max_batch;
   bool ok = M->alloc(M->p, o) && M->alloc(M->g, o) && M->alloc(M->m, o) && M->alloc(M->v, o) && M->alloc(M->pb, o) &&
             M->alloc(M->X0, B * d_in) && M->alloc(M->A1, B * hidden) && M->alloc(M->A2, B * hidden) &&
             M->alloc(M->A3, B * hidden) && M->alloc(M->dYb, B * d_out) && M->alloc(M->dZ, 2 * B * hidden) &&
             M->alloc(M->Z1, B * hidden) && M->alloc(M->Z2, B * hidden) && M->alloc(M->Z3, B * hidden) &&
-            M->alloc(M->Y, B * d_out) && M->alloc(M->dA, B * wide) && M->alloc(M->part, 256);
-  if (!ok || hipHostMalloc((void**)&M->h_part, 256 * sizeof(double)) != hipSuccess) {
+            M->alloc(M->Y, B * d_out) && M->alloc(M->part, 256);
+  if (!ok || hipHostMalloc((void**)&M->h_part, 256 * sizeof(double)) != hipSuccess ||
+      hipEventCreateWithFlags(&M->loss_ev, hipEventDisableTiming) != hipSuccess) {
     ddps_mlp_destroy(M);
     return DDPS_E_NOMEM;
   }
@@ -196,7 +203,8 @@ int ddps_mlp_gradients(ddps_mlp M, int32_t batch, const float* X, const float* T
   if (!M || !X || !T || batch < 1 || batch > M->max_batch) return DDPS_E_ARG;
   int rc = forward(M, batch, X);
   if (rc) return rc;
-  if ((rc = backward(M, batch, T, loss))) return rc;
+  int W;
+  if ((rc = backward(M, batch, T, loss != nullptr, &W)) || (rc = read_loss(M, batch, W, loss))) return rc;
   if (host_grads) {
     if (hipMemcpyAsync(host_grads, M->g, sizeof(float) * M->count, hipMemcpyDeviceToHost, M->stream) != hipSuccess ||
         hipStreamSynchronize(M->stream) != hipSuccess)
@@ -209,10 +217,12 @@ int ddps_mlp_train_step(ddps_mlp M, int32_t batch, const float* X, const float* 
   if (!M || !X || !T || batch < 1 || batch > M->max_batch || !(lr > 0.f)) return DDPS_E_ARG;
   int rc = forward(M, batch, X);
   if (rc) return rc;
-  if ((rc = backward(M, batch, T, loss))) return rc;
+  int W;
+  if ((rc = backward(M, batch, T, loss != nullptr, &W))) return rc;
   M->adam_t += 1;
   mlp_adam(M->count, lr, 0.9f, 0.999f, 1e-8f, M->adam_t, M->p, M->g, M->m, M->v, M->pb, M->stream);
-  return hipGetLastError() == hipSuccess ? DDPS_OK : DDPS_E_HIP;
+  if (hipGetLastError() != hipSuccess) return DDPS_E_HIP;
+  return read_loss(M, batch, W, loss);
 }
 
 void ddps_mlp_destroy(ddps_mlp M) {
@@ -220,6 +230,7 @@ void ddps_mlp_destroy(ddps_mlp M) {
   if (M->stream) (void)hipStreamSynchronize(M->stream);
   for (void* q : M->allocs) (void)hipFree(q);
   if (M->h_part) (void)hipHostFree(M->h_part);
+  if (M->loss_ev) (void)hipEventDestroy(M->loss_ev);
   delete M;
 }
 
