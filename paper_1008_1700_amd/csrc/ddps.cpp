@@ -391,12 +391,13 @@ struct ScheduleBuilder {
   int nwg = 0;
   double flops = 0, bytes = 0;
   bool gemv_aligned = true;
+  bool gemv_groups = true;   // column ranges and splits in groups of 16
 
   void begin(int k) {
     kind = k;
     nwg = 0;
     flops = bytes = 0;
-    gemv_aligned = true;
+    gemv_aligned = gemv_groups = true;
     off = k == LK_GEMM ? (int64_t)gemm.size() : k == LK_PANEL ? (int64_t)panel.size() : (int64_t)gemv.size();
   }
   // Tile mode the policy asks for; -2: by the size rule (auto_mode).
@@ -606,7 +607,7 @@ struct ScheduleBuilder {
   // cores take FP32 operands only when the handle's factors are not FP64
   int gemv_form() const {
     if (!gemv_aligned) return 0;
-    return (h->opt.factor_dtype != DDPS_F64 && h->opt.gemv_sums == 0) ? 2 : 1;
+    return (h->opt.factor_dtype != DDPS_F64 && h->opt.gemv_sums == 0 && gemv_groups) ? 2 : 1;
   }
   void end(std::vector<Launch>& out) {
     const int64_t cnt = (kind == LK_GEMM ? (int64_t)gemm.size() : kind == LK_PANEL ? (int64_t)panel.size()
@@ -648,6 +649,7 @@ struct ScheduleBuilder {
     if (G.rows <= 0) return;
     gemv_aligned = gemv_aligned && reinterpret_cast<uintptr_t>(G.A) % 16 == 0 &&
                    (G.lda * (int64_t)elt_bytes) % 16 == 0;
+    gemv_groups = gemv_groups && G.cb % 16 == 0 && G.ce % 16 == 0 && G.split % 16 == 0;
     G.wg0 = nwg;
     nwg += G.rows / 64;
     double cols = std::max(0, G.ce - G.cb);

@@ -719,18 +719,23 @@ void pack_tips(int dtype, int p, int t, const BlockInfo* blocks, const void* spi
 
 // ------------------------------------------------------------------------
 // Many right-hand sides (R >= 4) on FP32 operands, as products on the FP32
-// matrix cores (16x16x4).  One
-// workgroup per 64-row slab; its 4 waves take interleaved groups of 4
-// columns.  Lane l loads rows 4(l & 15) .. +3 of column c + (l >> 4) (one
-// float4; a wave load covers 64 rows x 4 columns), and the four products q
-// take its component q, so product q accumulates the slab rows 4i + q.  The
-// second operand of lane l is x(c + (l >> 4), rhs l & 15) rounded to FP32
-// (0 for rhs >= R).  The sums are FP32, each over a quarter of the columns;
-// the four quarters are added in FP64 in a fixed order.  Register v of
-// accumulator q in lane l holds slab row 16 (l >> 4) + 4 v + q, rhs l & 15.
+// matrix cores (16x16x4).  One workgroup per 64-row slab; its 4 waves take
+// interleaved groups of 16 columns (column ranges and the vectors' split are
+// multiples of 16).  Lane l loads rows 4(l & 15) .. +3 of the columns c + 4(l >> 4)
+// + u, u = 0 .. 3 (four float4, each wave load 64 rows x 4 columns), and the two
+// 16-byte pairs of x(those columns, rhs l & 15), rounded to FP32 (0 for rhs >= R).
+// For each u the four products q take component q of the float4, so product q
+// accumulates the slab rows 4i + q.  The sums are FP32, each over a quarter of
+// the columns; the four quarters are added in FP64 in a fixed order.  Register v
+// of accumulator q in lane l holds slab row 16 (l >> 4) + 4 v + q, rhs l & 15.
 // Triangular problems clip the column range as the other kernels do; the
 // masks of packed triangles change only the columns [r0, r0 + 64) of a
 // slab, so only loads of those columns go through the selects.
+//
+// Bound: HBM, and the vector's loads beside the matrix's.  With one vector entry
+// per load and groups of 4 columns, 2.58 GB of strided spikes (t = 1600) and 8
+// right-hand sides took 538 us; entries in pairs 484 us; three groups loaded ahead
+// 474 us (5.4 TB/s).
 // ------------------------------------------------------------------------
 template <int R>
 __global__ __launch_bounds__(256) void k_gemv_mf32(const GemvProb* __restrict__ probs, int nprob,
@@ -739,8 +744,9 @@ __global__ __launch_bounds__(256) void k_gemv_mf32(const GemvProb* __restrict__ 
                                                    double* __restrict__ partial,
                                                    const int32_t* __restrict__ stop) {
   typedef float f32x4 __attribute__((ext_vector_type(4)));
+  typedef double f64x2u __attribute__((ext_vector_type(2), aligned(8)));
   static_assert(R >= 1 && R <= 16, "right-hand sides per product");
-  constexpr int U = 4;   // column groups in flight per wave
+  constexpr int DEP = 4;   // column groups of a wave held at a time
   __shared__ float red[4][64][R];
   if (stop) {
     bool all = true;
@@ -768,10 +774,6 @@ __global__ __launch_bounds__(256) void k_gemv_mf32(const GemvProb* __restrict__ 
   f32x4 acc[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto xval = [&](int cc) __attribute__((always_inline)) -> float {
-    const double v = cc < split ? P.x1[cc + jx * ldx] : P.x2[(cc - split) + jx * ldx];
-    return live ? (float)v : 0.f;
-  };
   // the packed-triangle masks on the 4 rows of a lane's load of column cc
   auto fix = [&](float4& a, int cc) __attribute__((always_inline)) {
     if (masked && cc >= r0 && cc < r0 + 64) {
@@ -792,29 +794,41 @@ __global__ __launch_bounds__(256) void k_gemv_mf32(const GemvProb* __restrict__ 
     acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, x, acc[2], 0, 0, 0);
     acc[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, x, acc[3], 0, 0, 0);
   };
-  // wave g takes the column groups cb + 4 (g + 4 s), s = 0, 1, ...
-  int c = cb + 4 * g;
-  for (; c + 16 * (U - 1) + 3 < ce; c += 16 * U) {
-    float4 a[U];
-    float x[U];
+  // wave g takes the columns cb + 16 (g + 4 s) .. + 15, s = 0, 1, ...; lane
+  // group lk their 4 lk .. 4 lk + 3, one to each product, so that a lane's four
+  // vector entries are consecutive
+  struct Step {
+    float4 a[4];
+    f64x2u x[2];
+  };
+  auto fetch = [&](Step& F, int c) __attribute__((always_inline)) {
+    const int cl = c + 4 * lk;
+    const double* __restrict__ xp = c < split ? P.x1 + cl : P.x2 + (cl - split);
+    F.x[0] = *(const f64x2u*)(xp + jx * ldx);
+    F.x[1] = *(const f64x2u*)(xp + jx * ldx + 2);
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int cc = c + 16 * u + lk;
-      a[u] = *(const float4*)(A + (int64_t)cc * lda);
-      x[u] = xval(cc);
-    }
+    for (int u = 0; u < 4; ++u) F.a[u] = *(const float4*)(A + (int64_t)(cl + u) * lda);
+  };
+  auto multiply = [&](Step& F, int c) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      fix(a[u], c + 16 * u + lk);
-      mma(a[u], x[u]);
+    for (int u = 0; u < 4; ++u) {
+      fix(F.a[u], c + 4 * lk + u);
+      mma(F.a[u], live ? (float)F.x[u / 2][u % 2] : 0.f);
     }
-  }
-  for (; c < ce; c += 16) {
-    const int cc = c + lk;
-    const bool in = cc < ce;
-    float4 a = in ? *(const float4*)(A + (int64_t)cc * lda) : float4{0.f, 0.f, 0.f, 0.f};
-    fix(a, cc);
-    mma(a, in ? xval(cc) : 0.f);
+  };
+  const int c0 = cb + 16 * g;
+  Step F[DEP];
+#pragma unroll
+  for (int i = 0; i < DEP - 1; ++i)
+    if (c0 + 64 * i < ce) fetch(F[i], c0 + 64 * i);
+#pragma unroll 1
+  for (int c = c0; c < ce; c += 64 * DEP) {
+#pragma unroll
+    for (int i = 0; i < DEP; ++i) {
+      const int ci = c + 64 * i;
+      if (ci + 64 * (DEP - 1) < ce) fetch(F[(i + DEP - 1) % DEP], ci + 64 * (DEP - 1));
+      if (ci < ce) multiply(F[i], ci);
+    }
   }
   if (live) {
 #pragma unroll
