@@ -18,17 +18,19 @@
 // their order per entry are those of a one-wave elimination, so the factors
 // do not depend on the split.
 //
-// Inversion, with the factors in LDS (row-major, L below the diagonal, U on
-// and above it); waves 0 and 2 form Y = U^{-1} and waves 1 and 3 X = L^{-1}
-// at the same time (waves 4-7 only meet the barriers), lane r computing row
-// r one 16-column block at a time (each wave 8 of its columns) with the
-// earlier blocks' rows in LDS:
-//   Y = U^{-1}, blocks left to right:
-//       Y(r,r) = 1/u(r,r),  Y(r,j) = -( sum_{r<=l<j} Y(r,l) U(l,j) ) / u(j,j),  j > r
-//   X = L^{-1}, blocks right to left (unit diagonal implied, not stored):
-//       X(r,j) = -( L(r,j) + sum_{j<l<r} X(r,l) L(l,j) ),  j < r
-// Entries outside each triangle are held at zero so that every sum runs over
-// its whole range without conditions.
+// Inversion, in place in LDS (row-major, L below the diagonal, U on and above
+// it), by halves: for a triangle of blocks
+//   [U00 U01]^-1   [Y00  -Y00 U01 Y11]      [L00    ]^-1   [X00             ]
+//   [    U11]    = [          Y11    ]      [L10 L11]    = [-X11 L10 X00 X11]
+// First the eight 16 x 16 diagonal triangles, one per wave, a lane per column
+// by substitution; then the four 16 x 16 off-diagonal blocks of the 32 x 32
+// triangles and the two 32 x 32 blocks of the whole, as products on the matrix
+// cores (16x16x4, in the factors' own type).  By rows, each a sum over all
+// earlier columns on the vector units, the inversion was two thirds of the
+// kernel.  Alone an f64 sub-tile took 31 us, now 23 us, f32 24 and 17 us; beside
+// the products of the other stream f64 66 and 31 us, because 51 instead of 110 KiB
+// of LDS fit a CU that still runs half of its products.  What remains is the
+// elimination's chain of 64 reciprocals and the reads of pivot rows between lanes.
 //
 // Pivot check, after the elimination: lane r of wave 2 tests u_rr against
 // thresh[row] (the row's threshold in the padded layout); a pivot at or below
@@ -41,11 +43,11 @@ namespace ddps {
 namespace {
 
 constexpr int kN = kTile;      // 64
-constexpr int kB = 16;         // column block of the inversions
+constexpr int kB = 16;         // diagonal blocks of the inversions
 constexpr int kW = 8;          // waves of the workgroup
 constexpr int kE = kN / kW;    // columns per wave in the elimination
-constexpr int kLdLU = kN + 4;  // row-major LU: 16-byte aligned 16-column pieces
-constexpr int kLdR = kN + 1;   // per-lane rows: conflict-free column access
+constexpr int kLd = kN + 1;    // row-major LU: conflict-free column access
+constexpr int kLdT = 2 * kB + 1;
 
 // value of x in lane `lane` (wave-uniform), broadcast to the wave
 __device__ __forceinline__ float lane_value(float x, int lane) {
@@ -58,17 +60,42 @@ __device__ __forceinline__ double lane_value(double x, int lane) {
   return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+template <typename T>
+struct Mat;
+// acc(16 x 16) += a b, lane l giving a = A(l % 16, l / 16) and b = B(l / 16, l % 16)
+// of four columns / rows; row of the result's element v in lane l (column l % 16)
+template <>
+struct Mat<double> {
+  typedef f64x4 acc_t;
+  static __device__ __forceinline__ f64x4 mul(double a, double b, f64x4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int v, int lane) { return 4 * v + (lane >> 4); }
+};
+template <>
+struct Mat<float> {
+  typedef f32x4 acc_t;
+  static __device__ __forceinline__ f32x4 mul(float a, float b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+  static __device__ __forceinline__ int row(int v, int lane) { return 4 * (lane >> 4) + v; }
+};
+
 }  // namespace
 
 template <typename T>
 __global__ __launch_bounds__(64 * kW) void k_panel(const PanelProb* __restrict__ probs,
                                                const double* __restrict__ thresh,
                                                unsigned long long* __restrict__ bad) {
-  __shared__ __attribute__((aligned(16))) T LU[kN][kLdLU];  // L (c < r) and U (c >= r), row-major
-  __shared__ T Wy[kN][kLdR];                               // rows of U^{-1}
-  __shared__ T Wx[kN][kLdR];                               // rows of L^{-1}
-  __shared__ T Rv[kN];                                     // 1 / u(k, k)
-  __shared__ T Lm[2][kE][kN];                              // multipliers of the current round
+  __shared__ T LU[kN][kLd];   // L (c < r) and U (c >= r), row-major; then their inverses
+  __shared__ T Rv[kN];        // 1 / u(k, k)
+  // multipliers of the current round; then the inner products of the inversion
+  __shared__ union {
+    T Lm[2][kE][kN];
+    T H[2][2 * kB][kLdT];
+  } S;
   const PanelProb P = probs[blockIdx.x];
   T* __restrict__ D = (T*)P.D;
   const int r = threadIdx.x & 63;
@@ -83,17 +110,23 @@ __global__ __launch_bounds__(64 * kW) void k_panel(const PanelProb* __restrict__
   for (int kb = 0; kb < kW; ++kb) {
     // the owner eliminates its kE columns and publishes their multipliers
     if (w == kb) {
+      T rv = T(0);   // lane k: 1 / u(k, k)
 #pragma unroll
       for (int kc = 0; kc < kE; ++kc) {
         const int k = kE * kb + kc;
-        const T rp = T(1) / lane_value(a[kc], k);
-        if (r == 0) Rv[k] = rp;
-        const T l = r > k ? a[kc] * rp : T(0);
-        a[kc] = r > k ? l : a[kc];
-        Lm[kb & 1][kc][r] = l;
+        T u[kE];   // row k, read ahead of its uses: each read stalls what follows it
 #pragma unroll
-        for (int c = kc + 1; c < kE; ++c) a[c] -= l * lane_value(a[c], k);
+        for (int c = kc; c < kE; ++c) u[c] = lane_value(a[c], k);
+        __builtin_amdgcn_sched_barrier(0);
+        const T rp = T(1) / u[kc];
+        rv = r == k ? rp : rv;
+        const T l = r > k ? a[kc] * rp : T(0);
+#pragma unroll
+        for (int c = kc + 1; c < kE; ++c) a[c] -= l * u[c];
+        a[kc] = r > k ? l : a[kc];
+        S.Lm[kb & 1][kc][r] = l;
       }
+      if (r / kE == kb) Rv[r] = rv;
     }
     __syncthreads();
     // the waves right of it apply the same steps to their columns
@@ -101,9 +134,14 @@ __global__ __launch_bounds__(64 * kW) void k_panel(const PanelProb* __restrict__
 #pragma unroll
       for (int kc = 0; kc < kE; ++kc) {
         const int k = kE * kb + kc;
-        const T l = Lm[kb & 1][kc][r];
+        const T l = S.Lm[kb & 1][kc][r];
+        T u[kE];
 #pragma unroll
-        for (int c = 0; c < kE; ++c) a[c] -= l * lane_value(a[c], k);
+        for (int c = 0; c < kE; ++c) u[c] = lane_value(a[c], k);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < kE; ++c) a[c] -= l * u[c];
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   }
@@ -118,108 +156,84 @@ __global__ __launch_bounds__(64 * kW) void k_panel(const PanelProb* __restrict__
       atomicMin(bad, ((unsigned long long)P.block << 40) | (unsigned long long)(P.row0 + r));
   }
 
-  // Inversions, four rounds on all four waves: round b takes block 16b of
-  // Y = U^{-1} (waves 0 and 2) and block 48 - 16b of X = L^{-1} (waves 1
-  // and 3).  Each wave sums the earlier (Y) or later (X) blocks' terms for 8
-  // of the 16 columns.  Within a block, Y's columns depend on those to their
-  // left and X's on those to their right: wave 0 finishes Y's left half and
-  // wave 3 X's right half first; after a barrier wave 2 and wave 1 finish
-  // the other halves with those from LDS.  Every entry takes the terms in
-  // the same order as a one-wave inversion.
-  constexpr int kH = kB / 2;
-  const bool isY = (w & 1) == 0;
-  const int h0 = (w == 0 || w == 1) ? 0 : kH;   // first column of this wave's half
-#pragma unroll 1
-  for (int b = 0; b < kN / kB; ++b) {
-    const int j0 = isY ? kB * b : kN - kB - kB * b;
-    T acc[kH];
-    if (w >= 4) {
-    } else if (isY) {
+  // diagonal triangles: wave w < 4 that of U, else of L, of block b; lane j (of
+  // each 16 lanes alike) column j
+  const int o = kB * (w & 3), j = r & 15;
+  T x[kB];
+  if (w < 8) {
 #pragma unroll
-      for (int jj = 0; jj < kH; ++jj) acc[jj] = T(0);
-#pragma unroll 4
-      for (int l = 0; l < j0; ++l) {
-        const T yl = Wy[r][l];
+    for (int i = 0; i < kB; ++i) x[i] = i == j ? T(1) : T(0);
+    if (w < 4) {
 #pragma unroll
-        for (int jj = 0; jj < kH; ++jj) acc[jj] += yl * LU[l][j0 + h0 + jj];
+      for (int i = kB - 1; i >= 0; --i) {
+        x[i] *= Rv[o + i];
+#pragma unroll
+        for (int m = 0; m < i; ++m) x[m] -= LU[o + m][o + i] * x[i];
       }
     } else {
 #pragma unroll
-      for (int jj = 0; jj < kH; ++jj) acc[jj] = j0 + h0 + jj < r ? LU[r][j0 + h0 + jj] : T(0);
-#pragma unroll 4
-      for (int l = j0 + kB; l < kN; ++l) {
-        const T xl = Wx[r][l];
+      for (int i = 0; i < kB; ++i)
 #pragma unroll
-        for (int jj = 0; jj < kH; ++jj) acc[jj] += xl * LU[l][j0 + h0 + jj];
-      }
+        for (int m = i + 1; m < kB; ++m) x[m] -= LU[o + m][o + i] * x[i];
     }
-    // first halves: Y's left (wave 0), X's right (wave 3)
-    if (w == 0) {
-      T y[kH];
-#pragma unroll
-      for (int jj = 0; jj < kH; ++jj) {
-        const int j = j0 + jj;
-        T s = acc[jj];
-#pragma unroll
-        for (int ll = 0; ll < jj; ++ll) s += y[ll] * LU[j0 + ll][j];
-        const T rv = Rv[j];
-        y[jj] = j < r ? T(0) : (j == r ? rv : -s * rv);
-      }
-#pragma unroll
-      for (int jj = 0; jj < kH; ++jj) Wy[r][j0 + jj] = y[jj];
-    } else if (w == 3) {
-      T x[kH];
-#pragma unroll
-      for (int jj = kH - 1; jj >= 0; --jj) {
-        const int j = j0 + kH + jj;
-        T s = acc[jj];
-#pragma unroll
-        for (int ll = jj + 1; ll < kH; ++ll) s += x[ll] * LU[j0 + kH + ll][j];
-        x[jj] = j < r ? -s : T(0);
-      }
-#pragma unroll
-      for (int jj = 0; jj < kH; ++jj) Wx[r][j0 + kH + jj] = x[jj];
-    }
-    __syncthreads();
-    // second halves, with the first halves from LDS
-    if (w == 2) {
-      T y[kH];
-#pragma unroll
-      for (int jj = 0; jj < kH; ++jj) {
-        const int j = j0 + kH + jj;
-        T s = acc[jj];
-#pragma unroll
-        for (int ll = 0; ll < kH; ++ll) s += Wy[r][j0 + ll] * LU[j0 + ll][j];
-#pragma unroll
-        for (int ll = 0; ll < jj; ++ll) s += y[ll] * LU[j0 + kH + ll][j];
-        const T rv = Rv[j];
-        y[jj] = j < r ? T(0) : (j == r ? rv : -s * rv);
-      }
-#pragma unroll
-      for (int jj = 0; jj < kH; ++jj) Wy[r][j0 + kH + jj] = y[jj];
-    } else if (w == 1) {
-      T x[kH];
-#pragma unroll
-      for (int jj = kH - 1; jj >= 0; --jj) {
-        const int j = j0 + jj;
-        T s = acc[jj];
-#pragma unroll
-        for (int ll = jj + 1; ll < kH; ++ll) s += x[ll] * LU[j0 + ll][j];
-#pragma unroll
-        for (int ll = kH; ll < kB; ++ll) s += Wx[r][j0 + ll] * LU[j0 + ll][j];
-        x[jj] = j < r ? -s : T(0);
-      }
-#pragma unroll
-      for (int jj = 0; jj < kH; ++jj) Wx[r][j0 + jj] = x[jj];
-    }
-    __syncthreads();
   }
+  __syncthreads();   // both triangles of a block are read
+  if (w < 8) {
+#pragma unroll
+    for (int i = 0; i < kB; ++i)
+      if (r < kB && (w < 4 ? i <= j : i > j)) LU[o + i][o + j] = x[i];
+  }
+  __syncthreads();
+  // entry (i, k) of the inverse of U (up) or of L on its diagonal blocks
+  auto inv = [&](bool up, int i, int k) __attribute__((always_inline)) {
+    const T v = LU[i][k], d = !up && i == k ? T(1) : T(0);
+    return (up ? i <= k : i > k) ? v : d;
+  };
+  const int li = r & 15, lk = r >> 4;
+  typedef typename Mat<T>::acc_t acc_t;
+  // Off-diagonal block at (ro, co) of a triangle whose diagonal blocks start at
+  // ro and at co: -inv(ro, ro) F inv(co, co), F the factor's entries there; here
+  // the 16 x 16 part at (ti, tj) of blocks of size n, with the inner product in H.
+  auto first = [&](bool up, int ro, int co, int n, int ti, int tj, T(*H)[kLdT]) __attribute__((always_inline)) {
+    acc_t h = {};
+#pragma unroll
+    for (int s = 0; s < n; s += 4)
+      h = Mat<T>::mul(LU[ro + ti + li][co + s + lk], inv(up, co + s + lk, co + tj + li), h);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) H[ti + Mat<T>::row(v, r)][tj + li] = h[v];
+  };
+  auto second = [&](bool up, int ro, int co, int n, int ti, int tj, T(*H)[kLdT]) __attribute__((always_inline)) {
+    acc_t h = {};
+#pragma unroll
+    for (int s = 0; s < n; s += 4) h = Mat<T>::mul(inv(up, ro + ti + li, ro + s + lk), H[s + lk][tj + li], h);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) LU[ro + ti + Mat<T>::row(v, r)][co + tj + li] = -h[v];
+  };
+  // the 32 x 32 triangles: waves 0 and 1 of U, 2 and 3 of L, first and second
+  if (w < 4) {
+    const bool up = w < 2;
+    const int o = 2 * kB * (w & 1), ro = up ? o : o + kB, co = up ? o + kB : o;
+    T(*H)[kLdT] = &S.H[w >> 1][kB * (w & 1)];
+    first(up, ro, co, kB, 0, 0, H);
+    second(up, ro, co, kB, 0, 0, H);
+  }
+  __syncthreads();
+  // the whole: wave w takes the 16 x 16 block (ti, tj) of U's off-diagonal half
+  // (w < 4) or of L's
+  {
+    const bool up = w < 4;
+    const int ro = up ? 0 : 2 * kB, co = up ? 2 * kB : 0, ti = kB * (w >> 1 & 1), tj = kB * (w & 1);
+    if (w < 8) first(up, ro, co, 2 * kB, ti, tj, S.H[w >> 2 & 1]);
+    __syncthreads();
+    if (w < 8) second(up, ro, co, 2 * kB, ti, tj, S.H[w >> 2 & 1]);
+  }
+  __syncthreads();
   // U^{-1} on and above the diagonal, L^{-1} strictly below it: each wave
   // writes kE of the 64 columns
 #pragma unroll
   for (int cc = 0; cc < kE; ++cc) {
     const int c = kE * w + cc;
-    D[c * ld + r] = c >= r ? Wy[r][c] : Wx[r][c];
+    D[c * ld + r] = LU[r][c];
   }
 }
 
