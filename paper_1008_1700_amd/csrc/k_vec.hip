@@ -99,51 +99,39 @@ __device__ __forceinline__ double sum_of(const double* __restrict__ sums, int j,
   return sums[2 * j + q];
 }
 
-// The sums of a reduction in every thread of a workgroup: read from `sums`
-// when they have been reduced (W = 0), else added up from the [W][R][2]
-// partials in the order of k_reduce2, the same in every workgroup, with
-// workgroup 0 leaving them in `sums` for later kernels.  For few partials
-// this is quicker than a launch of its own (4.7 us and the gap before it).
-template <int R>
-__device__ __forceinline__ void take_sums(int W, const double* __restrict__ part, double* __restrict__ sums,
-                                          double (&v)[R][2], double (*sh)[R][2]) {
+// The sums of a reduction for column j of R in every thread of a workgroup: read
+// from `sums` when they have been reduced (W = 0), else added up from the
+// [W][R][2] partials in the order of k_reduce2, the same in every workgroup, with
+// the column's workgroup 0 leaving them in `sums` for later kernels.  For few
+// partials this is quicker than a launch of its own (4.7 us and the gap before
+// it).
+__device__ __forceinline__ void take_sums(int W, int R, int j, const double* __restrict__ part,
+                                          double* __restrict__ sums, double (&v)[2], double (*sh)[1][2]) {
   if (W == 0) {
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      v[j][0] = sums[2 * j];
-      v[j][1] = sums[2 * j + 1];
-    }
+    v[0] = sums[2 * j];
+    v[1] = sums[2 * j + 1];
     return;
   }
-#pragma unroll
-  for (int j = 0; j < R; ++j) v[j][0] = v[j][1] = 0.0;
-  for (int w = threadIdx.x; w < W; w += 256)
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      v[j][0] += part[((int64_t)w * R + j) * 2 + 0];
-      v[j][1] += part[((int64_t)w * R + j) * 2 + 1];
-    }
+  v[0] = v[1] = 0.0;
+  for (int w = threadIdx.x; w < W; w += 256) {
+    v[0] += part[((int64_t)w * R + j) * 2 + 0];
+    v[1] += part[((int64_t)w * R + j) * 2 + 1];
+  }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
-  for (int j = 0; j < R; ++j)
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      double x = v[j][q];
-      for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-      if (lane == 0) sh[wave][j][q] = x;
-    }
+  for (int q = 0; q < 2; ++q) {
+    double x = v[q];
+    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+    if (lane == 0) sh[wave][0][q] = x;
+  }
   __syncthreads();
 #pragma unroll
-  for (int j = 0; j < R; ++j)
-#pragma unroll
-    for (int q = 0; q < 2; ++q) v[j][q] = sh[0][j][q] + sh[1][j][q] + sh[2][j][q] + sh[3][j][q];
+  for (int q = 0; q < 2; ++q) v[q] = sh[0][0][q] + sh[1][0][q] + sh[2][0][q] + sh[3][0][q];
   __syncthreads();
-  if (blockIdx.x == 0 && threadIdx.x == 0)
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      sums[2 * j] = v[j][0];
-      sums[2 * j + 1] = v[j][1];
-    }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    sums[2 * j] = v[0];
+    sums[2 * j + 1] = v[1];
+  }
 }
 
 // ------------------------------------------------------------ layout moves
@@ -249,176 +237,132 @@ __device__ __forceinline__ bool s_ok(const KState* st, int it, int j, double rtv
   return st->status[it & 1][j] == KS_RUNNING && rtv != 0.0 && isfinite(alpha);
 }
 
+// The vector kernels of an iteration, grid (W, R): workgroup (b, j) takes rows of
+// column j, so that eight columns are eight times the workgroups and not eight
+// loads and stores one after another in a thread (m = 63488, 8 columns: k_bicg_xr
+// 26 us, k_bicg_p 17 us, k_bicg_s 10 us with the columns in a loop).
+
 // s = r - alpha v, alpha = rho / (r~.v); partial s.s
-template <int R>
 __global__ __launch_bounds__(256) void k_bicg_s(int it, int64_t m, int w1, const double* __restrict__ p1,
-                                                double* __restrict__ s1, KState* __restrict__ st, const double* __restrict__ r,
-                                                const double* __restrict__ v, double* __restrict__ s,
-                                                double* __restrict__ part) {
-  __shared__ double sh[4][R][2];
-  double al[R], v1[R][2];
-  bool run[R];
-  bool any = false;
-  take_sums<R>(w1, p1, s1, v1, sh);
-#pragma unroll
-  for (int j = 0; j < R; ++j) {
-    run[j] = s_ok(st, it, j, v1[j][0], al[j]);
-    any |= run[j];
-  }
-  __syncthreads();
-  if (blockIdx.x == 0 && threadIdx.x == 0)
-#pragma unroll
-    for (int j = 0; j < R; ++j) st->alpha[j] = al[j];
-  double acc[R][2];
-#pragma unroll
-  for (int j = 0; j < R; ++j) acc[j][0] = acc[j][1] = 0.0;
-  if (any)
+                                                double* __restrict__ s1, KState* __restrict__ st,
+                                                const double* __restrict__ r, const double* __restrict__ v,
+                                                double* __restrict__ s, double* __restrict__ part) {
+  __shared__ double sh[4][1][2];
+  const int j = blockIdx.y, R = gridDim.y;
+  double al, v1[2];
+  take_sums(w1, R, j, p1, s1, v1, sh);
+  const bool run = s_ok(st, it, j, v1[0], al);
+  if (blockIdx.x == 0 && threadIdx.x == 0) st->alpha[j] = al;
+  double acc[1][2] = {{0.0, 0.0}};
+  if (run)
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m;
          i += (int64_t)gridDim.x * blockDim.x) {
-#pragma unroll
-      for (int j = 0; j < R; ++j)
-        if (run[j]) {
-          const int64_t k = i + j * m;
-          const double sv = r[k] - al[j] * v[k];
-          s[k] = sv;
-          acc[j][0] += sv * sv;
-        }
+      const int64_t k = i + j * m;
+      const double sv = r[k] - al * v[k];
+      s[k] = sv;
+      acc[0][0] += sv * sv;
     }
-  block_sum<R>(acc, sh);
-  if (threadIdx.x == 0)
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      part[((int64_t)blockIdx.x * R + j) * 2 + 0] = acc[j][0];
-      part[((int64_t)blockIdx.x * R + j) * 2 + 1] = 0.0;
-    }
+  block_sum<1>(acc, sh);
+  if (threadIdx.x == 0) {
+    part[((int64_t)blockIdx.x * R + j) * 2 + 0] = acc[0][0];
+    part[((int64_t)blockIdx.x * R + j) * 2 + 1] = 0.0;
+  }
 }
 
 // half-step test on ||s||: x += alpha p; otherwise omega = t.s / t.t,
-// x += alpha p + omega s, r = s - omega t; partials (r.r, r~.r)
-template <int R>
+// x += alpha p + omega s, r = s - omega t; partials (r.r, r~.r).  px, sx: the
+// directions added to x (M^{-1}p, M^{-1}s when preconditioned, else p, s)
 __global__ __launch_bounds__(256) void k_bicg_xr(int it, int64_t m, double tol, const double* __restrict__ s1,
                                                  int w2, const double* __restrict__ p2, double* __restrict__ s2,
                                                  int w3, const double* __restrict__ p3, double* __restrict__ s3,
                                                  KState* __restrict__ st, double* __restrict__ x,
-                                                 const double* __restrict__ /*p: the update uses px*/,
-                                                 const double* __restrict__ s,
-                                                 const double* __restrict__ t, double* __restrict__ r,
-                                                 const double* __restrict__ rt, double* __restrict__ part,
-                                                 const double* __restrict__ px, const double* __restrict__ sx) {
-  // px, sx: the directions added to x (M^{-1}p, M^{-1}s when preconditioned, else p, s)
-  __shared__ double sh[4][R][2];
-  double al[R], om[R], v2[R][2], v3[R][2];
-  bool run[R], half[R];
-  take_sums<R>(w2, p2, s2, v2, sh);
-  take_sums<R>(w3, p3, s3, v3, sh);
-#pragma unroll
-  for (int j = 0; j < R; ++j) {
-    const bool ok = s_ok(st, it, j, sum_of(s1, j, 0), al[j]);
-    const double ts = v3[j][0], tt = v3[j][1];
-    half[j] = ok && sqrt(v2[j][0]) / st->ref[j] <= tol;
-    run[j] = ok && !half[j];
-    om[j] = tt != 0.0 ? ts / tt : 0.0;
-  }
-  __syncthreads();
-  if (blockIdx.x == 0 && threadIdx.x == 0)
-#pragma unroll
-    for (int j = 0; j < R; ++j) st->omega[j] = om[j];
-  double acc[R][2];
-#pragma unroll
-  for (int j = 0; j < R; ++j) acc[j][0] = acc[j][1] = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m;
-       i += (int64_t)gridDim.x * blockDim.x) {
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
+                                                 const double* __restrict__ s, const double* __restrict__ t,
+                                                 double* __restrict__ r, const double* __restrict__ rt,
+                                                 double* __restrict__ part, const double* __restrict__ px,
+                                                 const double* __restrict__ sx) {
+  __shared__ double sh[4][1][2];
+  const int j = blockIdx.y, R = gridDim.y;
+  double al, v2[2], v3[2];
+  take_sums(w2, R, j, p2, s2, v2, sh);
+  take_sums(w3, R, j, p3, s3, v3, sh);
+  const bool ok = s_ok(st, it, j, sum_of(s1, j, 0), al);
+  const double ts = v3[0], tt = v3[1];
+  const bool half = ok && sqrt(v2[0]) / st->ref[j] <= tol;
+  const bool run = ok && !half;
+  const double om = tt != 0.0 ? ts / tt : 0.0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) st->omega[j] = om;
+  double acc[1][2] = {{0.0, 0.0}};
+  if (half || run)
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m;
+         i += (int64_t)gridDim.x * blockDim.x) {
       const int64_t k = i + j * m;
-      if (half[j]) {
-        x[k] += al[j] * px[k];
-      } else if (run[j]) {
+      if (half) {
+        x[k] += al * px[k];
+      } else {
         const double sv = s[k];
-        x[k] += al[j] * px[k] + om[j] * sx[k];
-        const double rv = sv - om[j] * t[k];
+        x[k] += al * px[k] + om * sx[k];
+        const double rv = sv - om * t[k];
         r[k] = rv;
-        acc[j][0] += rv * rv;
-        acc[j][1] += rt[k] * rv;
+        acc[0][0] += rv * rv;
+        acc[0][1] += rt[k] * rv;
       }
     }
+  block_sum<1>(acc, sh);
+  if (threadIdx.x == 0) {
+    part[((int64_t)blockIdx.x * R + j) * 2 + 0] = acc[0][0];
+    part[((int64_t)blockIdx.x * R + j) * 2 + 1] = acc[0][1];
   }
-  block_sum<R>(acc, sh);
-  if (threadIdx.x == 0)
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      part[((int64_t)blockIdx.x * R + j) * 2 + 0] = acc[j][0];
-      part[((int64_t)blockIdx.x * R + j) * 2 + 1] = acc[j][1];
-    }
 }
 
 // End of iteration `it`: every decision of the iteration is re-derived from
 // the reduced sums, the next status is written to status[(it+1) & 1], and
 // p = r + beta (p - omega v) for the columns that continue.
-template <int R>
 __global__ __launch_bounds__(256) void k_bicg_p(int it, int maxit, int64_t m, double tol,
-                                                const double* __restrict__ s1,
-                                                const double* __restrict__ s2,
+                                                const double* __restrict__ s1, const double* __restrict__ s2,
                                                 const double* __restrict__ s3, int w4,
                                                 const double* __restrict__ p4, double* __restrict__ s4,
                                                 KState* __restrict__ st, const double* __restrict__ r,
                                                 double* __restrict__ p, const double* __restrict__ v) {
-  __shared__ double sh[4][R][2];
-  double v4[R][2];
-  take_sums<R>(w4, p4, s4, v4, sh);
-  double be[R], om[R], rho_new[R], res[R];
-  int32_t nst[R], it2[R];
-  bool cont[R];
-  bool any = false;
-#pragma unroll
-  for (int j = 0; j < R; ++j) {
-    double al;
-    const int32_t st0 = st->status[it & 1][j];
-    const bool ok = s_ok(st, it, j, sum_of(s1, j, 0), al);
-    const double ref = st->ref[j];
-    const double ress = sqrt(sum_of(s2, j, 0)) / ref;
-    const double ts = sum_of(s3, j, 0), tt = sum_of(s3, j, 1);
-    om[j] = tt != 0.0 ? ts / tt : 0.0;
-    rho_new[j] = v4[j][1];
-    const double rho_old = st->rho[it & 1][j];
-    be[j] = (rho_new[j] / rho_old) * (al / om[j]);
-    res[j] = st->res[j];
-    it2[j] = st->iters2[j];
-    if (st0 != KS_RUNNING) {
-      nst[j] = st0;
-    } else if (!ok) {
-      nst[j] = KS_BREAKDOWN;
-    } else if (ress <= tol) {
-      nst[j] = KS_CONVERGED; it2[j] = 2 * it - 1; res[j] = ress;
-    } else {
-      res[j] = sqrt(v4[j][0]) / ref;
-      it2[j] = 2 * it;
-      if (res[j] <= tol) nst[j] = KS_CONVERGED;
-      else if (om[j] == 0.0 || rho_new[j] == 0.0 || !isfinite(be[j])) nst[j] = KS_BREAKDOWN;
-      else if (it >= maxit) nst[j] = KS_MAXIT;
-      else nst[j] = KS_RUNNING;
-    }
-    cont[j] = nst[j] == KS_RUNNING;
-    any |= cont[j];
+  __shared__ double sh[4][1][2];
+  const int j = blockIdx.y, R = gridDim.y;
+  double v4[2], al;
+  take_sums(w4, R, j, p4, s4, v4, sh);
+  const int32_t st0 = st->status[it & 1][j];
+  const bool ok = s_ok(st, it, j, sum_of(s1, j, 0), al);
+  const double ref = st->ref[j];
+  const double ress = sqrt(sum_of(s2, j, 0)) / ref;
+  const double ts = sum_of(s3, j, 0), tt = sum_of(s3, j, 1);
+  const double om = tt != 0.0 ? ts / tt : 0.0;
+  const double rho_new = v4[1];
+  const double rho_old = st->rho[it & 1][j];
+  const double be = (rho_new / rho_old) * (al / om);
+  double res = st->res[j];
+  int32_t it2 = st->iters2[j], nst;
+  if (st0 != KS_RUNNING) {
+    nst = st0;
+  } else if (!ok) {
+    nst = KS_BREAKDOWN;
+  } else if (ress <= tol) {
+    nst = KS_CONVERGED; it2 = 2 * it - 1; res = ress;
+  } else {
+    res = sqrt(v4[0]) / ref;
+    it2 = 2 * it;
+    if (res <= tol) nst = KS_CONVERGED;
+    else if (om == 0.0 || rho_new == 0.0 || !isfinite(be)) nst = KS_BREAKDOWN;
+    else if (it >= maxit) nst = KS_MAXIT;
+    else nst = KS_RUNNING;
   }
-  __syncthreads();
-  if (blockIdx.x == 0 && threadIdx.x == 0)
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      st->status[(it + 1) & 1][j] = nst[j];
-      st->rho[(it + 1) & 1][j] = rho_new[j];
-      st->iters2[j] = it2[j];
-      st->res[j] = res[j];
-    }
-  if (!any) return;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->status[(it + 1) & 1][j] = nst;
+    st->rho[(it + 1) & 1][j] = rho_new;
+    st->iters2[j] = it2;
+    st->res[j] = res;
+  }
+  if (nst != KS_RUNNING) return;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m;
        i += (int64_t)gridDim.x * blockDim.x) {
-#pragma unroll
-    for (int j = 0; j < R; ++j)
-      if (cont[j]) {
-        const int64_t k = i + j * m;
-        p[k] = r[k] + be[j] * (p[k] - om[j] * v[k]);
-      }
+    const int64_t k = i + j * m;
+    p[k] = r[k] + be * (p[k] - om * v[k]);
   }
 }
 
@@ -728,18 +672,19 @@ void bicg_init_state(int R, int k, double tol, const double* sums, KState* st, h
 }
 void bicg_s(int R, int it, int64_t m, PartSums s1, KState* st, const double* r, const double* v,
             double* sv, double* part, int W, hipStream_t s) {
-  DDPS_R_DISPATCH(R, hipLaunchKernelGGL(k_bicg_s<RR>, dim3(W), dim3(256), 0, s, it, m, s1.W, s1.part, s1.sums, st, r, v, sv, part));
+  hipLaunchKernelGGL(k_bicg_s, dim3(W, R), dim3(256), 0, s, it, m, s1.W, s1.part, s1.sums, st, r, v, sv, part);
 }
 void bicg_xr(int R, int it, int64_t m, double tol, const double* s1, PartSums s2, PartSums s3,
              KState* st, double* x, const double* p, const double* sv, const double* t, double* r,
              const double* rt, double* part, int W, hipStream_t s, const double* px, const double* sx) {
-  DDPS_R_DISPATCH(R, hipLaunchKernelGGL(k_bicg_xr<RR>, dim3(W), dim3(256), 0, s, it, m, tol, s1, s2.W, s2.part, s2.sums, s3.W, s3.part, s3.sums, st, x, p, sv, t, r, rt, part,
-                                        px ? px : p, sx ? sx : sv));
+  hipLaunchKernelGGL(k_bicg_xr, dim3(W, R), dim3(256), 0, s, it, m, tol, s1, s2.W, s2.part, s2.sums, s3.W, s3.part,
+                     s3.sums, st, x, sv, t, r, rt, part, px ? px : p, sx ? sx : sv);
 }
 void bicg_p(int R, int it, int maxit, int64_t m, double tol, const double* s1, const double* s2,
             const double* s3, PartSums s4, KState* st, const double* r, double* p, const double* v,
             int W, hipStream_t s) {
-  DDPS_R_DISPATCH(R, hipLaunchKernelGGL(k_bicg_p<RR>, dim3(W), dim3(256), 0, s, it, maxit, m, tol, s1, s2, s3, s4.W, s4.part, s4.sums, st, r, p, v));
+  hipLaunchKernelGGL(k_bicg_p, dim3(W, R), dim3(256), 0, s, it, maxit, m, tol, s1, s2, s3, s4.W, s4.part, s4.sums, st,
+                     r, p, v);
 }
 void bicg_restart(int R, int it, int64_t m, const int32_t* flag, const double* r, double* rt, double* p,
                   double* part, int W, double* sums, KState* st, hipStream_t s) {
