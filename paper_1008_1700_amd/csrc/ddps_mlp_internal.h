@@ -25,7 +25,13 @@ void mlp_gemm(bool ta, bool tb, int M, int N, int K, const __bf16* A, int lda, c
               const float* bias, const float* gate, int epi, float* Cf, __bf16* Cb, int ldc, hipStream_t s);
 void mlp_to_bf16(int64_t n, const float* x, __bf16* y, hipStream_t s);
 int mlp_mse(int64_t n, float scale, const float* Y, const float* T, __bf16* dY, double* part, hipStream_t s);
-void mlp_bias_grad(int rows, int cols, const __bf16* dZ, float* db, hipStream_t s);
+// bias gradients of the four layers: db[l][c] = sum over rows of dZ[l][r][c]
+struct MlpBiasGrad {
+  const __bf16* dZ[4];
+  float* db[4];
+  int cols[4];
+};
+void mlp_bias_grad(int rows, const MlpBiasGrad& G, hipStream_t s);
 void mlp_adam(int64_t n, float lr, float b1, float b2, float eps, int t, float* p, const float* g, float* m,
               float* v, __bf16* pb, hipStream_t s);
 // reduced vectors: k right-hand sides of mc = nif * t2 entries each; mask has mc entries

@@ -200,6 +200,7 @@ __global__ __launch_bounds__(256) void k_mse(int64_t n, float scale, const float
                                              double* __restrict__ part) {
   __shared__ double sh[256];
   double acc = 0.0;
+#pragma unroll 4
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     const float d = Y[i] - T[i];
     dY[i] = (__bf16)(2.f * d * scale);
@@ -214,16 +215,20 @@ __global__ __launch_bounds__(256) void k_mse(int64_t n, float scale, const float
   if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
 }
 
-// db[c] = sum over rows of dZ[r][c] (bf16 input, FP32 sums).  A workgroup
-// takes 64 columns (one wave reads 64 consecutive entries of a row); its 16
-// row groups g sum rows g, g + 16, ... in order, and the 16 partial sums are
-// added pairwise in a fixed tree, so the result does not depend on timing.
+// db[c] = sum over rows of dZ[r][c] (bf16 input, FP32 sums) of every layer, one
+// launch for all of them (four launches of 4 us each otherwise).  A workgroup
+// takes 64 columns of a layer (one wave reads 64 consecutive entries of a row);
+// its 16 row groups g sum rows g, g + 16, ... in order, and the 16 partial sums
+// are added pairwise in a fixed tree, so the result does not depend on timing.
 constexpr int kBiasGroups = 16;
-__global__ __launch_bounds__(64 * kBiasGroups) void k_bias_grad(int rows, int cols, const __bf16* __restrict__ dZ,
-                                                                float* __restrict__ db) {
+__global__ __launch_bounds__(64 * kBiasGroups) void k_bias_grad(int rows, MlpBiasGrad G) {
   __shared__ float part[kBiasGroups][64];
+  int l = 0, wg = blockIdx.x;
+  while (l < 3 && wg >= (G.cols[l] + 63) / 64) wg -= (G.cols[l++] + 63) / 64;
+  const int cols = G.cols[l];
+  const __bf16* __restrict__ dZ = G.dZ[l];
   const int lc = threadIdx.x & 63, g = threadIdx.x >> 6;
-  const int c = blockIdx.x * 64 + lc;
+  const int c = wg * 64 + lc;
   float s = 0.f;
   if (c < cols)
 #pragma unroll 8
@@ -234,7 +239,7 @@ __global__ __launch_bounds__(64 * kBiasGroups) void k_bias_grad(int rows, int co
     if (g < h) part[g][lc] += part[g + h][lc];
     __syncthreads();
   }
-  if (g == 0 && c < cols) db[c] = part[0][lc];
+  if (g == 0 && c < cols) G.db[l][c] = part[0][lc];
 }
 
 // Adam (Kingma & Ba 2015, Algorithm 1) on FP32 master parameters; the bf16
@@ -358,8 +363,10 @@ int mlp_mse(int64_t n, float scale, const float* Y, const float* T, __bf16* dY, 
   hipLaunchKernelGGL(k_mse, dim3(W), dim3(256), 0, s, n, scale, Y, T, dY, part);
   return W;
 }
-void mlp_bias_grad(int rows, int cols, const __bf16* dZ, float* db, hipStream_t s) {
-  hipLaunchKernelGGL(k_bias_grad, dim3((cols + 63) / 64), dim3(64 * kBiasGroups), 0, s, rows, cols, dZ, db);
+void mlp_bias_grad(int rows, const MlpBiasGrad& G, hipStream_t s) {
+  int wgs = 0;
+  for (int l = 0; l < 4; ++l) wgs += (G.cols[l] + 63) / 64;
+  hipLaunchKernelGGL(k_bias_grad, dim3(wgs), dim3(64 * kBiasGroups), 0, s, rows, G);
 }
 void mlp_adam(int64_t n, float lr, float b1, float b2, float eps, int t, float* p, const float* g, float* m,
               float* v, __bf16* pb, hipStream_t s) {

@@ -82,17 +82,21 @@ int backward(ddps_mlp_ctx* M, int B, const float* T, bool want_loss, int* W) {
   const __bf16* acts[4] = {M->X0, M->A1, M->A2, M->A3};
   const float* Zs[3] = {M->Z1, M->Z2, M->Z3};
   const __bf16* dcur = M->dYb;   // dZ of layer l (bf16), batch x fan_out(l)
+  MlpBiasGrad bias;
   for (int l = 3; l >= 0; --l) {
     const int fi = M->fan_in(l), fo = M->fan_out(l);
     // dW_l = act_{l}^T dZ_l   (fan_in x fan_out)
     mlp_gemm(true, false, fi, fo, B, acts[l], fi, dcur, fo, nullptr, nullptr, MLP_F32, g + M->off[2 * l], nullptr, fo, s);
-    mlp_bias_grad(B, fo, dcur, g + M->off[2 * l + 1], s);
+    bias.dZ[l] = dcur;
+    bias.db[l] = g + M->off[2 * l + 1];
+    bias.cols[l] = fo;
     if (l == 0) break;
     // dZ_{l-1} = dZ_l W_l^T (batch x fan_in) where Z_{l-1} > 0
-    __bf16* dz = (l % 2 == 1) ? M->dZ : M->dZ + (int64_t)M->max_batch * M->H;
+    __bf16* dz = M->dZ + (int64_t)(l - 1) * M->max_batch * M->H;
     mlp_gemm(false, true, B, fi, fo, dcur, fo, M->W(l), fo, nullptr, Zs[l - 1], MLP_GATE, nullptr, dz, fi, s);
     dcur = dz;
   }
+  mlp_bias_grad(B, bias, s);
   return hipGetLastError() == hipSuccess ? DDPS_OK : DDPS_E_HIP;
 }
 
@@ -142,7 +146,7 @@ int ddps_mlp_create(ddps_mlp* out, int32_t d_in, int32_t hidden, int32_t d_out, 
   const int64_t B = max_batch;
   bool ok = M->alloc(M->p, o) && M->alloc(M->g, o) && M->alloc(M->m, o) && M->alloc(M->v, o) && M->alloc(M->pb, o) &&
             M->alloc(M->X0, B * d_in) && M->alloc(M->A1, B * hidden) && M->alloc(M->A2, B * hidden) &&
-            M->alloc(M->A3, B * hidden) && M->alloc(M->dYb, B * d_out) && M->alloc(M->dZ, 2 * B * hidden) &&
+            M->alloc(M->A3, B * hidden) && M->alloc(M->dYb, B * d_out) && M->alloc(M->dZ, 3 * B * hidden) &&
             M->alloc(M->Z1, B * hidden) && M->alloc(M->Z2, B * hidden) && M->alloc(M->Z3, B * hidden) &&
             M->alloc(M->Y, B * d_out) && M->alloc(M->part, 256);
   if (!ok || hipHostMalloc((void**)&M->h_part, 256 * sizeof(double)) != hipSuccess ||
