@@ -1219,7 +1219,7 @@ void build_solve_schedules(ddps_ctx* h, ScheduleBuilder& sb) {
 }
 
 int run_launch(ddps_ctx* h, const Launch& L, int R, int64_t ldx, int64_t ldy, const double* dotv,
-               double* partial, const int32_t* stop, int tkind, hipStream_t s) {
+               double* partial, const int32_t* stop, int tkind, hipStream_t s, const TipStep* step = nullptr) {
   hipEvent_t a;
   h->tim_begin(tkind, a, s);
   switch (L.kind) {
@@ -1233,7 +1233,8 @@ int run_launch(ddps_ctx* h, const Launch& L, int R, int64_t ldx, int64_t ldy, co
       break;
     }
     case LK_TIPMV:
-      launch_tipmv(h->sdt, R, h->t, h->d_gemv + L.off, L.nprob, L.nwg, ldx, ldy, dotv, partial, stop, s);
+      launch_tipmv(h->sdt, R, h->t, h->d_gemv + L.off, L.nprob, L.nwg, ldx, ldy, dotv, partial, stop, s,
+                   step);
       break;
     default:
       launch_gemv(h->sdt, R, L.mode, h->d_gemv + L.off, L.nprob, L.nwg, ldx, ldy, dotv, partial, stop, s);
@@ -1526,9 +1527,16 @@ int inner_solve(ddps_ctx* h, int k, int use_guess, double tol, int maxit, std::v
   // Partial sums of the products (A) and of the vector kernels (B: s.s, C: r.r
   // and r~.r).  Few of them are added up by the kernel that needs the sums,
   // more by a reduction of their own.
+  // The first half of a step is part of the second product where its sums are
+  // few: three sets of W1 then (the two products' and s.s), for which launches of
+  // up to some 600 workgroups have room.
+  const int W1 = h->W1;
+  const bool step = !prec && h->l_st.kind == LK_TIPMV && tipmv_steps(h->sdt, h->l_st.nwg) && W1 * R <= kFuseParts &&
+                    ((int64_t)3 * W1 + W2) * R * 2 <= h->part_cap;
   double* partA = h->d_part_buf;
-  double* partB = partA + (int64_t)h->W1 * R * 2;
-  double* partC = partB + (int64_t)W2 * R * 2;
+  double* partT = step ? partA + (int64_t)W1 * R * 2 : partA;
+  double* partB = partT + (int64_t)W1 * R * 2;
+  double* partC = partB + (int64_t)(step ? W1 : W2) * R * 2;
   auto sums = [&](int W, const double* part, double* out, const int32_t* stop) {
     if (W * R <= kFuseParts) return PartSums{W, part, out};
     reduce2(R, W, part, out, stop, s, h->d_red1);
@@ -1546,11 +1554,18 @@ int inner_solve(ddps_ctx* h, int k, int use_guess, double tol, int maxit, std::v
       // right preconditioning: v = G^ M^{-1} p, t = G^ M^{-1} s, x += a M^{-1} p + w M^{-1} s
       if (prec) run_launch(h, h->l_lp, R, m, m, nullptr, nullptr, stop, TK_RSPMV);
       run_launch(h, prec ? h->l_pvh : h->l_pv, R, m, m, h->d_rt, partA, stop, TK_RSPMV);
-      bicg_s(R, it, m, sums(h->W1, partA, S1, stop), h->d_state, h->d_r, h->d_v, h->d_s, partB, W2, s);
-      const PartSums q2 = sums(W2, partB, S2, stop);
-      if (prec) run_launch(h, h->l_ls, R, m, m, nullptr, nullptr, stop, TK_RSPMV);
-      run_launch(h, prec ? h->l_sth : h->l_st, R, m, m, h->d_s, partA, stop, TK_RSPMV);
-      bicg_xr(R, it, m, tol, S1, q2, sums(h->W1, partA, S3, stop), h->d_state, h->d_zh, h->d_p, h->d_s, h->d_tv,
+      PartSums q2;
+      if (step) {
+        const TipStep f{it, {W1, partA, S1}, h->d_state, h->d_r, h->d_v, h->d_s, partB};
+        run_launch(h, h->l_st, R, m, m, h->d_s, partT, stop, TK_RSPMV, s, &f);
+        q2 = {W1, partB, S2};
+      } else {
+        bicg_s(R, it, m, sums(W1, partA, S1, stop), h->d_state, h->d_r, h->d_v, h->d_s, partB, W2, s);
+        q2 = sums(W2, partB, S2, stop);
+        if (prec) run_launch(h, h->l_ls, R, m, m, nullptr, nullptr, stop, TK_RSPMV);
+        run_launch(h, prec ? h->l_sth : h->l_st, R, m, m, h->d_s, partT, stop, TK_RSPMV);
+      }
+      bicg_xr(R, it, m, tol, S1, q2, sums(W1, partT, S3, stop), h->d_state, h->d_zh, h->d_p, h->d_s, h->d_tv,
               h->d_r, h->d_rt, partC, W2, s, prec ? h->d_mp : nullptr, prec ? h->d_ms : nullptr);
       bicg_p(R, it, maxit, m, tol, S1, S2, S3, sums(W2, partC, S4, stop), h->d_state, h->d_r, h->d_p, h->d_v, W2, s);
     }

@@ -198,14 +198,34 @@ void launch_panel(int dtype, const PanelProb* probs, int nprob, const double* th
 // otherwise as form 1
 void launch_gemv(int dtype, int nrhs, int form, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
                  int64_t ldy, const double* dotv, double* partial, const int32_t* stop, hipStream_t s);
+// Sums of a reduction as a kernel takes them: reduced already (W = 0, in
+// sums), or W partials of R columns at part, which the kernel adds up itself
+// and workgroup 0 leaves in sums (worth it up to kFuseParts values)
+struct PartSums {
+  int W;
+  const double* part;
+  double* sums;
+};
+constexpr int kFuseParts = 2048;
 // reduced-matrix product on the packed tips (same records as launch_gemv,
 // A = first packed row, lda = 2t; nrhs 1 or 2; one partial per workgroup,
 // tipmv_split(nwg) of them per 64 rows), whether tips of this size are packed
 // for it, and the packing of the tips after a factorisation
 bool tipmv_packs(int dtype, int t);
 int tipmv_split(int dtype, int nwg);
+// the first half of an iteration's step within the product G s: s = r - alpha v
+// is formed where the product reads it (in place of bicg_s); partial s.s in ss
+struct TipStep {
+  int it;
+  PartSums s1;   // r~.v
+  KState* st;
+  const double *r, *v;
+  double *s, *ss;
+};
+bool tipmv_steps(int dtype, int nwg);   // whether launch_tipmv takes a step
 void launch_tipmv(int dtype, int nrhs, int t, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
-                  int64_t ldy, const double* dotv, double* partial, const int32_t* stop, hipStream_t s);
+                  int64_t ldy, const double* dotv, double* partial, const int32_t* stop, hipStream_t s,
+                  const TipStep* step = nullptr);
 void pack_tips(int dtype, int p, int t, const BlockInfo* blocks, const void* spikes, void* tips, hipStream_t s);
 
 void setup_scan(int64_t n, int p, const int64_t* part, const int64_t* row_ptr, const int32_t* col,
@@ -250,15 +270,6 @@ void reduce2(int R, int W, const double* part, double* out, const int32_t* stop,
 void bicg_init(int R, int64_t m, int use_guess, const double* gh, double* x, const double* v, double* r,
                double* rt, double* p, double* part, int W, hipStream_t s);
 void bicg_init_state(int R, int k, double tol, const double* sums, KState* st, hipStream_t s);
-// Sums of a reduction as a kernel takes them: reduced already (W = 0, in
-// sums), or W partials of R columns at part, which the kernel adds up itself
-// and workgroup 0 leaves in sums (worth it up to kFuseParts values)
-struct PartSums {
-  int W;
-  const double* part;
-  double* sums;
-};
-constexpr int kFuseParts = 2048;
 void bicg_s(int R, int it, int64_t m, PartSums s1, KState* st, const double* r, const double* v,
             double* sv, double* part, int W, hipStream_t s);
 // px, sx (may be null = p, sv): directions added to x, M^{-1}p and M^{-1}s when preconditioned

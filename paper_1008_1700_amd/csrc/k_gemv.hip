@@ -9,6 +9,7 @@
 // the vector entries are wave-uniform (scalar loads).  Triangular problems
 // clip the column range per 64-row slab and mask the diagonal slab.
 #include "ddps_internal.h"
+#include "krylov_device.h"
 
 namespace ddps {
 
@@ -410,22 +411,39 @@ __global__ __launch_bounds__(64 * NW) void k_gemv_n(const GemvProb* __restrict__
 // idle.  With one row at a time and the vector entries in registers, reloaded by
 // every wave, six workgroups of 128-entry rows took 8.7 us, now 4.2 us.
 // ------------------------------------------------------------------------
-template <typename T, int R, int RPW>
+template <typename T, int R, int RPW, bool STEP>
 __global__ __launch_bounds__(256) void k_tipmv(const GemvProb* __restrict__ probs, int nprob,
                                                int64_t ldx, int64_t ldy,
                                                const double* __restrict__ dotv,
                                                double* __restrict__ partial,
-                                               const int32_t* __restrict__ stop) {
+                                               const int32_t* __restrict__ stop, TipStep F) {
   constexpr int VEC = 16 / sizeof(T);
   constexpr int SB = 16 / RPW;                  // workgroups per 64 rows
   typedef T vec_t __attribute__((ext_vector_type(VEC)));
   extern __shared__ __attribute__((aligned(16))) double xs[];   // [columns][R]
-  __shared__ double red[4][R][2];
+  constexpr int NS = STEP ? 3 : 2;              // sums per workgroup and column
+  __shared__ double red[4][R][NS];
   if (stop) {
     bool all = true;
 #pragma unroll
     for (int j = 0; j < R; ++j) all &= stop[j] != KS_RUNNING;
     if (all) return;
+  }
+  // the step's alpha, as k_bicg_s takes it
+  double al[R];
+  bool run[R];
+  if (STEP) {
+    __shared__ double sh[4][1][2];
+    bool any = false;
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      double v1[2];
+      take_sums(F.s1.W, R, j, F.s1.part, F.s1.sums, v1, sh);
+      run[j] = s_ok(F.st, F.it, j, v1[0], al[j]);
+      any |= run[j];
+      if (blockIdx.x == 0 && threadIdx.x == 0) F.st->alpha[j] = al[j];
+    }
+    if (!any) return;   // no column goes on: nothing reads s, the product or their sums
   }
   const int wg = blockIdx.x / SB;
   const GemvProb& P = probs[find_gemv(probs, nprob, wg, gridDim.x / SB)];
@@ -436,7 +454,13 @@ __global__ __launch_bounds__(256) void k_tipmv(const GemvProb* __restrict__ prob
   const int rbase = (wg - P.wg0) * 64 + (blockIdx.x % SB) * (64 / SB) + wave * RPW;
   for (int i = tid; i < nc * R; i += 256) {
     const int c = cb + i % nc, j = i / nc;
-    xs[(c - cb) * R + j] = c < split ? P.x1[c + j * ldx] : P.x2[(c - split) + j * ldx];
+    const double* xp = (c < split ? P.x1 + c : P.x2 + (c - split)) + j * ldx;
+    if (STEP) {
+      const int64_t o = xp - F.s;
+      xs[(c - cb) * R + j] = run[j] ? F.r[o] - al[j] * F.v[o] : 0.0;
+    } else {
+      xs[(c - cb) * R + j] = *xp;
+    }
   }
   __syncthreads();
   const T* __restrict__ A0 = (const T*)P.A + cb;
@@ -490,9 +514,9 @@ __global__ __launch_bounds__(256) void k_tipmv(const GemvProb* __restrict__ prob
       mine[j] = (lane >= rr && lane < rr + 4) ? w : mine[j];
     }
   }
-  double dot[R], dd[R];
+  double dot[R], dd[R], ss[R];
 #pragma unroll
-  for (int j = 0; j < R; ++j) dot[j] = dd[j] = 0.0;
+  for (int j = 0; j < R; ++j) dot[j] = dd[j] = ss[j] = 0.0;
   if (lane < RPW) {
     const int r = rbase + lane;
 #pragma unroll
@@ -500,9 +524,20 @@ __global__ __launch_bounds__(256) void k_tipmv(const GemvProb* __restrict__ prob
       double v = mine[j];
       if (fl & V_MASK) v *= P.mask[r];
       if (fl & V_NEG) v = -v;
-      if (fl & V_YIN) v += P.yin[r + j * ldy];
-      P.yout[r + j * ldy] = v;
-      if (fl & V_DOT) dot[j] = dotv[P.dot_off + r + j * ldy] * v;
+      if (STEP) {
+        // y_in and the vector of the dot product are s
+        const int64_t o = P.yin + r + j * ldy - F.s;
+        const double sv = run[j] ? F.r[o] - al[j] * F.v[o] : 0.0;
+        if (run[j]) F.s[o] = sv;
+        ss[j] = sv * sv;
+        v += sv;
+        P.yout[r + j * ldy] = v;
+        dot[j] = sv * v;
+      } else {
+        if (fl & V_YIN) v += P.yin[r + j * ldy];
+        P.yout[r + j * ldy] = v;
+        if (fl & V_DOT) dot[j] = dotv[P.dot_off + r + j * ldy] * v;
+      }
       if (fl & V_DOT2) dd[j] = v * v;
     }
   }
@@ -512,18 +547,25 @@ __global__ __launch_bounds__(256) void k_tipmv(const GemvProb* __restrict__ prob
       for (int off = RPW / 2; off > 0; off >>= 1) {
         dot[j] += __shfl_xor(dot[j], off, 64);
         dd[j] += __shfl_xor(dd[j], off, 64);
+        if (STEP) ss[j] += __shfl_xor(ss[j], off, 64);
       }
     if (lane == 0)
 #pragma unroll
       for (int j = 0; j < R; ++j) {
         red[wave][j][0] = dot[j];
         red[wave][j][1] = dd[j];
+        if (STEP) red[wave][j][NS - 1] = ss[j];
       }
     __syncthreads();
     if (tid < R) {
       const int j = tid;
       partial[((int64_t)blockIdx.x * R + j) * 2 + 0] = (red[0][j][0] + red[1][j][0]) + (red[2][j][0] + red[3][j][0]);
       partial[((int64_t)blockIdx.x * R + j) * 2 + 1] = (red[0][j][1] + red[1][j][1]) + (red[2][j][1] + red[3][j][1]);
+      if (STEP) {
+        F.ss[((int64_t)blockIdx.x * R + j) * 2 + 0] =
+            (red[0][j][NS - 1] + red[1][j][NS - 1]) + (red[2][j][NS - 1] + red[3][j][NS - 1]);
+        F.ss[((int64_t)blockIdx.x * R + j) * 2 + 1] = 0.0;
+      }
     }
   }
 }
@@ -673,15 +715,23 @@ bool tipmv_packs(int dtype, int t) { return 2 * t * (dtype == 0 ? 8 : 4) <= 1638
 // split) 1024 entries on 240 16.9 / 20.5, on 496 27.4 / 24.6.
 int tipmv_split(int dtype, int nwg) { return nwg <= (dtype == 0 ? 128 : 256) ? 4 : 1; }
 
+bool tipmv_steps(int dtype, int nwg) { return dtype == 0 || tipmv_split(dtype, nwg) == 4; }
+
 void launch_tipmv(int dtype, int nrhs, int t, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
-                  int64_t ldy, const double* dotv, double* partial, const int32_t* stop, hipStream_t s) {
+                  int64_t ldy, const double* dotv, double* partial, const int32_t* stop, hipStream_t s,
+                  const TipStep* step) {
   if (nwg <= 0 || nprob <= 0) return;
   const int sb = tipmv_split(dtype, nwg);
   const size_t lds = (size_t)2 * t * (nrhs == 1 ? 1 : 2) * sizeof(double);
 #define DDPS_TIPMV(...) \
   hipLaunchKernelGGL((__VA_ARGS__), dim3(nwg), dim3(256), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop)
-#define DDPS_TIPMV_S(...) \
-  hipLaunchKernelGGL((__VA_ARGS__), dim3(nwg * sb), dim3(256), lds, s, probs, nprob, ldx, ldy, dotv, partial, stop)
+#define DDPS_TIPMV_S(T, R, RPW)                                                                                     \
+  if (step)                                                                                                         \
+    hipLaunchKernelGGL((k_tipmv<T, R, RPW, true>), dim3(nwg * sb), dim3(256), lds, s, probs, nprob, ldx, ldy, dotv, \
+                       partial, stop, *step);                                                                       \
+  else                                                                                                              \
+    hipLaunchKernelGGL((k_tipmv<T, R, RPW, false>), dim3(nwg * sb), dim3(256), lds, s, probs, nprob, ldx, ldy,      \
+                       dotv, partial, stop, TipStep{})
 #define DDPS_TIPMV_C(T, R)                                 \
   switch (ns) {                                            \
     case 1: DDPS_TIPMV(k_tipmv_c<T, R, 1>); break;         \
@@ -691,15 +741,15 @@ void launch_tipmv(int dtype, int nrhs, int t, const GemvProb* probs, int nprob, 
   }
   if (dtype == 0) {
     if (nrhs == 1) {
-      if (sb == 4) DDPS_TIPMV_S(k_tipmv<double, 1, 4>);
-      else DDPS_TIPMV_S(k_tipmv<double, 1, 16>);
+      if (sb == 4) { DDPS_TIPMV_S(double, 1, 4); }
+      else { DDPS_TIPMV_S(double, 1, 16); }
     } else {
-      if (sb == 4) DDPS_TIPMV_S(k_tipmv<double, 2, 4>);
-      else DDPS_TIPMV_S(k_tipmv<double, 2, 16>);
+      if (sb == 4) { DDPS_TIPMV_S(double, 2, 4); }
+      else { DDPS_TIPMV_S(double, 2, 16); }
     }
   } else if (sb == 4) {
-    if (nrhs == 1) DDPS_TIPMV_S(k_tipmv<float, 1, 4>);
-    else DDPS_TIPMV_S(k_tipmv<float, 2, 4>);
+    if (nrhs == 1) { DDPS_TIPMV_S(float, 1, 4); }
+    else { DDPS_TIPMV_S(float, 2, 4); }
   } else {
     const int ns = (2 * t + 1023) / 1024;
     if (nrhs == 1) { DDPS_TIPMV_C(float, 1) }
