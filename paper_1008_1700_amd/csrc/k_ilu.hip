@@ -164,7 +164,7 @@ __device__ __forceinline__ void ilu_column_sweep(IluRows<T>& L, int r0, int r1, 
       }
       for (int u = min(nf, kFarMax); u < kFarMax; ++u) L.fk[i][u] = r, L.fv[i][u] = 0.0;
       for (int u = min(nn, kNearMax); u < kNearMax; ++u) L.nk[i][u] = UP ? r + 1 : r - 1, L.nv[i][u] = 0.0;
-      L.meta[i] = slow ? kFarMax + 1 : nf;
+      L.meta[i] = slow ? kFarMax + 1 : nf | nn << 8;
       if (UP) L.piv[i] = pivot;
     }
     __syncthreads();
@@ -205,7 +205,7 @@ __device__ __forceinline__ void ilu_column_sweep(IluRows<T>& L, int r0, int r1, 
   };
   auto solve = [&](const Far& F, const Rec& C, const T* w, int s) __attribute__((always_inline)) {
     const int r = row(s);
-    const int nf = __builtin_amdgcn_readfirstlane(C.meta);
+    const int meta = __builtin_amdgcn_readfirstlane(C.meta), nf = meta & 255, nn = meta >> 8;
     const double b = SRC == 0 || (SRC == 1 && (r < lo_ok || r > hi_ok)) ? 0.0 : (double)F.src;
     double acc = b;
     auto far = [&]() __attribute__((always_inline)) {
@@ -214,7 +214,7 @@ __device__ __forceinline__ void ilu_column_sweep(IluRows<T>& L, int r0, int r1, 
     };
     if (!UP) far();
 #pragma unroll
-    for (int u = 0; u < kNearMax; ++u) acc -= C.nv[u] * (double)(C.nk[u] == (UP ? r + 1 : r - 1) ? last : w[u]);
+    for (int u = 0; u < kNearMax; ++u) acc -= C.nv[u] * (double)(u >= nn ? T(0) : C.nk[u] == (UP ? r + 1 : r - 1) ? last : w[u]);
     if (UP) far();
     if (nf > kFarMax) {
       const int64_t R = B.s + r, d = dg[R], q1 = UP ? hi[R] : d;
