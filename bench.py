@@ -268,7 +268,7 @@ def run_ilu(d, mode, steps, warmup, tol, inner_tol, inner_prec=1):
                inner_iters_avg=info.inner_iters_avg, inner_tol=inner_tol, inner_prec=inner_prec,
                relres_inf=float(np.max(np.max(np.abs(r), axis=0) / nf)),
                relerr_xstar=float(np.max(np.linalg.norm(xs - xst, axis=0) / np.linalg.norm(xst, axis=0))),
-               block_solve=dict(kernel="k_ilu_solve", launches=sweeps["launches"],
+               block_solve=dict(kernel="k_ilu_solve_lds / k_ilu_solve", launches=sweeps["launches"],
                                 avg_launch_us=sweeps["ms"] * 1e3 / max(sweeps["launches"], 1),
                                 algorithmic_bytes_per_launch=sweeps["bytes"] / max(sweeps["launches"], 1),
                                 GBps=sweeps["bytes"] / (sweeps["ms"] * 1e-3) / 1e9 if sweeps["ms"] > 0 else None),
@@ -768,7 +768,7 @@ def main():
     traffic, traffic_src = recorded_traffic(args.config, args.mode, k["launches_per_step"])
     roof = dict(bound="mfma", achieved=achieved / 1e12, peak=peak / 1e12, unit="TFLOP/s",
                 frac=achieved / peak, traffic=traffic,
-                kernel="k_gemm_dl / k_gemm_bf16 / k_gemm_std (grouped GEMM of stages 2 and 4)",
+                kernel="k_gemm_x3 / k_gemm_dl / k_gemm_bf16 / k_gemm_dma (grouped GEMM of stages 2 and 4)",
                 launches_per_step=k["launches_per_step"], kernel_ms_per_step=kms,
                 stream_groups=res["exec"]["streams"], launch_timing=k.get("timing"),
                 avg_launch_us=kms * 1e3 / max(k["launches_per_step"], 1),
