@@ -137,10 +137,7 @@ __global__ __launch_bounds__(256) void k_mlp_gemm(int M, int N, int K, const __b
     rb[s].stage(Bs);
     __syncthreads();
     if (k0 + 2 * BK < K) fetch(s, k0 + 2 * BK);
-    const int ke = works ? min(BK, K - k0) : 0;
-#pragma unroll
-    for (int ks = 0; ks < BK; ks += 16) {
-      if (ks >= ke) break;
+    auto step = [&](int ks) __attribute__((always_inline)) {
       const int kk = ks + 8 * (lane >> 5);
       bf16x8 x[WB], y[WB];
 #pragma unroll
@@ -151,6 +148,16 @@ __global__ __launch_bounds__(256) void k_mlp_gemm(int M, int N, int K, const __b
       for (int i = 0; i < WB; ++i)
 #pragma unroll
         for (int j = 0; j < WB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(x[i], y[j], acc[i][j], 0, 0, 0);
+    };
+    if (!works) return;
+    // a whole chunk without tests between its steps, so that their LDS reads
+    // go ahead of the products
+    if (K - k0 >= BK) {
+#pragma unroll
+      for (int ks = 0; ks < BK; ks += 16) step(ks);
+    } else {
+#pragma unroll 1
+      for (int ks = 0; ks < K - k0; ks += 16) step(ks);
     }
   };
   if (K > 0) fetch(0, 0);
