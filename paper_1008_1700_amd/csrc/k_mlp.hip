@@ -21,7 +21,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // products are small (a 512 x 512 layer is 64 tiles), so what bounds them is the
 // latency of their loads: every thread has four 16-byte pieces of each operand
 // of each of the next two chunks in flight.  With one chunk of 32 ahead the first
-// layer of 512 rows (4098 x 512) took 73 us, the others 20 us; now 30 and 8 us.
+// layer of 512 rows (4098 x 512) took 73 us, the others 20 us; now 27 and 7 us.
 // Every operand is read in pieces of 8 elements along its contiguous dimension:
 // one 16-byte load where the base and the leading dimension keep 4-byte
 // alignment and the piece is inside the matrix, else one element at a time.
