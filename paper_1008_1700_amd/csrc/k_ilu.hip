@@ -325,16 +325,16 @@ __global__ __launch_bounds__(kIluThreads) void k_ilu_tips(const IluBlock* __rest
 }
 
 // D~^{-1} y for every block, in place on the padded vector (R columns,
-// column stride ldy), for blocks that k_ilu_solve_lds cannot take, one workgroup of kSolveThreads per block: forward
-// solve with L~ level by level, then backward with U~.  The solve is bound
-// by the latency of its dependent loads (level list -> row -> entries ->
-// vector), so each level-ordered slot carries its row's entry range (lq:
-// [lo, dg) of the forward order, uq: [dg + 1, hi) of the backward one,
-// pivot at uq.x - 1), read together with the row number, and a workgroup
-// runs 16 waves; the R lanes of one row are adjacent.  Entries are taken
-// four at a time with their loads issued together (columns and values,
-// then the vector entries), so a row costs three dependent loads, not two
-// per entry.
+// column stride ldy), for blocks that k_ilu_solve_lds cannot take: one
+// workgroup of kSolveThreads per block, forward solve with L~ level by level,
+// then backward with U~.  The solve is bound by the latency of its dependent
+// loads (level list -> row -> entries -> vector), so each level-ordered slot
+// carries its row's entry range (lq: [lo, dg) of the forward order, uq: [dg + 1,
+// hi) of the backward one, pivot at uq.x - 1), read together with the row
+// number, and a workgroup runs 16 waves; the R lanes of one row are adjacent.
+// Entries are taken four at a time with their loads issued together (columns
+// and values, then the vector entries), so a row costs three dependent loads,
+// not two per entry.
 constexpr int kSolveThreads = 1024;
 constexpr int64_t kIluLds = 160 * 1024;   // LDS of a workgroup
 

@@ -26,7 +26,7 @@
 // by substitution; then the four 16 x 16 off-diagonal blocks of the 32 x 32
 // triangles and the two 32 x 32 blocks of the whole, as products on the matrix
 // cores (16x16x4, in the factors' own type).  By rows, each a sum over all
-// earlier columns on the vector units, the inversion was two thirds of the
+// earlier columns on the vector units, the inversion was about half of the
 // kernel.  Alone an f64 sub-tile took 31 us, now 23 us, f32 24 and 17 us; beside
 // the products of the other stream f64 66 and 31 us, because 51 instead of 110 KiB
 // of LDS fit a CU that still runs half of its products.  What remains is the
