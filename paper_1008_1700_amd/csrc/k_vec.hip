@@ -534,48 +534,36 @@ __global__ __launch_bounds__(1024) void k_resid_reduce(int W, const double* __re
   if (g == 0) out[c] = a;
 }
 
-// out = a X + b Y + c Z (per column coefficients); Z may be null
-template <int R>
-__global__ void k_lincomb(int64_t n, Coef3 cf, const double* X, const double* Y, const double* Z,
-                          double* out) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      const int64_t k = i + j * n;
-      double v = cf.a[j] * X[k];
-      if (Y) v += cf.b[j] * Y[k];
-      if (Z) v += cf.c[j] * Z[k];
-      out[k] = v;
-    }
+// out = a X + b Y + c Z (per column coefficients); Z may be null.  Grid (., R):
+// a column per workgroup row, as in the inner iteration's kernels.
+__global__ void k_lincomb(int64_t n, Coef3 cf, const double* X, const double* Y, const double* Z, double* out) {
+  const int j = blockIdx.y;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t k = i + j * n;
+    double v = cf.a[j] * X[k];
+    if (Y) v += cf.b[j] * Y[k];
+    if (Z) v += cf.c[j] * Z[k];
+    out[k] = v;
   }
 }
 
-// partial dot products of up to two vector pairs; [W][R][2]
-template <int R>
+// partial dot products of up to two vector pairs; [W][R][2], grid (W, R)
 __global__ __launch_bounds__(256) void k_dot2(int64_t n, const double* __restrict__ a0,
                                               const double* __restrict__ b0, const double* __restrict__ a1,
                                               const double* __restrict__ b1, double* __restrict__ part) {
-  __shared__ double sh[4][R][2];
-  double acc[R][2];
-#pragma unroll
-  for (int j = 0; j < R; ++j) acc[j][0] = acc[j][1] = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x) {
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      const int64_t k = i + j * n;
-      acc[j][0] += a0[k] * b0[k];
-      if (a1) acc[j][1] += a1[k] * b1[k];
-    }
+  __shared__ double sh[4][1][2];
+  const int j = blockIdx.y, R = gridDim.y;
+  double acc[1][2] = {{0.0, 0.0}};
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+    const int64_t k = i + j * n;
+    acc[0][0] += a0[k] * b0[k];
+    if (a1) acc[0][1] += a1[k] * b1[k];
   }
-  block_sum<R>(acc, sh);
-  if (threadIdx.x == 0)
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      part[((int64_t)blockIdx.x * R + j) * 2 + 0] = acc[j][0];
-      part[((int64_t)blockIdx.x * R + j) * 2 + 1] = acc[j][1];
-    }
+  block_sum<1>(acc, sh);
+  if (threadIdx.x == 0) {
+    part[((int64_t)blockIdx.x * R + j) * 2 + 0] = acc[0][0];
+    part[((int64_t)blockIdx.x * R + j) * 2 + 1] = acc[0][1];
+  }
 }
 
 
@@ -694,11 +682,11 @@ void sum_parts(int rows, int R, int ns, const double* parts, int64_t pstride, in
 }
 void lincomb(int R, int64_t n, const Coef3& cf, const double* X, const double* Y, const double* Z,
              double* out, hipStream_t s) {
-  DDPS_R_DISPATCH(R, hipLaunchKernelGGL(k_lincomb<RR>, dim3(grid_for(n)), dim3(256), 0, s, n, cf, X, Y, Z, out));
+  hipLaunchKernelGGL(k_lincomb, dim3(grid_for(n), R), dim3(256), 0, s, n, cf, X, Y, Z, out);
 }
 void dot2(int R, int64_t n, const double* a0, const double* b0, const double* a1, const double* b1,
           double* part, int W, double* out, hipStream_t s) {
-  DDPS_R_DISPATCH(R, hipLaunchKernelGGL(k_dot2<RR>, dim3(W), dim3(256), 0, s, n, a0, b0, a1, b1, part));
+  hipLaunchKernelGGL(k_dot2, dim3(W, R), dim3(256), 0, s, n, a0, b0, a1, b1, part);
   reduce2(R, W, part, out, nullptr, s);
 }
 
