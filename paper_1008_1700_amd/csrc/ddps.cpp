@@ -440,13 +440,18 @@ struct ScheduleBuilder {
     double tiles, work, longest;
   };
   std::map<std::array<int, 5>, ShapeWork> shape_work;   // (mode, M, N, K, flags)
+  // most launches hold problems of one shape: no lookup for a repeated one
+  static bool same_shape(const GemmProb& a, const GemmProb& b) {
+    return a.M == b.M && a.N == b.N && a.K == b.K && a.flags == b.flags;
+  }
   double mode_time(const ModeCost& c) {
     int BM, BN;
     gemm_tile_shape(h->gdt, c.mode, &BM, &BN);
     double tiles = 0, work = 0, longest = 0;
+    auto it = shape_work.end();
     for (size_t q = (size_t)off; q < gemm.size(); ++q) {
       const GemmProb& P = gemm[q];
-      auto it = shape_work.find({c.mode, P.M, P.N, P.K, P.flags});
+      if (q == (size_t)off || !same_shape(P, gemm[q - 1])) it = shape_work.find({c.mode, P.M, P.N, P.K, P.flags});
       if (it == shape_work.end()) {
         ShapeWork w{0, 0, 0};
         for (int I0 = 0; I0 < P.M; I0 += BM)
@@ -548,16 +553,18 @@ struct ScheduleBuilder {
   // in the XCD's L2 (bf16x3, 64 problems: lower triangle times 1600 x 3200
   // with C0 2.35 ms, all sorted 2.51; times 1600^2 1.05 and 1.13; upper times
   // 1024 x 2048 0.61 and 0.59).  The kernel reads order[logical] for the tile
-  // to compute.  Launches of equal tiles keep the identity (cur_ord = -1).
+  // to compute.  Launches of equal tiles, or with a CU for every tile, keep the
+  // identity (cur_ord = -1).
   void tile_order(int mode, int BM, int BN) {
     cur_ord = -1;
-    if (nwg < 2) return;
+    if (nwg <= 256) return;
     // each tile's rank among the launch's distinct amounts of work (0: most),
     // from one pattern per problem shape
     std::map<std::array<int, 4>, std::vector<int>> shapes;
     std::map<float, int, std::greater<float>> rank;
     for (size_t q = (size_t)off; q < gemm.size(); ++q) {
       const GemmProb& P = gemm[q];
+      if (q > (size_t)off && same_shape(P, gemm[q - 1])) continue;
       std::vector<int>& w = shapes[{P.M, P.N, P.K, P.flags}];
       if (!w.empty()) continue;
       const int tm = (P.M + BM - 1) / BM, tn = (P.N + BN - 1) / BN;
