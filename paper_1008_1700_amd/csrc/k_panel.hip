@@ -60,6 +60,14 @@ __device__ __forceinline__ double lane_value(double x, int lane) {
   return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
 
+// LDS stores of the wave's lanes before their reads by other lanes of it; the
+// hardware keeps that order, so this costs no instruction
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 template <typename T>
@@ -215,6 +223,7 @@ __global__ __launch_bounds__(64 * kW) void k_panel(const PanelProb* __restrict__
     const int o = 2 * kB * (w & 1), ro = up ? o : o + kB, co = up ? o + kB : o;
     T(*H)[kLdT] = &S.H[w >> 1][kB * (w & 1)];
     first(up, ro, co, kB, 0, 0, H);
+    wave_sync();   // in FP32 a lane reads what other lanes stored to H
     second(up, ro, co, kB, 0, 0, H);
   }
   __syncthreads();
