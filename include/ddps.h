@@ -401,7 +401,8 @@ int ddps_mlp_get_params(ddps_mlp m, float* host_params);
 /* Y = net(X).  Asynchronous on the stream. */
 int ddps_mlp_forward(ddps_mlp m, int32_t batch, const float* X, float* Y);
 /* One Adam step on mean((net(X) - T)^2) with learning rate lr > 0; loss
- * (host, may be NULL) receives the loss before the step (synchronises). */
+ * (host, may be NULL) receives the loss before the step (synchronises: the
+ * stream has run up to and with the gradients; the update follows on it). */
 int ddps_mlp_train_step(ddps_mlp m, int32_t batch, const float* X, const float* T, float lr, double* loss);
 /* Gradients of mean((net(X) - T)^2) without a step: host_grads (host,
  * float[param_count], may be NULL) and loss (host, may be NULL). */

@@ -26,7 +26,6 @@ struct ddps_mlp_ctx {
   float *Z1 = nullptr, *Z2 = nullptr, *Z3 = nullptr, *Y = nullptr;
   double* part = nullptr;
   double* h_part = nullptr;
-  hipEvent_t loss_ev = nullptr;   // the loss's partial sums have reached h_part
   int adam_t = 0;
   std::vector<void*> allocs;
   template <typename T>
@@ -67,17 +66,12 @@ int forward(ddps_mlp_ctx* M, int B, const float* X) {
   return hipGetLastError() == hipSuccess ? DDPS_OK : DDPS_E_HIP;
 }
 
-// gradients of mean((Y - T)^2) into M->g; *W: partial sums of the loss on their
-// way to h_part, if it is wanted (read_loss).  They are copied before the
-// products, so that the caller's wait for them does not leave the GPU idle.
-int backward(ddps_mlp_ctx* M, int B, const float* T, bool want_loss, int* W) {
+// gradients of mean((Y - T)^2) into M->g; the loss through *loss, for which the
+// stream is waited for (the products and whatever else was on it are done then)
+int backward(ddps_mlp_ctx* M, int B, const float* T, double* loss) {
   hipStream_t s = M->stream;
   const int64_t ny = (int64_t)B * M->d_out;
-  *W = mlp_mse(ny, 1.f / (float)ny, M->Y, T, M->dYb, M->part, s);
-  if (want_loss &&
-      (hipMemcpyAsync(M->h_part, M->part, sizeof(double) * *W, hipMemcpyDeviceToHost, s) != hipSuccess ||
-       hipEventRecord(M->loss_ev, s) != hipSuccess))
-    return DDPS_E_HIP;
+  const int W = mlp_mse(ny, 1.f / (float)ny, M->Y, T, M->dYb, M->part, s);
   float* g = M->g;
   const __bf16* acts[4] = {M->X0, M->A1, M->A2, M->A3};
   const float* Zs[3] = {M->Z1, M->Z2, M->Z3};
@@ -97,15 +91,15 @@ int backward(ddps_mlp_ctx* M, int B, const float* T, bool want_loss, int* W) {
     dcur = dz;
   }
   mlp_bias_grad(B, bias, s);
-  return hipGetLastError() == hipSuccess ? DDPS_OK : DDPS_E_HIP;
-}
-
-int read_loss(ddps_mlp_ctx* M, int B, int W, double* loss) {
-  if (!loss) return DDPS_OK;
-  if (hipEventSynchronize(M->loss_ev) != hipSuccess) return DDPS_E_HIP;
-  double acc = 0;
-  for (int i = 0; i < W; ++i) acc += M->h_part[i];
-  *loss = acc / (double)((int64_t)B * M->d_out);
+  if (hipGetLastError() != hipSuccess) return DDPS_E_HIP;
+  if (loss) {
+    if (hipMemcpyAsync(M->h_part, M->part, sizeof(double) * W, hipMemcpyDeviceToHost, s) != hipSuccess ||
+        hipStreamSynchronize(s) != hipSuccess)
+      return DDPS_E_HIP;
+    double acc = 0;
+    for (int i = 0; i < W; ++i) acc += M->h_part[i];
+    *loss = acc / (double)ny;
+  }
   return DDPS_OK;
 }
 
@@ -149,8 +143,7 @@ int ddps_mlp_create(ddps_mlp* out, int32_t d_in, int32_t hidden, int32_t d_out, 
             M->alloc(M->A3, B * hidden) && M->alloc(M->dYb, B * d_out) && M->alloc(M->dZ, 3 * B * hidden) &&
             M->alloc(M->Z1, B * hidden) && M->alloc(M->Z2, B * hidden) && M->alloc(M->Z3, B * hidden) &&
             M->alloc(M->Y, B * d_out) && M->alloc(M->part, 256);
-  if (!ok || hipHostMalloc((void**)&M->h_part, 256 * sizeof(double)) != hipSuccess ||
-      hipEventCreateWithFlags(&M->loss_ev, hipEventDisableTiming) != hipSuccess) {
+  if (!ok || hipHostMalloc((void**)&M->h_part, 256 * sizeof(double)) != hipSuccess) {
     ddps_mlp_destroy(M);
     return DDPS_E_NOMEM;
   }
@@ -207,8 +200,7 @@ int ddps_mlp_gradients(ddps_mlp M, int32_t batch, const float* X, const float* T
   if (!M || !X || !T || batch < 1 || batch > M->max_batch) return DDPS_E_ARG;
   int rc = forward(M, batch, X);
   if (rc) return rc;
-  int W;
-  if ((rc = backward(M, batch, T, loss != nullptr, &W)) || (rc = read_loss(M, batch, W, loss))) return rc;
+  if ((rc = backward(M, batch, T, loss))) return rc;
   if (host_grads) {
     if (hipMemcpyAsync(host_grads, M->g, sizeof(float) * M->count, hipMemcpyDeviceToHost, M->stream) != hipSuccess ||
         hipStreamSynchronize(M->stream) != hipSuccess)
@@ -221,12 +213,10 @@ int ddps_mlp_train_step(ddps_mlp M, int32_t batch, const float* X, const float* 
   if (!M || !X || !T || batch < 1 || batch > M->max_batch || !(lr > 0.f)) return DDPS_E_ARG;
   int rc = forward(M, batch, X);
   if (rc) return rc;
-  int W;
-  if ((rc = backward(M, batch, T, loss != nullptr, &W))) return rc;
+  if ((rc = backward(M, batch, T, loss))) return rc;
   M->adam_t += 1;
   mlp_adam(M->count, lr, 0.9f, 0.999f, 1e-8f, M->adam_t, M->p, M->g, M->m, M->v, M->pb, M->stream);
-  if (hipGetLastError() != hipSuccess) return DDPS_E_HIP;
-  return read_loss(M, batch, W, loss);
+  return hipGetLastError() == hipSuccess ? DDPS_OK : DDPS_E_HIP;
 }
 
 void ddps_mlp_destroy(ddps_mlp M) {
@@ -234,7 +224,6 @@ void ddps_mlp_destroy(ddps_mlp M) {
   if (M->stream) (void)hipStreamSynchronize(M->stream);
   for (void* q : M->allocs) (void)hipFree(q);
   if (M->h_part) (void)hipHostFree(M->h_part);
-  if (M->loss_ev) (void)hipEventDestroy(M->loss_ev);
   delete M;
 }
 
