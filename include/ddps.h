@@ -280,9 +280,9 @@ int ddps_last_singular(ddps_handle h, int32_t* block, int64_t* row);
  *   1  64 x 64 only,
  *   2  256 x 128 where every problem allows it (bf16 arithmetic, else as 0),
  *   3  a tile chosen per launch by ddps_autotune (as 0 until it has run),
- *   4  128 x 128 with operands loaded straight into LDS (bf16 arithmetic,
- *      else as 0),
- *   5  256 x 256 on 8 waves (bf16 arithmetic, else as 0; launches with a
+ *   4  128 x 128 where every problem allows it, for bf16 arithmetic with
+ *      operands loaded straight into LDS,
+ *   5  256 x 256 on 8 waves (bf16 arithmetic, else as 4; launches with a
  *      side below 256 take 4's tile).
  * Rebuilds the launch schedules; call before ddps_factor.  Errors:
  * DDPS_E_ARG, DDPS_E_NOMEM, DDPS_E_HIP. */

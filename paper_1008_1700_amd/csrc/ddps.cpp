@@ -50,6 +50,9 @@ struct SumRec {
 enum TimingKind { TK_GEMM = 0, TK_PANEL = 1, TK_SWEEP = 2, TK_RSPMV = 3, TK_RETR = 4, TK_CSR = 5, TK_RFAC = 6,
                   TK_N = 7 };
 
+// offset of the entries of ddps_ctx::mode_choice that are not narrowed
+constexpr int kAsRan = 5;
+
 struct Launch {
   int kind;
   int64_t off;
@@ -59,6 +62,7 @@ struct Launch {
   double bytes;
   int mode;  // GEMM: tile mode; GEMV: 1 = every problem 16-byte aligned (wide loads)
   int64_t ord = -1;  // GEMM: offset of its tile order in d_order, -1 for the plain order
+  int8_t choice = 0;  // GEMM: mode_choice entry that gives this launch the tile it has
 };
 
 struct TimingRec {
@@ -180,7 +184,9 @@ struct ddps_ctx {
                            // 2: 256 x 128 (bf16 arithmetic) where every problem allows,
                            // 3: per launch, from mode_choice, 4 / 5: 128 x 128 / 256 x 256 with
                            // direct LDS loads (bf16 arithmetic) where every problem allows
-  std::vector<int8_t> mode_choice;  // policy 3: requested tile mode of each factor GEMM launch, in order
+  // policy 3: requested tile mode of each factor GEMM launch, in order; kAsRan
+  // more for a mode the launch takes although its problems do not fill the tile
+  std::vector<int8_t> mode_choice;
   int mode_cursor = 0;              // next factor GEMM launch while the schedules are built
   bool use_graph = false;  // capture ddps_factor once as a HIP graph, then replay it
   hipStream_t fstream = nullptr;          // internal stream of the factorisation
@@ -383,6 +389,7 @@ struct ScheduleBuilder {
   std::vector<GemmProb> gemm;
   std::vector<int32_t> order;   // tile orders (see tile_order)
   int64_t cur_ord = -1;
+  int8_t cur_choice = 0;
   std::vector<PanelProb> panel;
   std::vector<GemvProb> gemv;
   // current launch
@@ -504,21 +511,24 @@ struct ScheduleBuilder {
                 (uintptr_t)gemm[q].lda * h->elt | (uintptr_t)gemm[q].ldb * h->elt;
     return bits % 16 == 0;
   }
+  // the largest tile up to `mode` that every problem of the launch fills
+  // (256 x 256 and 256 x 128 only for bf16 arithmetic, 128 x 128, else 64 x 64)
+  int narrowed(int mode) const {
+    if (mode >= 2 && h->gdt < 2) mode = 1;
+    for (size_t q = (size_t)off; q < gemm.size(); ++q) {
+      if (gemm[q].M < 128 || gemm[q].N < 128) mode = 0;
+      else if (mode == 2 && gemm[q].M < 256) mode = 1;
+      else if (mode == 4 && (gemm[q].M < 256 || gemm[q].N < 256)) mode = 3;
+    }
+    return mode;
+  }
   // GEMM launches: the tile of the size rule, or the requested one narrowed to
-  // the largest one every problem of the launch fills (256 x 256 and
-  // 256 x 128 only for bf16 arithmetic, 128 x 128, else 64 x 64); assigns
-  // each problem its first workgroup.
+  // what the launch's problems fill; assigns each problem its first workgroup.
   int finish_gemm() {
     int mode = requested_mode();
     if (mode == -2 && gemm.size() > (size_t)off) mode = auto_mode();
-    else {
-      if (mode >= 2 && h->gdt < 2) mode = 1;
-      for (size_t q = (size_t)off; q < gemm.size(); ++q) {
-        if (gemm[q].M < 128 || gemm[q].N < 128) mode = 0;
-        else if (mode == 2 && gemm[q].M < 256) mode = 1;
-        else if (mode == 4 && (gemm[q].M < 256 || gemm[q].N < 256)) mode = 3;
-      }
-    }
+    else if (mode >= kAsRan) mode = h->gdt < 2 ? std::min(mode - kAsRan, 1) : mode - kAsRan;
+    else mode = narrowed(mode);
     if (mode != 0 || h->gdt < 2) {
       // direct LDS loads need 16-byte aligned operand columns; the 256 x 256
       // tile keeps 256 columns of B within a 32-bit byte offset
@@ -537,6 +547,9 @@ struct ScheduleBuilder {
       flops += gemm_prob_flops(P, BM, BN);
     }
     tile_order(mode, BM, BN);
+    // the size rule does not narrow its choice, a recorded one would be
+    cur_choice = (int8_t)std::max(0, mode);
+    if (narrowed(cur_choice) != cur_choice) cur_choice += kAsRan;
     return mode;
   }
   // Dispatch order of the launch's tiles.  The kernels map workgroup b to
@@ -621,14 +634,14 @@ struct ScheduleBuilder {
                                                                               : (int64_t)gemv.size()) - off;
     const int mode = kind == LK_GEMM ? finish_gemm() : gemv_form();
     if (cnt > 0 && nwg > 0) {
-      out.push_back({kind, off, (int)cnt, nwg, flops, bytes, mode, kind == LK_GEMM ? cur_ord : -1});
+      out.push_back({kind, off, (int)cnt, nwg, flops, bytes, mode, kind == LK_GEMM ? cur_ord : -1, cur_choice});
       if (kind == LK_GEMM) ++h->mode_cursor;
     }
   }
   Launch end_one() {
     const int64_t cnt = (kind == LK_GEMM ? (int64_t)gemm.size() : (int64_t)gemv.size()) - off;
     const int mode = kind == LK_GEMM ? finish_gemm() : gemv_form();
-    return Launch{kind, off, (int)cnt, nwg, flops, bytes, mode, kind == LK_GEMM ? cur_ord : -1};
+    return Launch{kind, off, (int)cnt, nwg, flops, bytes, mode, kind == LK_GEMM ? cur_ord : -1, cur_choice};
   }
   void add_gemm(const void* A, int lda, const void* B, int ldb, const void* C0, int ldc0, void* D, int ldd,
                 int M, int N, int K, int flags) {
@@ -2964,7 +2977,7 @@ std::string tune_key(ddps_ctx* h) {
 // The cache is a flat JSON object {"key": {"streams": s, "tile_policy": q,
 // "factor_ms": ms, "modes": "..."}, ...}, one entry per line, written and
 // read by this file only; "modes" (policy 3) holds the tile mode of each
-// factor GEMM launch as one digit.
+// factor GEMM launch as one digit (kAsRan more where it is not narrowed).
 bool cache_lookup(const char* path, const std::string& key, int* streams, int* policy, double* ms,
                   std::string* modes) {
   if (!path) return false;
@@ -2991,7 +3004,7 @@ bool cache_lookup(const char* path, const std::string& key, int* streams, int* p
   const std::string tag = "\"modes\": \"";
   const size_t mp = txt.find(tag, br);
   if (mp != std::string::npos && mp < end)
-    for (size_t i = mp + tag.size(); i < txt.size() && txt[i] >= '0' && txt[i] <= '4'; ++i) modes->push_back(txt[i]);
+    for (size_t i = mp + tag.size(); i < txt.size() && txt[i] >= '0' && txt[i] < '0' + 2 * kAsRan; ++i) modes->push_back(txt[i]);
   return true;
 }
 
@@ -3079,7 +3092,7 @@ int tune_launch_modes(ddps_ctx* h, int groups, double* ms) {
   static const int policy_of[5] = {0, 1, 2, 4, 5};
   const int nq = h->gdt >= 2 ? 5 : 2;
   std::vector<std::vector<float>> t(nq);
-  std::vector<std::vector<int8_t>> modes(nq);   // tile mode of each launch under each policy
+  std::vector<std::vector<int8_t>> modes(nq);   // tile of each launch under each policy
   int rc;
   std::vector<float> t2;
   for (int q = 0; q < nq; ++q) {
@@ -3091,7 +3104,7 @@ int tune_launch_modes(ddps_ctx* h, int groups, double* ms) {
     for (size_t i = 0; i < t2.size(); ++i) t[q][i] = std::min(t[q][i], t2[i]);
     for (const auto& S : h->sch_group)
       for (const Launch& L : S)
-        if (L.kind == LK_GEMM) modes[q].push_back((int8_t)std::max(0, L.mode));
+        if (L.kind == LK_GEMM) modes[q].push_back(L.choice);
     if (modes[q].size() != t[q].size()) return DDPS_E_STATE;
   }
   h->mode_choice.assign(t[0].size(), 1);
