@@ -1235,7 +1235,7 @@ void build_solve_schedules(ddps_ctx* h, ScheduleBuilder& sb) {
     h->l_pvh = reduced(h->d_mp, h->d_v, h->d_rt, V_DOT);
     h->l_sth = reduced(h->d_ms, h->d_tv, h->d_s, V_DOT | V_DOT2);
   }
-  h->W1 = h->l_pv.nwg * (h->tip_packed ? tipmv_split(h->sdt, h->l_pv.nwg) : 1);
+  h->W1 = h->l_pv.nwg * (h->tip_packed ? tipmv_split(h->sdt, h->t, h->l_pv.nwg) : 1);
 }
 
 int run_launch(ddps_ctx* h, const Launch& L, int R, int64_t ldx, int64_t ldy, const double* dotv,
@@ -1551,7 +1551,7 @@ int inner_solve(ddps_ctx* h, int k, int use_guess, double tol, int maxit, std::v
   // few: three sets of W1 then (the two products' and s.s), for which launches of
   // up to some 600 workgroups have room.
   const int W1 = h->W1;
-  const bool step = !prec && h->l_st.kind == LK_TIPMV && tipmv_steps(h->sdt, h->l_st.nwg) && W1 * R <= kFuseParts &&
+  const bool step = !prec && h->l_st.kind == LK_TIPMV && tipmv_steps(h->sdt, h->t, h->l_st.nwg) && W1 * R <= kFuseParts &&
                     ((int64_t)3 * W1 + W2) * R * 2 <= h->part_cap;
   double* partA = h->d_part_buf;
   double* partT = step ? partA + (int64_t)W1 * R * 2 : partA;

@@ -209,10 +209,10 @@ struct PartSums {
 constexpr int kFuseParts = 2048;
 // reduced-matrix product on the packed tips (same records as launch_gemv,
 // A = first packed row, lda = 2t; nrhs 1 or 2; one partial per workgroup,
-// tipmv_split(nwg) of them per 64 rows), whether tips of this size are packed
+// tipmv_split of them per 64 rows), whether tips of this size are packed
 // for it, and the packing of the tips after a factorisation
 bool tipmv_packs(int dtype, int t);
-int tipmv_split(int dtype, int nwg);
+int tipmv_split(int dtype, int t, int nwg);
 // the first half of an iteration's step within the product G s: s = r - alpha v
 // is formed where the product reads it (in place of bicg_s); partial s.s in ss
 struct TipStep {
@@ -222,7 +222,7 @@ struct TipStep {
   const double *r, *v;
   double *s, *ss;
 };
-bool tipmv_steps(int dtype, int nwg);   // whether launch_tipmv takes a step
+bool tipmv_steps(int dtype, int t, int nwg);   // whether launch_tipmv takes a step
 void launch_tipmv(int dtype, int nrhs, int t, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
                   int64_t ldy, const double* dotv, double* partial, const int32_t* stop, hipStream_t s,
                   const TipStep* step = nullptr);

@@ -575,7 +575,7 @@ __global__ __launch_bounds__(256) void k_tipmv(const GemvProb* __restrict__ prob
 // streams its 64 rows one after another as one contiguous run, and a wave's
 // vector entries (NS pieces of 64 VEC columns) stay in registers.  A wave
 // reduces its part of eight rows at a time; the four parts of a row are added
-// in LDS.  1.06 GB of f32 tips take 175 us (6.0 TB/s; by rows 187 us).
+// in LDS.  1.06 GB of f32 tips take 177 us (6.0 TB/s; by rows 189 us).
 template <typename T, int R, int NS>
 __global__ __launch_bounds__(256) void k_tipmv_c(const GemvProb* __restrict__ probs, int nprob,
                                                  int64_t ldx, int64_t ldy,
@@ -712,20 +712,50 @@ __global__ __launch_bounds__(256) void k_pack_tips(const BlockInfo* __restrict__
 // whether rows of 2t entries are kept packed (at most 16 KiB each)
 bool tipmv_packs(int dtype, int t) { return 2 * t * (dtype == 0 ? 8 : 4) <= 16384; }
 
-// Workgroups (and partial sums) per 64 rows: four of 16 rows each where
-// 64-row workgroups would leave CUs idle.  Four against one, in us: f64 rows of
-// 512 entries on 120 workgroups 5.8 / 8.3, but of 2048 on 224 47.7 / 39.6 (a
-// CU's workgroups read the same vector entries again); f32 (one: the column
-// split) 1024 entries on 240 16.9 / 20.5, on 496 27.4 / 24.6.
-int tipmv_split(int dtype, int nwg) { return nwg <= (dtype == 0 ? 128 : 256) ? 4 : 1; }
+// Workgroups (and partial sums) per 64 rows: four of 16 rows each where 64-row
+// workgroups would leave CUs idle, two where four would keep so many rows of 16
+// KiB in flight that they meet in the same memory channels.  One column, us with
+// four / two / one to 64 rows (FP32's one: the better of rows and column split):
+//   f64  1024 entries   128 workgroups 12.9 / 17.4 / 15.4, 192 18.5 / 22.0 / 18.1
+//        1920           150            22.9 / 24.3 / 26.2, 210 31.1 / 30.7 / 31.6
+//        2048 (16 KiB)   64            15.3 / 16.6 / 23.7,  96 20.9 / 19.7 / 24.1,
+//                       128            27.0 / 24.3 / 25.4, 160 34.0 / 28.4 / 28.1
+//   f32  1024           192            11.0 / 10.2 / 12.6, 224 16.1 / 12.4 / 13.2
+//        1536           216            15.9 / 16.1 / 16.9, 264 18.1 / 18.3 / 18.9
+//        2048           192            18.9 / 22.7 / 20.2, 256 24.5 / 30.8 / 23.4
+//        3072           144            18.9 / 19.6 / 21.3, 240 28.9 / 29.0 / 26.6
+//        3456           216            28.8 / 29.1 / 29.6
+//        4096 (16 KiB)  128            27.7 / 24.9 / 26.1, 192 37.4 / 31.6 / 29.7
+int tipmv_split(int dtype, int t, int nwg) {
+  const int row = 2 * t * (dtype == 0 ? 8 : 4);   // bytes
+  if (row % 16384 == 0) return nwg < 96 ? 4 : nwg <= 128 ? 2 : 1;
+  if (dtype == 0) return nwg <= 160 ? 4 : 1;
+  return nwg <= (row % 4096 == 0 ? 192 : 256) ? 4 : 1;
+}
 
-bool tipmv_steps(int dtype, int nwg) { return dtype == 0 || tipmv_split(dtype, nwg) == 4; }
+// FP32 with one workgroup to 64 rows: the column split where its pieces (1024
+// entries of a row each, a quarter per wave) are nearly filled, else by rows.
+// Column split / rows, us:
+//   one column    1024 entries, 512 workgroups 24.9 / 23.5   1536, 768 56.0 / 47.3
+//                 1664, 520 44.8 / 34.8                      1920, 780 74.6 / 67.0
+//                 2048, 512 40.0 / 42.3, on 256 24.4 / 23.4
+//                 2176, 306 28.1 / 29.9    3200, 1000 138 / 152   4096, 512 86.5 / 90.1
+//   two columns   2304, 288 35.7 / 32.8
+//                 2688, 1008 126 / 139     3200, 1000 153 / 166   3712, 2030 325 / 345
+static bool tipmv_by_columns(int dtype, int nrhs, int t, int nwg) {
+  if (dtype == 0) return false;
+  if (t <= 1024) return t == 1024 && nwg > 256;
+  return nrhs == 1 || 9 * 2 * t >= 7 * ((2 * t + 1023) / 1024 * 1024);
+}
+
+// the step for FP32 only where a workgroup takes few rows, so that its sums are worth taking up
+bool tipmv_steps(int dtype, int t, int nwg) { return dtype == 0 || tipmv_split(dtype, t, nwg) > 1; }
 
 void launch_tipmv(int dtype, int nrhs, int t, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
                   int64_t ldy, const double* dotv, double* partial, const int32_t* stop, hipStream_t s,
                   const TipStep* step) {
   if (nwg <= 0 || nprob <= 0) return;
-  const int sb = tipmv_split(dtype, nwg);
+  const int sb = tipmv_split(dtype, t, nwg);
   const size_t lds = (size_t)2 * t * (nrhs == 1 ? 1 : 2) * sizeof(double);
   // Three workgroups of the column split fit a CU for one column and rows of two
   // pieces.  Where two to a CU take no more rounds, LDS holds it to two, which
@@ -743,27 +773,26 @@ void launch_tipmv(int dtype, int nrhs, int t, const GemvProb* probs, int nprob, 
                        dotv, partial, stop, TipStep{})
 #define DDPS_TIPMV_C(T, R)                                            \
   switch (ns) {                                                       \
-    case 1: DDPS_TIPMV(0, k_tipmv_c<T, R, 1>); break;                 \
     case 2: DDPS_TIPMV(R == 1 ? two : 0, k_tipmv_c<T, R, 2>); break;  \
     case 3: DDPS_TIPMV(0, k_tipmv_c<T, R, 3>); break;                 \
     default: DDPS_TIPMV(0, k_tipmv_c<T, R, 4>); break;                \
   }
-  if (dtype == 0) {
-    if (nrhs == 1) {
-      if (sb == 4) { DDPS_TIPMV_S(double, 1, 4); }
-      else { DDPS_TIPMV_S(double, 1, 16); }
-    } else {
-      if (sb == 4) { DDPS_TIPMV_S(double, 2, 4); }
-      else { DDPS_TIPMV_S(double, 2, 16); }
-    }
-  } else if (sb == 4) {
-    if (nrhs == 1) { DDPS_TIPMV_S(float, 1, 4); }
-    else { DDPS_TIPMV_S(float, 2, 4); }
-  } else {
+#define DDPS_TIPMV_R(T, R)                   \
+  if (sb == 4) { DDPS_TIPMV_S(T, R, 4); }      \
+  else if (sb == 2) { DDPS_TIPMV_S(T, R, 8); } \
+  else { DDPS_TIPMV_S(T, R, 16); }
+  if (sb == 1 && tipmv_by_columns(dtype, nrhs, t, nwg)) {
     const int ns = (2 * t + 1023) / 1024;
     if (nrhs == 1) { DDPS_TIPMV_C(float, 1) }
     else { DDPS_TIPMV_C(float, 2) }
+  } else if (dtype == 0) {
+    if (nrhs == 1) { DDPS_TIPMV_R(double, 1) }
+    else { DDPS_TIPMV_R(double, 2) }
+  } else {
+    if (nrhs == 1) { DDPS_TIPMV_R(float, 1) }
+    else { DDPS_TIPMV_R(float, 2) }
   }
+#undef DDPS_TIPMV_R
 #undef DDPS_TIPMV_C
 #undef DDPS_TIPMV_S
 #undef DDPS_TIPMV
