@@ -63,6 +63,7 @@ struct Launch {
   int mode;  // GEMM: tile mode; GEMV: 1 = every problem 16-byte aligned (wide loads)
   int64_t ord = -1;  // GEMM: offset of its tile order in d_order, -1 for the plain order
   int8_t choice = 0;  // GEMM: mode_choice entry that gives this launch the tile it has
+  int cols = 0;       // GEMV: columns of the widest range
 };
 
 struct TimingRec {
@@ -399,12 +400,14 @@ struct ScheduleBuilder {
   double flops = 0, bytes = 0;
   bool gemv_aligned = true;
   bool gemv_groups = true;   // column ranges and splits in groups of 16
+  int gemv_cols = 0;         // columns of the widest range
 
   void begin(int k) {
     kind = k;
     nwg = 0;
     flops = bytes = 0;
     gemv_aligned = gemv_groups = true;
+    gemv_cols = 0;
     off = k == LK_GEMM ? (int64_t)gemm.size() : k == LK_PANEL ? (int64_t)panel.size() : (int64_t)gemv.size();
   }
   // Tile mode the policy asks for; -2: by the size rule (auto_mode).
@@ -634,14 +637,14 @@ struct ScheduleBuilder {
                                                                               : (int64_t)gemv.size()) - off;
     const int mode = kind == LK_GEMM ? finish_gemm() : gemv_form();
     if (cnt > 0 && nwg > 0) {
-      out.push_back({kind, off, (int)cnt, nwg, flops, bytes, mode, kind == LK_GEMM ? cur_ord : -1, cur_choice});
+      out.push_back({kind, off, (int)cnt, nwg, flops, bytes, mode, kind == LK_GEMM ? cur_ord : -1, cur_choice, gemv_cols});
       if (kind == LK_GEMM) ++h->mode_cursor;
     }
   }
   Launch end_one() {
     const int64_t cnt = (kind == LK_GEMM ? (int64_t)gemm.size() : (int64_t)gemv.size()) - off;
     const int mode = kind == LK_GEMM ? finish_gemm() : gemv_form();
-    return Launch{kind, off, (int)cnt, nwg, flops, bytes, mode, kind == LK_GEMM ? cur_ord : -1, cur_choice};
+    return Launch{kind, off, (int)cnt, nwg, flops, bytes, mode, kind == LK_GEMM ? cur_ord : -1, cur_choice, gemv_cols};
   }
   void add_gemm(const void* A, int lda, const void* B, int ldb, const void* C0, int ldc0, void* D, int ldd,
                 int M, int N, int K, int flags) {
@@ -669,6 +672,7 @@ struct ScheduleBuilder {
     if (G.rows <= 0) return;
     gemv_aligned = gemv_aligned && reinterpret_cast<uintptr_t>(G.A) % 16 == 0 &&
                    (G.lda * (int64_t)elt_bytes) % 16 == 0;
+    gemv_cols = std::max(gemv_cols, G.ce - G.cb);
     gemv_groups = gemv_groups && G.cb % 16 == 0 && G.ce % 16 == 0 && G.split % 16 == 0;
     G.wg0 = nwg;
     nwg += G.rows / 64;
@@ -1257,7 +1261,7 @@ int run_launch(ddps_ctx* h, const Launch& L, int R, int64_t ldx, int64_t ldy, co
                    step);
       break;
     default:
-      launch_gemv(h->sdt, R, L.mode, h->d_gemv + L.off, L.nprob, L.nwg, ldx, ldy, dotv, partial, stop, s);
+      launch_gemv(h->sdt, R, L.mode, L.cols, h->d_gemv + L.off, L.nprob, L.nwg, ldx, ldy, dotv, partial, stop, s);
       break;
   }
   h->tim_end(tkind, a, L.flops * (L.kind == LK_GEMV || L.kind == LK_TIPMV ? R : 1), L.bytes, s);

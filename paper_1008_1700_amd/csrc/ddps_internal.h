@@ -192,11 +192,12 @@ void launch_gemm(int dtype, int mode, const GemmProb* probs, int nprob, int nwg,
 void gemm_tile_shape(int dtype, int mode, int* bm, int* bn);
 void launch_panel(int dtype, const PanelProb* probs, int nprob, const double* thresh,
                   unsigned long long* bad, hipStream_t s);
-// form 0: plain (k_gemv); 1: every problem's A and column stride are 16-byte
-// aligned (k_gemv_w); 2: aligned, and for FP32 operands with 4 or more
+// cols: columns of the widest range among the problems.  form 0: plain (k_gemv);
+// 1: every problem's A and column stride are 16-byte aligned (k_gemv_n,
+// k_gemv_w); 2: aligned, and for FP32 operands with 4 or more
 // right-hand sides run on the FP32 matrix cores with FP32 sums (k_gemv_mf32),
 // otherwise as form 1
-void launch_gemv(int dtype, int nrhs, int form, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
+void launch_gemv(int dtype, int nrhs, int form, int cols, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
                  int64_t ldy, const double* dotv, double* partial, const int32_t* stop, hipStream_t s);
 // Sums of a reduction as a kernel takes them: reduced already (W = 0, in
 // sums), or W partials of R columns at part, which the kernel adds up itself

@@ -256,8 +256,8 @@ __global__ __launch_bounds__(256) void k_gemv_w(const GemvProb* __restrict__ pro
 // vector entries are staged in LDS once per workgroup (CH columns at a time), and the NW waves take
 // interleaved groups of columns, U loads of 1 KiB each in flight per wave (a
 // lane reads VEC consecutive rows of one column, a wave load 64 rows of VEC
-// columns).  The packed-triangle masks
-// change only a slab's diagonal columns [r0, r0 + 64).  Epilogue, flags and
+// columns).  SHORT: ranges of at most U loads per wave, without the stage in LDS:
+// a lane loads its columns' vector entries beside them.  Epilogue, flags and
 // partial sums as in k_gemv.
 //
 // Bound: HBM for long launches; the sweeps are chains of short launches, so
@@ -266,7 +266,7 @@ __global__ __launch_bounds__(256) void k_gemv_w(const GemvProb* __restrict__ pro
 // blocks) and a 512-wide f64 one of 16 blocks 20.1 us; this form takes 31 us,
 // and 7 us with sixteen waves.
 // ------------------------------------------------------------------------
-template <typename T, int R, int NW>
+template <typename T, int R, int NW, bool SHORT>
 __global__ __launch_bounds__(64 * NW) void k_gemv_n(const GemvProb* __restrict__ probs, int nprob,
                                                     int64_t ldx, int64_t ldy,
                                                     const double* __restrict__ dotv,
@@ -275,10 +275,11 @@ __global__ __launch_bounds__(64 * NW) void k_gemv_n(const GemvProb* __restrict__
   constexpr int VEC = 16 / sizeof(T);   // rows per lane
   constexpr int LPC = 64 / VEC;         // lanes per column
   constexpr int U = 8;                  // loads in flight per lane
-  constexpr int CH = 2048 / R;          // columns staged at a time
+  constexpr int CH = SHORT ? U * NW * VEC : 2048 / R;   // columns at a time
   typedef T vec_t __attribute__((ext_vector_type(VEC)));
   // the vector entries, then the waves' sums
-  __shared__ __attribute__((aligned(16))) double xs[CH * R > NW * 64 * R ? CH * R : NW * 64 * R];
+  constexpr int XS = SHORT ? 0 : CH * R;
+  __shared__ __attribute__((aligned(16))) double xs[XS > NW * 64 * R ? XS : NW * 64 * R];
   double (*red)[64][R] = (double (*)[64][R])xs;
   if (stop) {
     bool all = true;
@@ -307,40 +308,70 @@ __global__ __launch_bounds__(64 * NW) void k_gemv_n(const GemvProb* __restrict__
   for (int e = 0; e < VEC; ++e)
 #pragma unroll
     for (int j = 0; j < R; ++j) acc[e][j] = 0.0;
-  for (int c0 = cb; c0 < ce; c0 += CH) {
-    const int c1 = min(ce, c0 + CH);
-    if (c0 > cb) __syncthreads();   // every wave is done with the previous columns
-    for (int i = tid; i < (c1 - c0) * R; i += 64 * NW) {
-      const int cc = c0 + i % (c1 - c0), j = i / (c1 - c0);
-      xs[(cc - c0) * R + j] = cc < split ? P.x1[cc + j * ldx] : P.x2[(cc - split) + j * ldx];
+  auto xval = [&](int cc, int j) __attribute__((always_inline)) {
+    return cc < split ? P.x1[cc + j * ldx] : P.x2[(cc - split) + j * ldx];
+  };
+  auto fetch = [&](vec_t (&a)[U], int c, int c1) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int cc = c + u * NW * VEC;
+      a[u] = cc < c1 ? *(const vec_t*)(A + (int64_t)cc * lda) : vec_t{};
     }
-    __syncthreads();
-    // wave g takes the column groups c0 + VEC (g + NW s), s = 0, 1, ...
-    for (int c = c0 + g * VEC + q; c - q < c1; c += U * NW * VEC) {
-      vec_t a[U];
+  };
+  // the packed-triangle masks change only the columns [r0, r0 + 64) of a slab
+  auto fix = [&](vec_t& a, int cc) __attribute__((always_inline)) {
+    if (masked && cc >= r0 && cc < r0 + 64) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int cc = c + u * NW * VEC;
-        a[u] = cc < c1 ? *(const vec_t*)(A + (int64_t)cc * lda) : vec_t{};
+      for (int e = 0; e < VEC; ++e) {
+        const int rr = r0 + rl + e;
+        if (mlu) a[e] = rr > cc ? a[e] : (rr == cc ? T(1) : T(0));
+        if (mup) a[e] = rr <= cc ? a[e] : T(0);
+        if (mlo) a[e] = rr >= cc ? a[e] : T(0);
       }
+    }
+  };
+  // wave g takes the column groups c0 + VEC (g + NW s), s = 0, 1, ...
+  if constexpr (SHORT) {
+    vec_t a[U];
+    double xv[U][R];
+    const int c = cb + g * VEC + q;
+    fetch(a, c, ce);
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int cc = c + u * NW * VEC;
-        if (cc >= c1) continue;
-        if (masked && cc >= r0 && cc < r0 + 64) {
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-          for (int e = 0; e < VEC; ++e) {
-            const int rr = r0 + rl + e;
-            if (mlu) a[u][e] = rr > cc ? a[u][e] : (rr == cc ? T(1) : T(0));
-            if (mup) a[u][e] = rr <= cc ? a[u][e] : T(0);
-            if (mlo) a[u][e] = rr >= cc ? a[u][e] : T(0);
+      for (int j = 0; j < R; ++j) xv[u][j] = c + u * NW * VEC < ce ? xval(c + u * NW * VEC, j) : 0.0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (c + u * NW * VEC >= ce) continue;
+      fix(a[u], c + u * NW * VEC);
+#pragma unroll
+      for (int j = 0; j < R; ++j)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) acc[e][j] += (double)a[u][e] * xv[u][j];
+    }
+  } else {
+    for (int c0 = cb; c0 < ce; c0 += CH) {
+      const int c1 = min(ce, c0 + CH);
+      if (c0 > cb) __syncthreads();   // every wave is done with the previous columns
+      for (int i = tid; i < (c1 - c0) * R; i += 64 * NW) {
+        const int cc = c0 + i % (c1 - c0), j = i / (c1 - c0);
+        xs[(cc - c0) * R + j] = xval(cc, j);
+      }
+      __syncthreads();
+      for (int c = c0 + g * VEC + q; c - q < c1; c += U * NW * VEC) {
+        vec_t a[U];
+        fetch(a, c, c1);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int cc = c + u * NW * VEC;
+          if (cc >= c1) continue;
+          fix(a[u], cc);
+#pragma unroll
+          for (int j = 0; j < R; ++j) {
+            const double xv = xs[(cc - c0) * R + j];
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) acc[e][j] += (double)a[u][e] * xv;
           }
-        }
-#pragma unroll
-        for (int j = 0; j < R; ++j) {
-          const double xv = xs[(cc - c0) * R + j];
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) acc[e][j] += (double)a[u][e] * xv;
         }
       }
     }
@@ -351,7 +382,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemv_n(const GemvProb* __restrict__
 #pragma unroll
     for (int j = 0; j < R; ++j)
       for (int off = LPC; off < 64; off <<= 1) acc[e][j] += __shfl_xor(acc[e][j], off, 64);
-  __syncthreads();   // every wave is done with the vector entries
+  if (!SHORT) __syncthreads();   // every wave is done with the vector entries
   if (lane < LPC) {
 #pragma unroll
     for (int e = 0; e < VEC; ++e)
@@ -956,37 +987,47 @@ __global__ __launch_bounds__(256) void k_gemv_mf32(const GemvProb* __restrict__ 
 }
 
 template <typename T>
-static void gemv_dispatch(int nrhs, bool wide, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
+static void gemv_dispatch(int nrhs, bool wide, int cols, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
                           int64_t ldy, const double* dotv, double* partial, const int32_t* stop,
                           hipStream_t s) {
-#define DDPS_GEMV(...) \
-  hipLaunchKernelGGL((__VA_ARGS__), dim3(nwg), dim3(threads), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop)
-  // one workgroup per CU or fewer: sixteen waves each, so that a short launch
-  // has all its loads in flight at once; beyond, four fill the CUs with less
-  // to add up.  Sixteen against four on f64 triangles of 512 rows, in us: 128
-  // workgroups 7.0 / 11.9, 512 workgroups 20.8 / 19.3 (f32 14.2 / 11.7); of 64
-  // rows on 2000 23.8 / 12.7
-  const bool big = wide && nrhs <= 2 && nwg <= 256;
-  const int threads = big ? 1024 : 256;
+#define DDPS_GEMV(NT, ...) \
+  hipLaunchKernelGGL((__VA_ARGS__), dim3(nwg), dim3(NT), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop)
+#define DDPS_GEMV_N(NW, SHORT)                                        \
+  if (nrhs == 1) DDPS_GEMV(64 * NW, k_gemv_n<T, 1, NW, SHORT>);       \
+  else DDPS_GEMV(64 * NW, k_gemv_n<T, 2, NW, SHORT>)
+  if (wide && nrhs <= 2) {
+    // Ranges that four or eight waves load at once need no stage in LDS: f64
+    // triangles of 64 rows, 4 / 64 / 300 workgroups, us, 16 waves and stage 3.4 / 3.6
+    // / -, four waves and stage - / - / 3.6, without 2.8 / 2.9 / 3.3 (two columns, f32:
+    // 5.0 / 5.1 / 4.3 and 3.6 / 3.9 / 4.0); of 128 rows, eight waves, 64 / 1000
+    // workgroups 3.8 / 10.1 and 3.2 / 9.2, two columns 4.4 / 10.7 and 3.8 / 11.7.
+    // Wider ones, one workgroup per CU or fewer: sixteen waves each, so that a
+    // short launch has all its loads in flight at once; beyond, four fill the CUs with
+    // less to add up.  Sixteen against four on f64 triangles of 512 rows: 128
+    // workgroups 7.0 / 11.9, 512 workgroups 20.8 / 19.3 (f32 14.2 / 11.7).
+    constexpr int once = 8 * 4 * 16 / (int)sizeof(T);   // columns that four waves load at once
+    if (cols <= once) { DDPS_GEMV_N(4, true); }
+    else if (cols <= 2 * once && nwg <= 512) { DDPS_GEMV_N(8, true); }
+    else if (nwg <= 256) { DDPS_GEMV_N(16, false); }
+    else { DDPS_GEMV_N(4, false); }
+    return;
+  }
   if (wide) {
-    switch (nrhs) {
-      case 1: if (big) DDPS_GEMV(k_gemv_n<T, 1, 16>); else DDPS_GEMV(k_gemv_n<T, 1, 4>); break;
-      case 2: if (big) DDPS_GEMV(k_gemv_n<T, 2, 16>); else DDPS_GEMV(k_gemv_n<T, 2, 4>); break;
-      case 4: DDPS_GEMV(k_gemv_w<T, 4>); break;
-      default: DDPS_GEMV(k_gemv_w<T, 8>); break;
-    }
+    if (nrhs == 4) DDPS_GEMV(256, k_gemv_w<T, 4>);
+    else DDPS_GEMV(256, k_gemv_w<T, 8>);
     return;
   }
   switch (nrhs) {
-    case 1: DDPS_GEMV(k_gemv<T, 1>); break;
-    case 2: DDPS_GEMV(k_gemv<T, 2>); break;
-    case 4: DDPS_GEMV(k_gemv<T, 4>); break;
-    default: DDPS_GEMV(k_gemv<T, 8>); break;
+    case 1: DDPS_GEMV(256, k_gemv<T, 1>); break;
+    case 2: DDPS_GEMV(256, k_gemv<T, 2>); break;
+    case 4: DDPS_GEMV(256, k_gemv<T, 4>); break;
+    default: DDPS_GEMV(256, k_gemv<T, 8>); break;
   }
+#undef DDPS_GEMV_N
 #undef DDPS_GEMV
 }
 
-void launch_gemv(int dtype, int nrhs, int form, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
+void launch_gemv(int dtype, int nrhs, int form, int cols, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
                  int64_t ldy, const double* dotv, double* partial, const int32_t* stop, hipStream_t s) {
   if (nwg <= 0 || nprob <= 0) return;
   if (dtype == 1 && form == 2 && nrhs >= 4) {
@@ -996,8 +1037,8 @@ void launch_gemv(int dtype, int nrhs, int form, const GemvProb* probs, int nprob
       hipLaunchKernelGGL(k_gemv_mf32<8>, dim3(nwg), dim3(256), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop);
     return;
   }
-  if (dtype == 0) gemv_dispatch<double>(nrhs, form >= 1, probs, nprob, nwg, ldx, ldy, dotv, partial, stop, s);
-  else gemv_dispatch<float>(nrhs, form >= 1, probs, nprob, nwg, ldx, ldy, dotv, partial, stop, s);
+  if (dtype == 0) gemv_dispatch<double>(nrhs, form >= 1, cols, probs, nprob, nwg, ldx, ldy, dotv, partial, stop, s);
+  else gemv_dispatch<float>(nrhs, form >= 1, cols, probs, nprob, nwg, ldx, ldy, dotv, partial, stop, s);
 }
 
 }  // namespace ddps
