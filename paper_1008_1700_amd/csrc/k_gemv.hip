@@ -127,9 +127,10 @@ __global__ __launch_bounds__(256) void k_gemv(const GemvProb* __restrict__ probs
 // consecutive rows of one column in one 16-byte load, so one wave load
 // covers 64 rows of VEC columns (1 KB) instead of 64 rows of one column.
 // The VEC column slots of a wave are summed by lane shuffles, the 4 waves
-// through LDS; epilogue, flags and partial sums as in k_gemv.
+// through LDS; epilogue, flags and partial sums as in k_gemv.  U loads are in
+// flight per lane.
 // ------------------------------------------------------------------------
-template <typename T, int R>
+template <typename T, int R, int U>
 __global__ __launch_bounds__(256) void k_gemv_w(const GemvProb* __restrict__ probs, int nprob,
                                                 int64_t ldx, int64_t ldy,
                                                 const double* __restrict__ dotv,
@@ -173,7 +174,6 @@ __global__ __launch_bounds__(256) void k_gemv_w(const GemvProb* __restrict__ pro
   // columns are staged once per workgroup in LDS (double-buffered), so a
   // lane reads its columns' R entries as 16-byte LDS reads instead of R
   // separate global loads
-  constexpr int U = 8;           // loads in flight per lane (four: 521 us for 2.5 GB of f64, 8 rhs; eight: 479 us)
   constexpr int RC = U * STEP;   // columns per round
   __shared__ __attribute__((aligned(16))) double xs[2][RC][R];
   int buf = 0;
@@ -986,12 +986,27 @@ __global__ __launch_bounds__(256) void k_gemv_mf32(const GemvProb* __restrict__ 
   }
 }
 
+// rounds of workgroups that a launch of kernel K makes on the 256 CUs
+template <auto K>
+static int gemv_rounds(int nwg) {
+  static const int per_cu = [] {
+    int n = 0;
+    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, K, 256, 0) == hipSuccess && n > 0 ? n : 1;
+  }();
+  return (nwg + 256 * per_cu - 1) / (256 * per_cu);
+}
+
 template <typename T>
 static void gemv_dispatch(int nrhs, bool wide, int cols, const GemvProb* probs, int nprob, int nwg, int64_t ldx,
                           int64_t ldy, const double* dotv, double* partial, const int32_t* stop,
                           hipStream_t s) {
 #define DDPS_GEMV(NT, ...) \
   hipLaunchKernelGGL((__VA_ARGS__), dim3(nwg), dim3(NT), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop)
+#define DDPS_GEMV_W(R)                                                                      \
+  if (gemv_rounds<k_gemv_w<T, R, 4>>(nwg) < gemv_rounds<k_gemv_w<T, R, 8>>(nwg))            \
+    DDPS_GEMV(256, k_gemv_w<T, R, 4>);                                                      \
+  else                                                                                      \
+    DDPS_GEMV(256, k_gemv_w<T, R, 8>)
 #define DDPS_GEMV_N(NW, SHORT)                                        \
   if (nrhs == 1) DDPS_GEMV(64 * NW, k_gemv_n<T, 1, NW, SHORT>);       \
   else DDPS_GEMV(64 * NW, k_gemv_n<T, 2, NW, SHORT>)
@@ -1013,8 +1028,13 @@ static void gemv_dispatch(int nrhs, bool wide, int cols, const GemvProb* probs, 
     return;
   }
   if (wide) {
-    if (nrhs == 4) DDPS_GEMV(256, k_gemv_w<T, 4>);
-    else DDPS_GEMV(256, k_gemv_w<T, 8>);
+    // Eight loads in flight, or four where the smaller kernel, of which more
+    // workgroups fit a CU, makes fewer rounds.  Eight / four, f64, us: 8 columns, 512 x
+    // 512 triangles, 1040 workgroups (2 / 1 rounds) 58.6 / 50.5, 2400 (3 / 2) 110
+    // / 105; 1600 x 3200, 1600 (2 / 2) 477 / 514; 4 columns, 768 x 1536, 1536 (2 / 1)
+    // 226 / 204, 1024 x 2048, 2048 (2 / 2) 346 / 389.
+    if (nrhs == 4) DDPS_GEMV_W(4);
+    else DDPS_GEMV_W(8);
     return;
   }
   switch (nrhs) {
@@ -1024,6 +1044,7 @@ static void gemv_dispatch(int nrhs, bool wide, int cols, const GemvProb* probs, 
     default: DDPS_GEMV(256, k_gemv<T, 8>); break;
   }
 #undef DDPS_GEMV_N
+#undef DDPS_GEMV_W
 #undef DDPS_GEMV
 }
 
