@@ -463,14 +463,19 @@ struct ScheduleBuilder {
       const GemmProb& P = gemm[q];
       if (q == (size_t)off || !same_shape(P, gemm[q - 1])) it = shape_work.find({c.mode, P.M, P.N, P.K, P.flags});
       if (it == shape_work.end()) {
+        // whole tiles of a side without a triangle are alike
         ShapeWork w{0, 0, 0};
-        for (int I0 = 0; I0 < P.M; I0 += BM)
-          for (int J0 = 0; J0 < P.N; J0 += BN) {
+        const bool ta = P.flags & (G_A_UP | G_A_LO), tb = P.flags & (G_B_UP | G_B_LO);
+        for (int I0 = 0, ni; I0 < P.M; I0 += ni * BM) {
+          ni = ta ? 1 : std::max(1, (P.M - I0) / BM);
+          for (int J0 = 0, nj; J0 < P.N; J0 += nj * BN) {
+            nj = tb ? 1 : std::max(1, (P.N - J0) / BN);
             const double k = tile_work(P, c.mode, BM, BN, I0, J0);
-            w.tiles += 1;
-            w.work += k;
+            w.tiles += (double)ni * nj;
+            w.work += (double)ni * nj * k;
             w.longest = std::max(w.longest, k);
           }
+        }
         it = shape_work.insert({{c.mode, P.M, P.N, P.K, P.flags}, w}).first;
       }
       tiles += it->second.tiles;
@@ -575,38 +580,49 @@ struct ScheduleBuilder {
     cur_ord = -1;
     if (nwg <= 256) return;
     // each tile's rank among the launch's distinct amounts of work (0: most),
-    // from one pattern per problem shape
-    std::map<std::array<int, 4>, std::vector<int>> shapes;
+    // from one pattern per problem shape; tiles that differ in a side without a
+    // triangle only are alike (but for its last, partly filled one)
+    struct Pattern {
+      std::vector<float> work;   // of the tiles looked at
+      std::vector<int> of;       // per tile its entry in work, then its rank
+    };
+    std::map<std::array<int, 4>, Pattern> shapes;
     std::map<float, int, std::greater<float>> rank;
     for (size_t q = (size_t)off; q < gemm.size(); ++q) {
       const GemmProb& P = gemm[q];
       if (q > (size_t)off && same_shape(P, gemm[q - 1])) continue;
-      std::vector<int>& w = shapes[{P.M, P.N, P.K, P.flags}];
-      if (!w.empty()) continue;
+      Pattern& w = shapes[{P.M, P.N, P.K, P.flags}];
+      if (!w.of.empty()) continue;
       const int tm = (P.M + BM - 1) / BM, tn = (P.N + BN - 1) / BN;
-      w.resize((size_t)tm * tn);
-      for (int l = 0; l < tm * tn; ++l) {
-        const float k = (float)tile_work(P, mode, BM, BN, (l % tm) * BM, (l / tm) * BN);
-        rank[k] = 0;
-        std::memcpy(&w[l], &k, sizeof(k));
-      }
+      const bool ta = P.flags & (G_A_UP | G_A_LO), tb = P.flags & (G_B_UP | G_B_LO);
+      w.of.resize((size_t)tm * tn);
+      for (int j = 0, l = 0; j < tn; ++j)
+        for (int i = 0; i < tm; ++i, ++l) {
+          if (!tb && j > 0 && j + 1 < tn) w.of[l] = w.of[i];
+          else if (!ta && i > 0 && i + 1 < tm) w.of[l] = w.of[(size_t)j * tm];
+          else {
+            w.of[l] = (int)w.work.size();
+            w.work.push_back((float)tile_work(P, mode, BM, BN, i * BM, j * BN));
+            rank[w.work.back()] = 0;
+          }
+        }
     }
     if (rank.size() < 2) return;
     int nr = 0;
     for (auto& r : rank) r.second = nr++;
-    for (auto& sh : shapes)
-      for (int& w : sh.second) {
-        float k;
-        std::memcpy(&k, &w, sizeof(k));
-        w = rank[k];
-      }
+    std::vector<int> rk;
+    for (auto& sh : shapes) {
+      rk.clear();
+      for (float k : sh.second.work) rk.push_back(rank[k]);
+      for (int& w : sh.second.of) w = rk[w];
+    }
     std::vector<int> of(nwg);
     const std::vector<int>* w = nullptr;
     std::array<int, 4> last{};
     for (size_t q = (size_t)off; q < gemm.size(); ++q) {
       const GemmProb& P = gemm[q];
       const std::array<int, 4> key{P.M, P.N, P.K, P.flags};
-      if (!w || key != last) w = &shapes[key];
+      if (!w || key != last) w = &shapes[key].of;
       last = key;
       std::copy(w->begin(), w->end(), of.begin() + P.tile0);
     }
