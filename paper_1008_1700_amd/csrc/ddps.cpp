@@ -1518,9 +1518,8 @@ int block_solves(ddps_ctx* h, int tk) {
   hipEvent_t a;
   h->tim_begin(tk, a);
   if (h->d_ipack)
-    ilu_solve_packed(h->p, h->ilu_nmax, h->n, h->ilu_wmax, h->d_iblk, h->d_lrows, h->d_lptr, h->d_lq, h->d_urows,
-                     h->d_uptr, h->d_uq, h->d_col, h->d_fv, ilu_packed(h->d_ipack, h->n), h->d_ypad, h->Np, R,
-                     h->stream);
+    ilu_solve_packed(h->p, h->ilu_nmax, h->n, h->ilu_wmax, h->d_iblk, h->d_lptr, h->d_lq, h->d_uptr, h->d_uq, h->d_col,
+                     h->d_fv, ilu_packed(h->d_ipack, h->n), h->d_ypad, h->Np, R, h->stream);
   else
     ilu_solve(h->p, h->d_iblk, h->d_lrows, h->d_lptr, h->d_lq, h->d_urows, h->d_uptr, h->d_uq, h->d_col, h->d_fv,
               h->d_ypad, h->Np, R, h->d_vpad, h->stream);

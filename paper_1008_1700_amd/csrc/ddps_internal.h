@@ -150,9 +150,9 @@ IluPacked ilu_packed(void* buf, int64_t n_all);
 bool ilu_packs(int64_t nmax);
 void ilu_pack(int p, int64_t nmax, int64_t n_all, const IluBlock* blocks, const int32_t* lrows, const void* lq,
               const int32_t* urows, const void* uq, const int32_t* col, const double* fv, IluPacked P, hipStream_t s);
-void ilu_solve_packed(int p, int64_t nmax, int64_t n_all, int wmax, const IluBlock* blocks, const int32_t* lrows,
-                      const int64_t* lptr, const void* lq, const int32_t* urows, const int64_t* uptr, const void* uq,
-                      const int32_t* col, const double* fv, IluPacked P, double* y, int64_t ldy, int R, hipStream_t s);
+void ilu_solve_packed(int p, int64_t nmax, int64_t n_all, int wmax, const IluBlock* blocks, const int64_t* lptr,
+                      const void* lq, const int64_t* uptr, const void* uq, const int32_t* col, const double* fv,
+                      IluPacked P, double* y, int64_t ldy, int R, hipStream_t s);
 
 // ---------------------------------------------------------------- Krylov state
 constexpr int kMaxRhs = 8;

@@ -419,8 +419,10 @@ __global__ __launch_bounds__(kSolveThreads) void k_ilu_solve(const IluBlock* __r
 //        entry count, 16 bits each
 //   val: two entries at slot j and two at slot n_all + j, then (backward) the
 //        pivots
-// Rows beyond the first NT of a level and entries beyond the fourth of a row
-// are read in place.  Every row's sum is taken in the order of k_ilu_solve, so
+// Rows beyond the first NT of a level are loaded when they are due (from the CSR
+// positions two loads more, which made levels of 2000 to 5000 rows slower than
+// k_ilu_solve for one column: 93 and 88 us a solve, from here 79); entries beyond the
+// fourth of a row are read in place.  Every row's sum is taken in the order of k_ilu_solve, so
 // that both give the same bits.
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 typedef double f64x2_t __attribute__((ext_vector_type(2)));
@@ -458,9 +460,9 @@ __global__ __launch_bounds__(kIluThreads) void k_ilu_pack(const IluBlock* __rest
 
 template <bool UP, int NT>
 __device__ __forceinline__ void ilu_sweep(double* Y, int64_t s, int n, int64_t n_all, int64_t num,
-                                          const int64_t* __restrict__ ptr, const int32_t* __restrict__ rows,
-                                          const longlong2* __restrict__ rq, const int32_t* __restrict__ col,
-                                          const double* __restrict__ fv, const u32x4_t* __restrict__ pat,
+                                          const int64_t* __restrict__ ptr, const longlong2* __restrict__ rq,
+                                          const int32_t* __restrict__ col, const double* __restrict__ fv,
+                                          const u32x4_t* __restrict__ pat,
                                           const f64x2_t* __restrict__ val, const double* __restrict__ piv) {
   constexpr int D = 8;   // levels between loads and use
   struct Row {
@@ -469,7 +471,6 @@ __device__ __forceinline__ void ilu_sweep(double* Y, int64_t s, int n, int64_t n
     double piv;
   };
   const int tid = threadIdx.x, lane = tid & 63;
-  rows += s;
   rq += s;
   pat += s;
   val += s;
@@ -482,40 +483,38 @@ __device__ __forceinline__ void ilu_sweep(double* Y, int64_t s, int n, int64_t n
     const int a = __builtin_amdgcn_readlane(cur, k & 63), b = __builtin_amdgcn_readlane(nxt, k & 63);
     return (k < 64 ? a : b) - (int)s;
   };
-  auto fetch = [&](Row& F, int k) __attribute__((always_inline)) {
-    const int j = min(at(k) + tid, n - 1);
+  auto load = [&](Row& F, int j) __attribute__((always_inline)) {
     F.p = pat[j];
     F.v[0] = val[j];
     F.v[1] = val[n_all + j];
     if (UP) F.piv = piv[j];
   };
-  auto in_place = [&](double acc, int64_t q0, int64_t q1) __attribute__((always_inline)) {
+  auto fetch = [&](Row& F, int k) __attribute__((always_inline)) { load(F, min(at(k) + tid, n - 1)); };
+  auto solve = [&](const Row& F, int j) __attribute__((always_inline)) {
+    const int y = F.p.z & 0xffff, cnt = F.p.z >> 16;
+    double acc = Y[y];
+    const double x0 = Y[F.p.x & 0xffff], x1 = Y[F.p.x >> 16], x2 = Y[F.p.y & 0xffff], x3 = Y[F.p.y >> 16];
+    acc -= F.v[0].x * x0;
+    acc -= F.v[0].y * x1;
+    acc -= F.v[1].x * x2;
+    acc -= F.v[1].y * x3;
+    if (cnt > 4) {
+      const longlong2 q = rq[j];
 #pragma unroll 1
-    for (int64_t q = q0; q < q1; ++q) acc -= fv[q] * Y[col[q] - s];
-    return acc;
+      for (int64_t i = q.x + 4; i < q.y; ++i) acc -= fv[i] * Y[col[i] - s];
+    }
+    Y[y] = UP ? acc / F.piv : acc;
   };
   auto compute = [&](const Row& F, int k) __attribute__((always_inline)) {
     const int e = at(k + 1);
     int j = at(k) + tid;
     if (j < e) {
-      const int y = F.p.z & 0xffff, cnt = F.p.z >> 16;
-      double acc = Y[y];
-      const double x0 = Y[F.p.x & 0xffff], x1 = Y[F.p.x >> 16], x2 = Y[F.p.y & 0xffff], x3 = Y[F.p.y >> 16];
-      acc -= F.v[0].x * x0;
-      acc -= F.v[0].y * x1;
-      acc -= F.v[1].x * x2;
-      acc -= F.v[1].y * x3;
-      if (cnt > 4) {
-        const longlong2 q = rq[j];
-        acc = in_place(acc, q.x + 4, q.y);
-      }
-      Y[y] = UP ? acc / F.piv : acc;
+      solve(F, j);
 #pragma unroll 1
       for (j += NT; j < e; j += NT) {
-        const longlong2 q = rq[j];
-        const int yj = rows[j] - (int)s;
-        const double a = in_place(Y[yj], q.x, q.y);
-        Y[yj] = UP ? a / fv[q.x - 1] : a;
+        Row G;
+        load(G, j);
+        solve(G, j);
       }
     }
   };
@@ -543,10 +542,8 @@ __device__ __forceinline__ void ilu_sweep(double* Y, int64_t s, int n, int64_t n
 
 template <int NT>
 __global__ __launch_bounds__(NT) void k_ilu_solve_lds(const IluBlock* __restrict__ blocks, int p, int64_t n_all,
-                                                      const int32_t* __restrict__ lrows,
                                                       const int64_t* __restrict__ lptr,
                                                       const longlong2* __restrict__ lq,
-                                                      const int32_t* __restrict__ urows,
                                                       const int64_t* __restrict__ uptr,
                                                       const longlong2* __restrict__ uq,
                                                       const int32_t* __restrict__ col,
@@ -559,9 +556,9 @@ __global__ __launch_bounds__(NT) void k_ilu_solve_lds(const IluBlock* __restrict
   for (int r = threadIdx.x; r < n; r += NT) Y[r] = yc[r];
   if (threadIdx.x == 0) Y[n] = 0.0;
   __syncthreads();
-  ilu_sweep<false, NT>(Y, B.s, n, n_all, B.lnum, lptr + B.lbeg, lrows, lq, col, fv, (const u32x4_t*)P.lpat,
+  ilu_sweep<false, NT>(Y, B.s, n, n_all, B.lnum, lptr + B.lbeg, lq, col, fv, (const u32x4_t*)P.lpat,
                        (const f64x2_t*)P.lval, P.piv);
-  ilu_sweep<true, NT>(Y, B.s, n, n_all, B.unum, uptr + B.ubeg, urows, uq, col, fv, (const u32x4_t*)P.upat,
+  ilu_sweep<true, NT>(Y, B.s, n, n_all, B.unum, uptr + B.ubeg, uq, col, fv, (const u32x4_t*)P.upat,
                       (const f64x2_t*)P.uval, P.piv);
   __syncthreads();
   for (int r = threadIdx.x; r < n; r += NT) yc[r] = Y[r];
@@ -612,14 +609,13 @@ void ilu_pack(int p, int64_t nmax, int64_t n_all, const IluBlock* blocks, const 
                      (const longlong2*)uq, col, fv, P);
 }
 
-void ilu_solve_packed(int p, int64_t nmax, int64_t n_all, int wmax, const IluBlock* blocks, const int32_t* lrows,
-                      const int64_t* lptr, const void* lq, const int32_t* urows, const int64_t* uptr, const void* uq,
-                      const int32_t* col, const double* fv, IluPacked P, double* y, int64_t ldy, int R,
-                      hipStream_t s) {
+void ilu_solve_packed(int p, int64_t nmax, int64_t n_all, int wmax, const IluBlock* blocks, const int64_t* lptr,
+                      const void* lq, const int64_t* uptr, const void* uq, const int32_t* col, const double* fv,
+                      IluPacked P, double* y, int64_t ldy, int R, hipStream_t s) {
   const size_t lds = (size_t)(nmax + 1) * sizeof(double);
 #define DDPS_ILU_LDS(NT)                                                                                              \
-  hipLaunchKernelGGL(k_ilu_solve_lds<NT>, dim3((unsigned)(p * R)), dim3(NT), lds, s, blocks, p, n_all, lrows, lptr, \
-                     (const longlong2*)lq, urows, uptr, (const longlong2*)uq, col, fv, P, y, ldy)
+  hipLaunchKernelGGL(k_ilu_solve_lds<NT>, dim3((unsigned)(p * R)), dim3(NT), lds, s, blocks, p, n_all, lptr,        \
+                     (const longlong2*)lq, uptr, (const longlong2*)uq, col, fv, P, y, ldy)
   if (wmax <= 64) DDPS_ILU_LDS(64);
   else if (wmax <= 256) DDPS_ILU_LDS(256);
   else DDPS_ILU_LDS(512);
