@@ -38,10 +38,12 @@ typedef u16x8 __attribute__((aligned(4))) u16x8_a4;
 
 // 8 elements p[0..8) (contiguous), the first `valid` of them in range
 __device__ __forceinline__ u16x8 load_seg(const unsigned short* __restrict__ p, int valid, bool wide) {
-  if (wide && valid >= 8) return *(const u16x8_a4*)p;
-  u16x8 r;
+  u16x8 r = {};
+  if (wide && valid >= 8) r = *(const u16x8_a4*)p;
+  else if (!wide || valid > 0) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) r[e] = e < valid ? p[e] : (unsigned short)0;
+    for (int e = 0; e < 8; ++e) r[e] = e < valid ? p[e] : (unsigned short)0;
+  }
   return r;
 }
 
