@@ -13,11 +13,13 @@
 
 namespace ddps {
 
-// Problem of workgroup wg of nwg.  Most launches hold problems of equal size,
-// where the proportional guess is right and the dependent loads of a search
-// (a microsecond or more of a short kernel) are saved.
+// Problem of workgroup wg of nwg (an argument: gridDim would bring 256 bytes of
+// hidden ones with each launch, 0.5 to 1 us of host time in a chain of short
+// ones).  Most launches hold problems of equal size, where the proportional guess
+// is right and the dependent loads of a search (a microsecond or more of a short
+// kernel) are saved.
 __device__ __forceinline__ int find_gemv(const GemvProb* __restrict__ probs, int nprob, int wg, int nwg) {
-  const int gs = (int)((int64_t)wg * nprob / nwg);
+  const int gs = min((int)(((float)wg + 0.5f) * ((float)nprob * __builtin_amdgcn_rcpf((float)nwg))), nprob - 1);
   const int b0 = probs[gs].wg0, b1 = gs + 1 < nprob ? probs[gs + 1].wg0 : nwg;
   if (b0 <= wg && wg < b1) return gs;
   int lo = 0, hi = nprob - 1;
@@ -29,7 +31,7 @@ __device__ __forceinline__ int find_gemv(const GemvProb* __restrict__ probs, int
 }
 
 template <typename T, int R>
-__global__ __launch_bounds__(256) void k_gemv(const GemvProb* __restrict__ probs, int nprob,
+__global__ __launch_bounds__(256) void k_gemv(const GemvProb* __restrict__ probs, int nprob, int nwg,
                                               int64_t ldx, int64_t ldy,
                                               const double* __restrict__ dotv,
                                               double* __restrict__ partial,
@@ -42,7 +44,7 @@ __global__ __launch_bounds__(256) void k_gemv(const GemvProb* __restrict__ probs
     if (all) return;
   }
   const int wg = blockIdx.x;
-  const GemvProb& Pg = probs[find_gemv(probs, nprob, wg, gridDim.x)];
+  const GemvProb& Pg = probs[find_gemv(probs, nprob, wg, nwg)];
   const GemvProb P = Pg;
   const int r0 = (wg - P.wg0) * 64;
   int cb = P.cb, ce = P.ce;
@@ -131,7 +133,7 @@ __global__ __launch_bounds__(256) void k_gemv(const GemvProb* __restrict__ probs
 // flight per lane.
 // ------------------------------------------------------------------------
 template <typename T, int R, int U>
-__global__ __launch_bounds__(256) void k_gemv_w(const GemvProb* __restrict__ probs, int nprob,
+__global__ __launch_bounds__(256) void k_gemv_w(const GemvProb* __restrict__ probs, int nprob, int nwg,
                                                 int64_t ldx, int64_t ldy,
                                                 const double* __restrict__ dotv,
                                                 double* __restrict__ partial,
@@ -148,7 +150,7 @@ __global__ __launch_bounds__(256) void k_gemv_w(const GemvProb* __restrict__ pro
     if (all) return;
   }
   const int wg = blockIdx.x;
-  const GemvProb& Pg = probs[find_gemv(probs, nprob, wg, gridDim.x)];
+  const GemvProb& Pg = probs[find_gemv(probs, nprob, wg, nwg)];
   const GemvProb P = Pg;
   const int r0 = (wg - P.wg0) * 64;
   int cb = P.cb, ce = P.ce;
@@ -267,7 +269,7 @@ __global__ __launch_bounds__(256) void k_gemv_w(const GemvProb* __restrict__ pro
 // and 7 us with sixteen waves.
 // ------------------------------------------------------------------------
 template <typename T, int R, int NW, bool SHORT>
-__global__ __launch_bounds__(64 * NW) void k_gemv_n(const GemvProb* __restrict__ probs, int nprob,
+__global__ __launch_bounds__(64 * NW) void k_gemv_n(const GemvProb* __restrict__ probs, int nprob, int nwg,
                                                     int64_t ldx, int64_t ldy,
                                                     const double* __restrict__ dotv,
                                                     double* __restrict__ partial,
@@ -288,7 +290,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemv_n(const GemvProb* __restrict__
     if (all) return;
   }
   const int wg = blockIdx.x;
-  const GemvProb P = probs[find_gemv(probs, nprob, wg, gridDim.x)];
+  const GemvProb P = probs[find_gemv(probs, nprob, wg, nwg)];
   const int r0 = (wg - P.wg0) * 64;
   int cb = P.cb, ce = P.ce;
   if (P.tri == 1) ce = min(ce, r0 + 64);
@@ -443,7 +445,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemv_n(const GemvProb* __restrict__
 // every wave, six workgroups of 128-entry rows took 8.7 us, now 4.2 us.
 // ------------------------------------------------------------------------
 template <typename T, int R, int RPW, bool STEP>
-__global__ __launch_bounds__(256) void k_tipmv(const GemvProb* __restrict__ probs, int nprob,
+__global__ __launch_bounds__(256) void k_tipmv(const GemvProb* __restrict__ probs, int nprob, int nwg,
                                                int64_t ldx, int64_t ldy,
                                                const double* __restrict__ dotv,
                                                double* __restrict__ partial,
@@ -477,7 +479,7 @@ __global__ __launch_bounds__(256) void k_tipmv(const GemvProb* __restrict__ prob
     if (!any) return;   // no column goes on: nothing reads s, the product or their sums
   }
   const int wg = blockIdx.x / SB;
-  const GemvProb& P = probs[find_gemv(probs, nprob, wg, gridDim.x / SB)];
+  const GemvProb& P = probs[find_gemv(probs, nprob, wg, nwg)];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int fl = P.flags;
@@ -608,7 +610,7 @@ __global__ __launch_bounds__(256) void k_tipmv(const GemvProb* __restrict__ prob
 // reduces its part of eight rows at a time; the four parts of a row are added
 // in LDS.  1.06 GB of f32 tips take 177 us (6.0 TB/s; by rows 189 us).
 template <typename T, int R, int NS>
-__global__ __launch_bounds__(256) void k_tipmv_c(const GemvProb* __restrict__ probs, int nprob,
+__global__ __launch_bounds__(256) void k_tipmv_c(const GemvProb* __restrict__ probs, int nprob, int nwg,
                                                  int64_t ldx, int64_t ldy,
                                                  const double* __restrict__ dotv,
                                                  double* __restrict__ partial,
@@ -624,7 +626,7 @@ __global__ __launch_bounds__(256) void k_tipmv_c(const GemvProb* __restrict__ pr
     if (all) return;
   }
   const int wg = blockIdx.x;
-  const GemvProb& P = probs[find_gemv(probs, nprob, wg, gridDim.x)];
+  const GemvProb& P = probs[find_gemv(probs, nprob, wg, nwg)];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int cb = P.cb, split = P.split, nc = P.ce - cb;
@@ -794,13 +796,13 @@ void launch_tipmv(int dtype, int nrhs, int t, const GemvProb* probs, int nprob, 
   // 103 us; 640 workgroups, one round of three: 57 instead of 68 us).
   const size_t two = nwg > 768 && nwg <= 1024 ? 56 * 1024 : 0;
 #define DDPS_TIPMV(L, ...) \
-  hipLaunchKernelGGL((__VA_ARGS__), dim3(nwg), dim3(256), L, s, probs, nprob, ldx, ldy, dotv, partial, stop)
+  hipLaunchKernelGGL((__VA_ARGS__), dim3(nwg), dim3(256), L, s, probs, nprob, nwg, ldx, ldy, dotv, partial, stop)
 #define DDPS_TIPMV_S(T, R, RPW)                                                                                     \
   if (step)                                                                                                         \
-    hipLaunchKernelGGL((k_tipmv<T, R, RPW, true>), dim3(nwg * sb), dim3(256), lds, s, probs, nprob, ldx, ldy, dotv, \
+    hipLaunchKernelGGL((k_tipmv<T, R, RPW, true>), dim3(nwg * sb), dim3(256), lds, s, probs, nprob, nwg, ldx, ldy, dotv, \
                        partial, stop, *step);                                                                       \
   else                                                                                                              \
-    hipLaunchKernelGGL((k_tipmv<T, R, RPW, false>), dim3(nwg * sb), dim3(256), lds, s, probs, nprob, ldx, ldy,      \
+    hipLaunchKernelGGL((k_tipmv<T, R, RPW, false>), dim3(nwg * sb), dim3(256), lds, s, probs, nprob, nwg, ldx, ldy,      \
                        dotv, partial, stop, TipStep{})
 #define DDPS_TIPMV_C(T, R)                                            \
   switch (ns) {                                                       \
@@ -857,7 +859,7 @@ void pack_tips(int dtype, int p, int t, const BlockInfo* blocks, const void* spi
 // 474 us (5.4 TB/s).
 // ------------------------------------------------------------------------
 template <int R>
-__global__ __launch_bounds__(256) void k_gemv_mf32(const GemvProb* __restrict__ probs, int nprob,
+__global__ __launch_bounds__(256) void k_gemv_mf32(const GemvProb* __restrict__ probs, int nprob, int nwg,
                                                    int64_t ldx, int64_t ldy,
                                                    const double* __restrict__ dotv,
                                                    double* __restrict__ partial,
@@ -874,7 +876,7 @@ __global__ __launch_bounds__(256) void k_gemv_mf32(const GemvProb* __restrict__ 
     if (all) return;
   }
   const int wg = blockIdx.x;
-  const GemvProb P = probs[find_gemv(probs, nprob, wg, gridDim.x)];
+  const GemvProb P = probs[find_gemv(probs, nprob, wg, nwg)];
   const int r0 = (wg - P.wg0) * 64;
   int cb = P.cb, ce = P.ce;
   if (P.tri == 1) ce = min(ce, r0 + 64);
@@ -1001,7 +1003,7 @@ static void gemv_dispatch(int nrhs, bool wide, int cols, const GemvProb* probs, 
                           int64_t ldy, const double* dotv, double* partial, const int32_t* stop,
                           hipStream_t s) {
 #define DDPS_GEMV(NT, ...) \
-  hipLaunchKernelGGL((__VA_ARGS__), dim3(nwg), dim3(NT), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop)
+  hipLaunchKernelGGL((__VA_ARGS__), dim3(nwg), dim3(NT), 0, s, probs, nprob, nwg, ldx, ldy, dotv, partial, stop)
 #define DDPS_GEMV_W(R)                                                                      \
   if (gemv_rounds<k_gemv_w<T, R, 4>>(nwg) < gemv_rounds<k_gemv_w<T, R, 8>>(nwg))            \
     DDPS_GEMV(256, k_gemv_w<T, R, 4>);                                                      \
@@ -1053,9 +1055,9 @@ void launch_gemv(int dtype, int nrhs, int form, int cols, const GemvProb* probs,
   if (nwg <= 0 || nprob <= 0) return;
   if (dtype == 1 && form == 2 && nrhs >= 4) {
     if (nrhs == 4)
-      hipLaunchKernelGGL(k_gemv_mf32<4>, dim3(nwg), dim3(256), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop);
+      hipLaunchKernelGGL(k_gemv_mf32<4>, dim3(nwg), dim3(256), 0, s, probs, nprob, nwg, ldx, ldy, dotv, partial, stop);
     else
-      hipLaunchKernelGGL(k_gemv_mf32<8>, dim3(nwg), dim3(256), 0, s, probs, nprob, ldx, ldy, dotv, partial, stop);
+      hipLaunchKernelGGL(k_gemv_mf32<8>, dim3(nwg), dim3(256), 0, s, probs, nprob, nwg, ldx, ldy, dotv, partial, stop);
     return;
   }
   if (dtype == 0) gemv_dispatch<double>(nrhs, form >= 1, cols, probs, nprob, nwg, ldx, ldy, dotv, partial, stop, s);

@@ -41,10 +41,10 @@ __device__ __forceinline__ void block_sum(double (&v)[R][2], double (*sh)[R][2])
 // Fixed-order reduction of partials laid out [w][R][2] into out[R][2]: one
 // workgroup per column; thread i adds w = i, i + 256, ... in order, then a
 // fixed tree.  992 partials of 8 columns: 4.4 us, in one workgroup 6.1 us.
-__global__ __launch_bounds__(256) void k_reduce2(int W, const double* __restrict__ part, double* __restrict__ out,
-                                                 const int32_t* __restrict__ stop) {
+__global__ __launch_bounds__(256) void k_reduce2(int W, int R, const double* __restrict__ part,
+                                                 double* __restrict__ out, const int32_t* __restrict__ stop) {
   __shared__ double sh[4][1][2];
-  const int j = blockIdx.x, R = gridDim.x;
+  const int j = blockIdx.x;
   if (stop) {
     bool all = true;
     for (int q = 0; q < R; ++q) all &= stop[q] != KS_RUNNING;
@@ -613,10 +613,10 @@ void reduce2(int R, int W, const double* part, double* out, const int32_t* stop,
     const int per = (W + kReduceGroups - 1) / kReduceGroups;
     const int G = (W + per - 1) / per;
     DDPS_R_DISPATCH(R, hipLaunchKernelGGL(k_reduce2_part<RR>, dim3(G), dim3(256), 0, s, W, per, part, scratch, stop));
-    hipLaunchKernelGGL(k_reduce2, dim3(R), dim3(256), 0, s, G, scratch, out, stop);
+    hipLaunchKernelGGL(k_reduce2, dim3(R), dim3(256), 0, s, G, R, scratch, out, stop);
     return;
   }
-  hipLaunchKernelGGL(k_reduce2, dim3(R), dim3(256), 0, s, W, part, out, stop);
+  hipLaunchKernelGGL(k_reduce2, dim3(R), dim3(256), 0, s, W, R, part, out, stop);
 }
 void bicg_init(int R, int64_t m, int use_guess, const double* gh, double* x, const double* v, double* r,
                double* rt, double* p, double* part, int W, hipStream_t s) {
