@@ -13,6 +13,9 @@
 
 namespace ddps {
 
+template <typename T>
+using gptr = const T __attribute__((address_space(1)))*;
+
 // Problem of workgroup wg of nwg (an argument: gridDim would bring 256 bytes of
 // hidden ones with each launch, 0.5 to 1 us of host time in a chain of short
 // ones).  Most launches hold problems of equal size, where the proportional guess
@@ -255,12 +258,12 @@ __global__ __launch_bounds__(256) void k_gemv_w(const GemvProb* __restrict__ pro
 
 // ------------------------------------------------------------------------
 // One or two right-hand sides, 16-byte aligned problems: the column range's
-// vector entries are staged in LDS once per workgroup (CH columns at a time), and the NW waves take
-// interleaved groups of columns, U loads of 1 KiB each in flight per wave (a
-// lane reads VEC consecutive rows of one column, a wave load 64 rows of VEC
-// columns).  SHORT: ranges of at most U loads per wave, without the stage in LDS:
-// a lane loads its columns' vector entries beside them.  Epilogue, flags and
-// partial sums as in k_gemv.
+// vector entries are staged in LDS once per workgroup (CH columns at a time), and
+// the NW waves take interleaved groups of columns, U loads of 1 KiB each in flight
+// per wave (a lane reads VEC consecutive rows of one column, a wave load 64 rows
+// of VEC columns).  SHORT: ranges of at most U loads per wave, without the stage:
+// a lane loads the vector entries of its columns itself, and the masks are applied
+// to the batch at once.  Epilogue, flags and partial sums as in k_gemv.
 //
 // Bound: HBM for long launches; the sweeps are chains of short launches, so
 // latency: with four loads in flight on four waves and the vector entries
@@ -268,7 +271,7 @@ __global__ __launch_bounds__(256) void k_gemv_w(const GemvProb* __restrict__ pro
 // blocks) and a 512-wide f64 one of 16 blocks 20.1 us; this form takes 31 us,
 // and 7 us with sixteen waves.
 // ------------------------------------------------------------------------
-template <typename T, int R, int NW, bool SHORT>
+template <typename T, int R, int NW, int U, bool SHORT>
 __global__ __launch_bounds__(64 * NW) void k_gemv_n(const GemvProb* __restrict__ probs, int nprob, int nwg,
                                                     int64_t ldx, int64_t ldy,
                                                     const double* __restrict__ dotv,
@@ -276,7 +279,6 @@ __global__ __launch_bounds__(64 * NW) void k_gemv_n(const GemvProb* __restrict__
                                                     const int32_t* __restrict__ stop) {
   constexpr int VEC = 16 / sizeof(T);   // rows per lane
   constexpr int LPC = 64 / VEC;         // lanes per column
-  constexpr int U = 8;                  // loads in flight per lane
   constexpr int CH = SHORT ? U * NW * VEC : 2048 / R;   // columns at a time
   typedef T vec_t __attribute__((ext_vector_type(VEC)));
   // the vector entries, then the waves' sums
@@ -302,7 +304,9 @@ __global__ __launch_bounds__(64 * NW) void k_gemv_n(const GemvProb* __restrict__
   const int fl = P.flags;
   const bool mlu = fl & V_A_MLU, mup = fl & V_A_MUP, mlo = fl & V_A_MLO;
   const bool masked = mlu || mup || mlo;
-  const T* __restrict__ A = (const T*)P.A + r0 + rl;
+  // global pointers: a generic one would be loaded from through the LDS path too
+  gptr<T> A = (gptr<T>)P.A + r0 + rl;
+  gptr<double> x1 = (gptr<double>)P.x1, x2 = (gptr<double>)P.x2;
   const int64_t lda = P.lda;
   const int split = P.split;
   double acc[VEC][R];
@@ -311,46 +315,61 @@ __global__ __launch_bounds__(64 * NW) void k_gemv_n(const GemvProb* __restrict__
 #pragma unroll
     for (int j = 0; j < R; ++j) acc[e][j] = 0.0;
   auto xval = [&](int cc, int j) __attribute__((always_inline)) {
-    return cc < split ? P.x1[cc + j * ldx] : P.x2[(cc - split) + j * ldx];
+    gptr<double> xp = cc < split ? x1 + cc : x2 + (cc - split);
+    return xp[j * ldx];
   };
   auto fetch = [&](vec_t (&a)[U], int c, int c1) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int cc = c + u * NW * VEC;
-      a[u] = cc < c1 ? *(const vec_t*)(A + (int64_t)cc * lda) : vec_t{};
+      a[u] = cc < c1 ? *(gptr<vec_t>)(A + (int64_t)cc * lda) : vec_t{};
     }
   };
   // the packed-triangle masks change only the columns [r0, r0 + 64) of a slab
-  auto fix = [&](vec_t& a, int cc) __attribute__((always_inline)) {
-    if (masked && cc >= r0 && cc < r0 + 64) {
+  auto mask = [&](vec_t& a, int cc) __attribute__((always_inline)) {
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        const int rr = r0 + rl + e;
-        if (mlu) a[e] = rr > cc ? a[e] : (rr == cc ? T(1) : T(0));
-        if (mup) a[e] = rr <= cc ? a[e] : T(0);
-        if (mlo) a[e] = rr >= cc ? a[e] : T(0);
-      }
+    for (int e = 0; e < VEC; ++e) {
+      const int rr = r0 + rl + e;
+      if (mlu) a[e] = rr > cc ? a[e] : (rr == cc ? T(1) : T(0));
+      if (mup) a[e] = rr <= cc ? a[e] : T(0);
+      if (mlo) a[e] = rr >= cc ? a[e] : T(0);
     }
   };
   // wave g takes the column groups c0 + VEC (g + NW s), s = 0, 1, ...
   if constexpr (SHORT) {
-    vec_t a[U];
-    double xv[U][R];
-    const int c = cb + g * VEC + q;
-    fetch(a, c, ce);
+    // the ranges are multiples of 16, so whether a column group is inside is the
+    // same for the wave; a whole range goes without that test
+    const int c = cb + g * VEC;
+    auto batch = [&](auto all) __attribute__((always_inline)) {
+      vec_t a[U] = {};
+      double xv[U][R] = {};
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+      for (int u = 0; u < U; ++u) {
+        const int cu = c + u * NW * VEC;
+        if (!decltype(all)::value && cu >= ce) break;
+        a[u] = *(gptr<vec_t>)(A + (int64_t)(cu + q) * lda);
 #pragma unroll
-      for (int j = 0; j < R; ++j) xv[u][j] = c + u * NW * VEC < ce ? xval(c + u * NW * VEC, j) : 0.0;
+        for (int j = 0; j < R; ++j) xv[u][j] = xval(cu + q, j);
+      }
+      // the masks hold for every column of a clipped range: one test for the batch
+      auto select = [&](auto in) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (c + u * NW * VEC >= ce) continue;
-      fix(a[u], c + u * NW * VEC);
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int j = 0; j < R; ++j)
+          for (int e = 0; e < VEC; ++e) a[u][e] = in(a[u][e], r0 + rl + e, c + u * NW * VEC + q);
+      };
+      if (mlu) select([](T v, int r, int cc) { return r > cc ? v : (r == cc ? T(1) : T(0)); });
+      if (mup) select([](T v, int r, int cc) { return r <= cc ? v : T(0); });
+      if (mlo) select([](T v, int r, int cc) { return r >= cc ? v : T(0); });
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) acc[e][j] += (double)a[u][e] * xv[u][j];
-    }
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int j = 0; j < R; ++j)
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) acc[e][j] += (double)a[u][e] * xv[u][j];
+    };
+    if (ce - cb == CH) batch(std::true_type{});
+    else batch(std::false_type{});
   } else {
     for (int c0 = cb; c0 < ce; c0 += CH) {
       const int c1 = min(ce, c0 + CH);
@@ -367,7 +386,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemv_n(const GemvProb* __restrict__
         for (int u = 0; u < U; ++u) {
           const int cc = c + u * NW * VEC;
           if (cc >= c1) continue;
-          fix(a[u], cc);
+          if (masked && cc >= r0 && cc < r0 + 64) mask(a[u], cc);
 #pragma unroll
           for (int j = 0; j < R; ++j) {
             const double xv = xs[(cc - c0) * R + j];
@@ -1009,24 +1028,28 @@ static void gemv_dispatch(int nrhs, bool wide, int cols, const GemvProb* probs, 
     DDPS_GEMV(256, k_gemv_w<T, R, 4>);                                                      \
   else                                                                                      \
     DDPS_GEMV(256, k_gemv_w<T, R, 8>)
-#define DDPS_GEMV_N(NW, SHORT)                                        \
-  if (nrhs == 1) DDPS_GEMV(64 * NW, k_gemv_n<T, 1, NW, SHORT>);       \
-  else DDPS_GEMV(64 * NW, k_gemv_n<T, 2, NW, SHORT>)
+#define DDPS_GEMV_N(NW, U, SHORT)                                     \
+  if (nrhs == 1) DDPS_GEMV(64 * NW, k_gemv_n<T, 1, NW, U, SHORT>);    \
+  else DDPS_GEMV(64 * NW, k_gemv_n<T, 2, NW, U, SHORT>)
   if (wide && nrhs <= 2) {
-    // Ranges that four or eight waves load at once need no stage in LDS: f64
-    // triangles of 64 rows, 4 / 64 / 300 workgroups, us, 16 waves and stage 3.4 / 3.6
-    // / -, four waves and stage - / - / 3.6, without 2.8 / 2.9 / 3.3 (two columns, f32:
-    // 5.0 / 5.1 / 4.3 and 3.6 / 3.9 / 4.0); of 128 rows, eight waves, 64 / 1000
-    // workgroups 3.8 / 10.1 and 3.2 / 9.2, two columns 4.4 / 10.7 and 3.8 / 11.7.
+    // Ranges that four or eight waves load at once need no stage in LDS.  Chains of
+    // sweeps, us per launch, with the stage / without: four waves, f64 64 columns, 4 /
+    // 300 workgroups 3.7 / 2.7 and 5.5 / 4.3 (two right-hand sides 4.3 / 3.0 and 6.1 /
+    // 4.9), f32 128 columns, 64 / 1000 workgroups 4.2 / 3.3 and 9.4 / 8.4 (5.5 / 4.0 and
+    // 10.5 / 10.8).  Eight waves: f64 128 columns, 256 / 500 / 1000 workgroups 5.8 /
+    // 5.0, 9.5 / 8.1, 14.3 / 13.8 (6.5 / 5.6, 10.1 / 10.4, 15.2 / 19.0), f32 256 columns,
+    // 240 / 500 / 1000 workgroups 5.6 / 4.7, 7.9 / 6.6, 12.1 / 12.4 (7.0 / 5.5, 8.9 /
+    // 9.6, 13.5 / 19.2).
     // Wider ones, one workgroup per CU or fewer: sixteen waves each, so that a
     // short launch has all its loads in flight at once; beyond, four fill the CUs with
     // less to add up.  Sixteen against four on f64 triangles of 512 rows: 128
     // workgroups 7.0 / 11.9, 512 workgroups 20.8 / 19.3 (f32 14.2 / 11.7).
     constexpr int once = 8 * 4 * 16 / (int)sizeof(T);   // columns that four waves load at once
-    if (cols <= once) { DDPS_GEMV_N(4, true); }
-    else if (cols <= 2 * once && nwg <= 512) { DDPS_GEMV_N(8, true); }
-    else if (nwg <= 256) { DDPS_GEMV_N(16, false); }
-    else { DDPS_GEMV_N(4, false); }
+    if (cols <= 64) { DDPS_GEMV_N(4, 512 / once, true); }
+    else if (cols <= once) { DDPS_GEMV_N(4, 8, true); }
+    else if (cols <= 2 * once && nwg <= (nrhs == 1 ? 512 : 256)) { DDPS_GEMV_N(8, 8, true); }
+    else if (nwg <= 256) { DDPS_GEMV_N(16, 8, false); }
+    else { DDPS_GEMV_N(4, 8, false); }
     return;
   }
   if (wide) {

@@ -9,7 +9,7 @@ from tests import test_gpu_gemv_forms as forms
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("p,t", [(3, 128), (5, 256), (4, 320), (257, 128), (150, 256)])
+@pytest.mark.parametrize("p,t", [(3, 128), (5, 256), (4, 320), (140, 128), (257, 128), (150, 256)])
 @pytest.mark.parametrize("dtype,k", [("f64", 1), ("f64", 2), ("f32", 1), ("f32", 2)])
 def test_short_ranges(p, t, dtype, k):
     forms.test_products_at_dispatch_edges(p, t, dtype, k)
