@@ -337,8 +337,8 @@ __global__ __launch_bounds__(64 * NW) void k_gemv_n(const GemvProb* __restrict__
   };
   // wave g takes the column groups c0 + VEC (g + NW s), s = 0, 1, ...
   if constexpr (SHORT) {
-    // the ranges are multiples of 16, so whether a column group is inside is the
-    // same for the wave; a whole range goes without that test
+    // a range may begin and end at any column (the parts of a direct reduced solve
+    // do); one of CH columns goes without the tests
     const int c = cb + g * VEC;
     auto batch = [&](auto all) __attribute__((always_inline)) {
       vec_t a[U] = {};
@@ -346,7 +346,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemv_n(const GemvProb* __restrict__
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int cu = c + u * NW * VEC;
-        if (!decltype(all)::value && cu >= ce) break;
+        if (!decltype(all)::value && cu + q >= ce) continue;
         a[u] = *(gptr<vec_t>)(A + (int64_t)(cu + q) * lda);
 #pragma unroll
         for (int j = 0; j < R; ++j) xv[u][j] = xval(cu + q, j);
