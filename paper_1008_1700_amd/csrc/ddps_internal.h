@@ -172,8 +172,6 @@ enum KStatus : int32_t {
 struct KState {
   double ref[kMaxRhs];       // ||g^||_2 (1 if zero)
   double rho[2][kMaxRhs];    // rho of iteration it in slot it & 1
-  double alpha[kMaxRhs];
-  double omega[kMaxRhs];
   double res[kMaxRhs];       // last relative residual
   int32_t status[2][kMaxRhs];
   int32_t iters2[kMaxRhs];   // iterations counted in half steps

@@ -18,13 +18,12 @@
 // one column of D, and the stores to the column-major D are 64-128-byte
 // segments.
 #include "ddps_internal.h"
+#include "mma_device.h"
 
 #include <type_traits>
 
 namespace ddps {
 
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
@@ -78,24 +77,6 @@ __device__ __forceinline__ bool store_ok(int fl, int r, int c) {
   return true;
 }
 
-template <typename T> struct Mma;
-// Accumulator layouts (lane l, register v) -> row of the 16 x 16 result:
-// f32 16x16x4: 4 (l >> 4) + v;   f64 16x16x4: (l >> 4) + 4 v  (measured).
-template <> struct Mma<double> {
-  using acc = f64x4;
-  static __device__ __forceinline__ int row(int lane, int v) { return (lane >> 4) + 4 * v; }
-  static __device__ __forceinline__ acc run(double a, double b, acc c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-};
-template <> struct Mma<float> {
-  using acc = f32x4;
-  static __device__ __forceinline__ int row(int lane, int v) { return 4 * (lane >> 4) + v; }
-  static __device__ __forceinline__ acc run(float a, float b, acc c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-};
-
 struct TileCoord {
   int I0, J0, kb, ke;
 };
@@ -119,14 +100,13 @@ __device__ __forceinline__ TileCoord tile_of(const GemmProb& P, int wg) {
 
 // ------------------------------------------------------------------------
 // f64 / f32 with element loads (any alignment): 256 threads = 4 waves in a
-// 2 x 2 arrangement, each wave a (BM/2) x (BN/2) sub-tile of 16 x 16 MFMA
-// blocks; K advances in chunks of 16 staged through LDS, with the next
+// 2 x 2 arrangement, each wave a 32 x 32 sub-tile of 16 x 16 MFMA blocks; K advances in chunks of 16 staged through LDS, with the next
 // chunk's global loads in flight while the current chunk is multiplied.
 // ------------------------------------------------------------------------
-template <typename T, int BM, int BN, int BK = 16, int OCC = 1>
-__global__ __launch_bounds__(256, OCC) void k_gemm_std(const GemmProb* __restrict__ probs, int nprob,
-                                                 const int32_t* __restrict__ order) {
-  constexpr int PADL = 4;
+template <typename T>
+__global__ __launch_bounds__(256, 2) void k_gemm_std(const GemmProb* __restrict__ probs, int nprob,
+                                                     const int32_t* __restrict__ order) {
+  constexpr int BM = 64, BN = 64, BK = 16, PADL = 4;
   constexpr int MB = BM / 32, NB = BN / 32;          // 16x16 blocks per wave
   constexpr int AE = BM * BK / 256, BE = BN * BK / 256;  // elements per thread
   __shared__ T As[2][BK][BM + PADL];
@@ -520,7 +500,7 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_bf16(const GemmProb* __re
 //
 // LDS, two stages of a 32-deep K chunk:
 //   A as [k][m] (m contiguous, as in global memory): one wave instruction
-//     fills 256 / BM rows of k; a fragment (8 consecutive k of one row) is
+//     fills 2 rows of k; a fragment (8 consecutive k of one row) is
 //     eight 4-byte reads.
 //   B as [n][k] (k contiguous): one wave instruction fills 8 columns; the
 //     eight 16-byte slots of column n hold k pieces slot ^ (n & 7), so that
@@ -556,23 +536,24 @@ __device__ __forceinline__ void split8(const float (&x)[8], bf16x8& h, bf16x8& l
   }
 }
 
+constexpr int kDlTile = 128, kDlBK = 32;
+constexpr int kDlInstr = kDlBK * kDlTile / 256 / 4;   // instructions per wave, operand and chunk
+
 // One K chunk of k_gemm_dl.  The LDS pointers are restrict: the compiler then
 // sees that the reads of the current stage (ca, cb) do not alias the DMA into
 // the next stage (na, nb), and does not make them wait for it.
-template <bool SPLIT, int BM, int BN, int NW>
+template <bool SPLIT>
 __device__ __forceinline__ void dl_chunk(const float* __restrict__ ca, const float* __restrict__ cb,
                                          float* __restrict__ na, float* __restrict__ nb,
                                          const char* __restrict__ ga, const char* __restrict__ gb,
-                                         const int64_t (&goff)[16], bool issue_next, int lane, int wm, int wn,
-                                         f32x16 (&acc)[BM / 64][BN / (16 * NW)]) {
-  constexpr int BK = 32;
-  constexpr int MB = BM / 64, NB = BN / (16 * NW);
-  constexpr int NA = BK * BM / 256 / NW, NBI = BN / 8 / NW;
+                                         const int64_t (&goff)[2 * kDlInstr], bool issue_next, int lane, int wm, int wn,
+                                         f32x16 (&acc)[2][2]) {
+  constexpr int BM = kDlTile, BN = kDlTile, BK = kDlBK, MB = 2, NB = 2, NA = kDlInstr, NBI = kDlInstr;
   auto read = [&](int ks, float (&xb)[NB][8], float (&xa)[MB][8]) __attribute__((always_inline)) {
     const int kk = ks * 16 + 8 * (lane >> 5);
 #pragma unroll
     for (int ni = 0; ni < NB; ++ni) {
-      const int n = wn * (2 * BN / NW) + ni * 32 + (lane & 31);
+      const int n = wn * (BN / 2) + ni * 32 + (lane & 31);
       const int s0 = (kk >> 2) ^ (n & 7), s1 = ((kk >> 2) + 1) ^ (n & 7);
       const f32x4 v0 = *(const f32x4*)&cb[n * BK + 4 * s0];
       const f32x4 v1 = *(const f32x4*)&cb[n * BK + 4 * s1];
@@ -631,17 +612,11 @@ __device__ __forceinline__ void dl_chunk(const float* __restrict__ ca, const flo
   }
 }
 
-template <bool SPLIT, int BM, int BN, int NW, int OCC>
-__global__ __launch_bounds__(64 * NW, OCC) void k_gemm_dl(const GemmProb* __restrict__ probs, int nprob,
-                                                 const int32_t* __restrict__ order) {
-  constexpr int BK = 32;
-  constexpr int MB = BM / 64, NB = BN / (16 * NW);
-  constexpr int NA = BK * BM / 256 / NW;   // A instructions per wave and chunk
-  constexpr int NBI = BN / 8 / NW;         // B instructions per wave and chunk
-  constexpr int KPI = BM >= 256 ? 1 : 256 / BM;   // k rows per A instruction
-  static_assert(BM <= 256 && NA >= 1 && NBI >= 1 && NA + NBI <= 16 && (BK * BM) % (256 * NW) == 0 &&
-                    BN % (8 * NW) == 0 && NB >= 1,
-                "chunk split");
+template <bool SPLIT>
+__global__ __launch_bounds__(256, 2) void k_gemm_dl(const GemmProb* __restrict__ probs, int nprob,
+                                                    const int32_t* __restrict__ order) {
+  constexpr int BM = kDlTile, BN = kDlTile, BK = kDlBK, MB = 2, NB = 2, NA = kDlInstr, NBI = kDlInstr;
+  constexpr int KPI = 256 / BM;   // k rows per A instruction
   __shared__ __attribute__((aligned(16))) float As[2][BK * BM];
   __shared__ __attribute__((aligned(16))) float Bs[2][BN * BK];
 
@@ -694,29 +669,29 @@ __global__ __launch_bounds__(64 * NW, OCC) void k_gemm_dl(const GemmProb* __rest
       const bool bm = (b_lu || b_up || b_lo) && k0 + BK > J0 && k0 < J0 + BN;
       if (am || bm) {
         if (am)
-          for (int i = tid; i < BK * BM; i += 64 * NW) {
+          for (int i = tid; i < BK * BM; i += 256) {
             const int k = i / BM, m = i % BM;
             As[st][i] = select_op(As[st][i], I0 + m, k0 + k, a_lu, a_up, a_lo, 1 << 30, 1 << 30);
           }
         if (bm)
-          for (int i = tid; i < BN * BK; i += 64 * NW) {
+          for (int i = tid; i < BN * BK; i += 256) {
             const int n = i / BK, k = 4 * (((i % BK) >> 2) ^ (n & 7)) + (i & 3);
             Bs[st][i] = select_op(Bs[st][i], k0 + k, J0 + n, b_lu, b_up, b_lo, 1 << 30, 1 << 30);
           }
         __syncthreads();
       }
       const int k1 = k0 + BK;
-      int64_t goff[16];
+      int64_t goff[NA + NBI];
 #pragma unroll
       for (int q = 0; q < NA; ++q) goff[q] = a_off(k1, q);
 #pragma unroll
       for (int q = 0; q < NBI; ++q) goff[NA + q] = b_off(k1, q);
-      dl_chunk<SPLIT, BM, BN, NW>(As[st], Bs[st], &As[st ^ 1][wave * NA * 256], &Bs[st ^ 1][wave * NBI * 256], A, B,
-                                  goff, k1 < ke, lane, wm, wn, acc);
+      dl_chunk<SPLIT>(As[st], Bs[st], &As[st ^ 1][wave * NA * 256], &Bs[st ^ 1][wave * NBI * 256], A, B, goff, k1 < ke,
+                      lane, wm, wn, acc);
       st ^= 1;
     }
   }
-  store_tile32<MB, NB>(P, acc, I0 + wm * (BM / 2), J0 + wn * (2 * BN / NW), lane);
+  store_tile32<MB, NB>(P, acc, I0 + wm * (BM / 2), J0 + wn * (BN / 2), lane);
 }
 
 // ------------------------------------------------------------------------
@@ -1124,13 +1099,6 @@ struct X3Wave {
     bh[ni] = *(const bf16x8*)(lds + st * kStage + ni * 8192 + fb);
     if (SPLIT) bl[ni] = *(const bf16x8*)(lds + st * kStage + ni * 8192 + (fb ^ 32));
   }
-  __device__ __forceinline__ void mma(f32x16& c, int mi, int ni) {
-    if (SPLIT) {
-      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bl[ni], ah[mi & 1], c, 0, 0, 0);
-      c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bh[ni], al[mi & 1], c, 0, 0, 0);
-    }
-    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bh[ni], ah[mi & 1], c, 0, 0, 0);
-  }
   __device__ __forceinline__ void sync() {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
@@ -1293,8 +1261,8 @@ void launch_gemm(int dtype, int mode, const GemmProb* probs, int nprob, int nwg,
   const dim3 g(nwg), b(256);
   if (dtype <= 1) {
     if (mode < 0) {
-      if (dtype == 0) hipLaunchKernelGGL((k_gemm_std<double, 64, 64, 16, 2>), g, b, 0, s, probs, nprob, order);
-      else hipLaunchKernelGGL((k_gemm_std<float, 64, 64, 16, 2>), g, b, 0, s, probs, nprob, order);
+      if (dtype == 0) hipLaunchKernelGGL(k_gemm_std<double>, g, b, 0, s, probs, nprob, order);
+      else hipLaunchKernelGGL(k_gemm_std<float>, g, b, 0, s, probs, nprob, order);
     } else if (mode >= 1) {
       if (dtype == 0) hipLaunchKernelGGL((k_gemm_dma<double, 128, 128, 2>), g, b, 0, s, probs, nprob, order);
       else hipLaunchKernelGGL((k_gemm_dma<float, 128, 128, 2>), g, b, 0, s, probs, nprob, order);
@@ -1311,8 +1279,8 @@ void launch_gemm(int dtype, int mode, const GemmProb* probs, int nprob, int nwg,
       else hipLaunchKernelGGL((k_gemm_x3<false>), g, dim3(512), 0, s, probs, nprob, order);
       break;
     case 3:
-      if (split) hipLaunchKernelGGL((k_gemm_dl<true, 128, 128, 4, 2>), g, b, 0, s, probs, nprob, order);
-      else hipLaunchKernelGGL((k_gemm_dl<false, 128, 128, 4, 2>), g, b, 0, s, probs, nprob, order);
+      if (split) hipLaunchKernelGGL(k_gemm_dl<true>, g, b, 0, s, probs, nprob, order);
+      else hipLaunchKernelGGL(k_gemm_dl<false>, g, b, 0, s, probs, nprob, order);
       break;
     case 2:
       if (split) hipLaunchKernelGGL((k_gemm_bf16<true, 256, 128, 1, 2>), g, b, 0, s, probs, nprob, order);

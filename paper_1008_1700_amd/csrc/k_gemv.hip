@@ -493,7 +493,6 @@ __global__ __launch_bounds__(256) void k_tipmv(const GemvProb* __restrict__ prob
       take_sums(F.s1.W, R, j, F.s1.part, F.s1.sums, v1, sh);
       run[j] = s_ok(F.st, F.it, j, v1[0], al[j]);
       any |= run[j];
-      if (blockIdx.x == 0 && threadIdx.x == 0) F.st->alpha[j] = al[j];
     }
     if (!any) return;   // no column goes on: nothing reads s, the product or their sums
   }

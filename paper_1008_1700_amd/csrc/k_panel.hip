@@ -37,6 +37,7 @@
 // it, or not finite, records (block, global row) in *bad through an atomic
 // minimum, so the first bad pivot in (block, row) order is reported.
 #include "ddps_internal.h"
+#include "mma_device.h"
 
 namespace ddps {
 
@@ -67,29 +68,6 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
-
-typedef double f64x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-template <typename T>
-struct Mat;
-// acc(16 x 16) += a b, lane l giving a = A(l % 16, l / 16) and b = B(l / 16, l % 16)
-// of four columns / rows; row of the result's element v in lane l (column l % 16)
-template <>
-struct Mat<double> {
-  typedef f64x4 acc_t;
-  static __device__ __forceinline__ f64x4 mul(double a, double b, f64x4 c) {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int row(int v, int lane) { return 4 * v + (lane >> 4); }
-};
-template <>
-struct Mat<float> {
-  typedef f32x4 acc_t;
-  static __device__ __forceinline__ f32x4 mul(float a, float b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-  }
-  static __device__ __forceinline__ int row(int v, int lane) { return 4 * (lane >> 4) + v; }
-};
 
 }  // namespace
 
@@ -168,29 +146,25 @@ __global__ __launch_bounds__(64 * kW) void k_panel(const PanelProb* __restrict__
   // each 16 lanes alike) column j
   const int o = kB * (w & 3), j = r & 15;
   T x[kB];
-  if (w < 8) {
 #pragma unroll
-    for (int i = 0; i < kB; ++i) x[i] = i == j ? T(1) : T(0);
-    if (w < 4) {
+  for (int i = 0; i < kB; ++i) x[i] = i == j ? T(1) : T(0);
+  if (w < 4) {
 #pragma unroll
-      for (int i = kB - 1; i >= 0; --i) {
-        x[i] *= Rv[o + i];
+    for (int i = kB - 1; i >= 0; --i) {
+      x[i] *= Rv[o + i];
 #pragma unroll
-        for (int m = 0; m < i; ++m) x[m] -= LU[o + m][o + i] * x[i];
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < kB; ++i)
-#pragma unroll
-        for (int m = i + 1; m < kB; ++m) x[m] -= LU[o + m][o + i] * x[i];
+      for (int m = 0; m < i; ++m) x[m] -= LU[o + m][o + i] * x[i];
     }
-  }
-  __syncthreads();   // both triangles of a block are read
-  if (w < 8) {
+  } else {
 #pragma unroll
     for (int i = 0; i < kB; ++i)
-      if (r < kB && (w < 4 ? i <= j : i > j)) LU[o + i][o + j] = x[i];
+#pragma unroll
+      for (int m = i + 1; m < kB; ++m) x[m] -= LU[o + m][o + i] * x[i];
   }
+  __syncthreads();   // both triangles of a block are read
+#pragma unroll
+  for (int i = 0; i < kB; ++i)
+    if (r < kB && (w < 4 ? i <= j : i > j)) LU[o + i][o + j] = x[i];
   __syncthreads();
   // entry (i, k) of the inverse of U (up) or of L on its diagonal blocks
   auto inv = [&](bool up, int i, int k) __attribute__((always_inline)) {
@@ -198,7 +172,7 @@ __global__ __launch_bounds__(64 * kW) void k_panel(const PanelProb* __restrict__
     return (up ? i <= k : i > k) ? v : d;
   };
   const int li = r & 15, lk = r >> 4;
-  typedef typename Mat<T>::acc_t acc_t;
+  typedef typename Mma<T>::acc acc_t;
   // Off-diagonal block at (ro, co) of a triangle whose diagonal blocks start at
   // ro and at co: -inv(ro, ro) F inv(co, co), F the factor's entries there; here
   // the 16 x 16 part at (ti, tj) of blocks of size n, with the inner product in H.
@@ -206,16 +180,16 @@ __global__ __launch_bounds__(64 * kW) void k_panel(const PanelProb* __restrict__
     acc_t h = {};
 #pragma unroll
     for (int s = 0; s < n; s += 4)
-      h = Mat<T>::mul(LU[ro + ti + li][co + s + lk], inv(up, co + s + lk, co + tj + li), h);
+      h = Mma<T>::run(LU[ro + ti + li][co + s + lk], inv(up, co + s + lk, co + tj + li), h);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) H[ti + Mat<T>::row(v, r)][tj + li] = h[v];
+    for (int v = 0; v < 4; ++v) H[ti + Mma<T>::row(r, v)][tj + li] = h[v];
   };
   auto second = [&](bool up, int ro, int co, int n, int ti, int tj, T(*H)[kLdT]) __attribute__((always_inline)) {
     acc_t h = {};
 #pragma unroll
-    for (int s = 0; s < n; s += 4) h = Mat<T>::mul(inv(up, ro + ti + li, ro + s + lk), H[s + lk][tj + li], h);
+    for (int s = 0; s < n; s += 4) h = Mma<T>::run(inv(up, ro + ti + li, ro + s + lk), H[s + lk][tj + li], h);
 #pragma unroll
-    for (int v = 0; v < 4; ++v) LU[ro + ti + Mat<T>::row(v, r)][co + tj + li] = -h[v];
+    for (int v = 0; v < 4; ++v) LU[ro + ti + Mma<T>::row(r, v)][co + tj + li] = -h[v];
   };
   // the 32 x 32 triangles: waves 0 and 1 of U, 2 and 3 of L, first and second
   if (w < 4) {
@@ -232,9 +206,9 @@ __global__ __launch_bounds__(64 * kW) void k_panel(const PanelProb* __restrict__
   {
     const bool up = w < 4;
     const int ro = up ? 0 : 2 * kB, co = up ? 2 * kB : 0, ti = kB * (w >> 1 & 1), tj = kB * (w & 1);
-    if (w < 8) first(up, ro, co, 2 * kB, ti, tj, S.H[w >> 2 & 1]);
+    first(up, ro, co, 2 * kB, ti, tj, S.H[w >> 2 & 1]);
     __syncthreads();
-    if (w < 8) second(up, ro, co, 2 * kB, ti, tj, S.H[w >> 2 & 1]);
+    second(up, ro, co, 2 * kB, ti, tj, S.H[w >> 2 & 1]);
   }
   __syncthreads();
   // U^{-1} on and above the diagonal, L^{-1} strictly below it: each wave

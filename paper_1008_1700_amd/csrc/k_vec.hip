@@ -181,8 +181,6 @@ __global__ void k_bicg_init_state(int k, double tol, const double* __restrict__ 
   const double ref = gg > 0.0 ? sqrt(gg) : 1.0;
   st->ref[j] = ref;
   st->rho[1][j] = rr;
-  st->alpha[j] = 0.0;
-  st->omega[j] = 0.0;
   const double res = sqrt(rr) / ref;
   st->res[j] = res;
   st->iters2[j] = 0;
@@ -204,7 +202,6 @@ __global__ __launch_bounds__(256) void k_bicg_s(int it, int64_t m, int w1, const
   double al, v1[2];
   take_sums(w1, R, j, p1, s1, v1, sh);
   const bool run = s_ok(st, it, j, v1[0], al);
-  if (blockIdx.x == 0 && threadIdx.x == 0) st->alpha[j] = al;
   double acc[1][2] = {{0.0, 0.0}};
   if (run)
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m;
@@ -242,7 +239,6 @@ __global__ __launch_bounds__(256) void k_bicg_xr(int it, int64_t m, double tol, 
   const bool half = ok && sqrt(v2[0]) / st->ref[j] <= tol;
   const bool run = ok && !half;
   const double om = tt != 0.0 ? ts / tt : 0.0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) st->omega[j] = om;
   double acc[1][2] = {{0.0, 0.0}};
   if (half || run)
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m;
