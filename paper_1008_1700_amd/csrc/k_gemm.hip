@@ -7,9 +7,8 @@
 // operands staged through registers), k_gemm_dl (the same bf16 products with
 // the operands copied straight into LDS, split as they are read) and
 // k_gemm_x3 (256 x 256 tiles, split as they are staged); all three give the
-// same bits.  Operands are column-major
-// (LAPACK layout); M and N need only be multiples of 64 (a larger tile on the
-// edge is masked).  Triangular operands are exploited twice: the K range of
+// same bits.  Operands are column-major (LAPACK layout); M and N need only be
+// multiples of 64 (a larger tile on the edge is masked).  Triangular operands are exploited twice: the K range of
 // each output tile is clipped to where both operands can be nonzero, and
 // masks read the unit-lower / upper / lower halves of the packed tiles.
 //
@@ -947,13 +946,14 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_dma(const GemmProb* __restric
 // the problem, or crossing the diagonal of a triangular A, does only the
 // products of the 64-row groups that have any, on all eight waves alike.
 //
-// Bound: power.  A 16-deep step takes about 1970 cycles of the 1536 its
-// products take on the matrix pipe, at a clock of 1.45 GHz instead of 2.4 (the
-// same kernel without the split: 1640 cycles); the energy of a product, not
-// its issue, sets the rate.  32 problems, TF/s of FP32 products, the kernel
-// that split every fragment it read (256 x 256 tiles) -> this one: dense
-// 1600^3 225 -> 277, 2048^2 x 1024 325 -> 383, upper triangle times 1600 x
-// 3200 230 -> 285, rank-256 update of 1344^2 104 -> 161.
+// Bound: the matrix pipe, at the clock that the card holds under it.  32 dense
+// products of 2048^2 x 4096 take 2.9 ms with the pipe busy for 76% of the cycles
+// (about 2020 per 16-deep step, of which the products are 1536) at 1.43 GHz, or
+// 1.57 GHz when they run for seconds (2.6 ms); the f64 and f32 kernels run at 2.38
+// GHz.  That the clock falls points to power, which could not be read.  32
+// problems, TF/s of FP32 products, the kernel that split every fragment it read
+// (256 x 256 tiles) -> this one: dense 1600^3 225 -> 277, 2048^2 x 1024 325 -> 383,
+// upper triangle times 1600 x 3200 230 -> 285, rank-256 update of 1344^2 104 -> 161.
 // ------------------------------------------------------------------------
 // LDS image of one 16-deep K step of one operand: row (column) r holds four
 // 16-byte units, the hi halves of k 0-7 and 8-15, then the lo halves; four

@@ -91,7 +91,10 @@ __global__ __launch_bounds__(kIluThreads) void k_ilu0(const IluBlock* __restrict
 // Bound: one wave's instruction rate (a row is some 150 instructions), so the
 // waves are made small and many; up to 16 share a CU's LDS.  2048 columns of 32
 // blocks of 8192 rows take 5.9 ms, 24.1 ms with a load of every entry in the
-// chain; of 512 blocks 47 and 77 ms.
+// chain; of 512 blocks 47 and 77 ms.  Rows read in place, all of them in a
+// 27-point stencil (13 entries a side), still gain from the smaller waves: a whole
+// factorisation of 20 blocks of 3200 rows 20.0 ms, with every row in place and
+// large waves 27.0, of 32 blocks of 8192 55.3 and 79.8 ms.
 constexpr int kNear = 16, kAhead = 8, kNearMax = 2, kFarMax = 4, kChunk = 32;
 
 template <typename T>
