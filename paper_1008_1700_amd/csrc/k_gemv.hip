@@ -817,10 +817,10 @@ void launch_tipmv(int dtype, int nrhs, int t, const GemvProb* probs, int nprob, 
   hipLaunchKernelGGL((__VA_ARGS__), dim3(nwg), dim3(256), L, s, probs, nprob, nwg, ldx, ldy, dotv, partial, stop)
 #define DDPS_TIPMV_S(T, R, RPW)                                                                                     \
   if (step)                                                                                                         \
-    hipLaunchKernelGGL((k_tipmv<T, R, RPW, true>), dim3(nwg * sb), dim3(256), lds, s, probs, nprob, nwg, ldx, ldy, dotv, \
-                       partial, stop, *step);                                                                       \
+    hipLaunchKernelGGL((k_tipmv<T, R, RPW, true>), dim3(nwg * sb), dim3(256), lds, s, probs, nprob, nwg, ldx, ldy,      \
+                       dotv, partial, stop, *step);                                                                 \
   else                                                                                                              \
-    hipLaunchKernelGGL((k_tipmv<T, R, RPW, false>), dim3(nwg * sb), dim3(256), lds, s, probs, nprob, nwg, ldx, ldy,      \
+    hipLaunchKernelGGL((k_tipmv<T, R, RPW, false>), dim3(nwg * sb), dim3(256), lds, s, probs, nprob, nwg, ldx, ldy,     \
                        dotv, partial, stop, TipStep{})
 #define DDPS_TIPMV_C(T, R)                                            \
   switch (ns) {                                                       \

@@ -424,9 +424,9 @@ __global__ __launch_bounds__(kSolveThreads) void k_ilu_solve(const IluBlock* __r
 //        pivots
 // Rows beyond the first NT of a level are loaded when they are due (from the CSR
 // positions two loads more, which made levels of 2000 to 5000 rows slower than
-// k_ilu_solve for one column: 93 and 88 us a solve, from here 79); entries beyond the
-// fourth of a row are read in place.  Every row's sum is taken in the order of k_ilu_solve, so
-// that both give the same bits.
+// k_ilu_solve for one column: 93 and 88 us a solve, from here 79); entries beyond
+// the fourth of a row are read in place.  Every row's sum is taken in the order of
+// k_ilu_solve, so that both give the same bits.
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 typedef double f64x2_t __attribute__((ext_vector_type(2)));
 
